@@ -1,6 +1,8 @@
 // Graph construction on gfx950: work planning, the pairwise-length
 // compatibility matrix (Eq. 1) and the SC2 weights of the O2Graph
 // (Eq. 2 restricted to i < j, Definition 2) on FP4 MFMA with exact float32 accumulation.
+#include <algorithm>
+
 #include "common.h"
 
 namespace tr {
@@ -132,7 +134,7 @@ __global__ void __launch_bounds__(1024) k_plan(const int32_t *offsets, int32_t n
 {
     constexpr int NV = kNumPrefix + 1;   // the work-list stages, then the SC2 cost
     __shared__ int64_t lds[17][NV];
-    __shared__ int64_t lds1[17][3];
+    __shared__ int64_t lds1[17][2];
     __shared__ int32_t kfirst[kCostKeys];        // pairs per size key, then the key's next free position
     __shared__ int32_t wfirst[16][kCostKeys];    // per wave of a chunk: pairs per key, then first position
     __shared__ int32_t nl[1024], ol[1024];       // B <= 1024: n of each valid pair (0 if invalid); the order
@@ -158,17 +160,16 @@ __global__ void __launch_bounds__(1024) k_plan(const int32_t *offsets, int32_t n
     for (int k = tid; k < kCostKeys; k += blockDim.x) kfirst[k] = 0;
     __syncthreads();
     // pass 1, pair order: descriptors, state, arena offsets, size-key counts, total SC2 cost
-    int64_t acarry = 0, ccarry = 0, sc2_cost = 0;
+    int64_t acarry = 0, sc2_cost = 0;
     for (int base = 0; base < B; base += blockDim.x) {
         const int b = base + tid;
         int32_t n, pt;
         const bool ok = size_of(b, n, pt);
         const int32_t npad = ok ? (n + kSc2Tile - 1) / kSc2Tile * kSc2Tile : 0;
-        int64_t v[3] = {(int64_t)npad * npad, ok ? stage_items(kSc2, n, H) * sc2_unit(npad) : 0,
-                        ok ? npad * c_pitch(npad) : 0}, excl[3], tot[3];
-        block_scan_multi<3>(v, excl, tot, lds1);
+        int64_t v[2] = {(int64_t)npad * npad, ok ? stage_items(kSc2, n, H) * sc2_unit(npad) : 0}, excl[2], tot[2];
+        block_scan_multi<2>(v, excl, tot, lds1);
         if (b < B) {
-            PairDesc d = pair_desc_of(n, pt, excl[0] + acarry, excl[2] + ccarry, pool);
+            PairDesc d = pair_desc_of(n, pt, excl[0] + acarry, pool);
             if (!ok) d.n = d.npad = d.kpiv = 0;
             pairs[b] = d;
             PairState st = {};
@@ -179,7 +180,6 @@ __global__ void __launch_bounds__(1024) k_plan(const int32_t *offsets, int32_t n
         }
         acarry += tot[0];
         sc2_cost += tot[1];
-        ccarry += tot[2];
     }
     __syncthreads();
     if (B < kOrderMinB) {   // a few pairs: slots in pair order
@@ -189,8 +189,8 @@ __global__ void __launch_bounds__(1024) k_plan(const int32_t *offsets, int32_t n
         }
     } else {
         {   // first position of each key, the largest key first
-            int64_t v[3] = {tid < kCostKeys ? kfirst[kCostKeys - 1 - tid] : 0, 0, 0}, excl[3], tot[3];
-            block_scan_multi<3>(v, excl, tot, lds1);
+            int64_t v[2] = {tid < kCostKeys ? kfirst[kCostKeys - 1 - tid] : 0, 0}, excl[2], tot[2];
+            block_scan_multi<2>(v, excl, tot, lds1);
             if (tid < kCostKeys) kfirst[kCostKeys - 1 - tid] = (int32_t)excl[0];
             __syncthreads();
         }
@@ -335,7 +335,7 @@ __device__ __forceinline__ bool near_tau(float la, float lb, float dl, float tau
 // (boundary pairs, edges) go to a per-item slot, so no atomics are needed;
 // non-finite inputs are counted by the diagonal tiles (third slot), which also clear the
 // pair's weight histograms and row maxima for their rows.
-template <bool LEARNED, bool BITS>
+template <bool LEARNED>
 __global__ void __launch_bounds__(256, 2) k_compat(Work w)
 {
     __shared__ float px[2][64][3], py[2][64][3];
@@ -507,16 +507,8 @@ __global__ void __launch_bounds__(256, 2) k_compat(Work w)
         nedge = wave_sum(nedge);
         if (lane == 0) { red[wv][0] = nbnd; red[wv][1] = nedge; red[wv][2] = any_bad; }
         __syncthreads();
-        uint8_t *Cb = w.C + d.cb_off;
-        const int64_t rs = c_pitch(d.npad);
-        const int r = tid >> 2, c8 = (tid & 3) * 8;
-        *reinterpret_cast<uint2 *>(Cb + ((int64_t)bi * kCompatTile + r) * rs + bj * (kCompatTile / 2) + c8) =
-            *reinterpret_cast<const uint2 *>(&tile[0][r * kNibStride + c8]);
-        if (!diag)
-            *reinterpret_cast<uint2 *>(Cb + ((int64_t)bj * kCompatTile + r) * rs + bi * (kCompatTile / 2) + c8) =
-                *reinterpret_cast<const uint2 *>(&tile[1][r * kNibStride + c8]);
-        if (BITS && tid < (diag ? 64 : 128)) {
-            // the same rows as bits (read only by the SC2 bit-count path) (threads 0-63: the tile's rows, 64-127: its transpose), 8 bytes per
+        if (tid < (diag ? 64 : 128)) {
+            // the rows as bits (threads 0-63: the tile's rows, 64-127: its transpose), 8 bytes per
             // row into the 16-byte piece of the row's 128-column block
             const int side = tid >> 6, rr = tid & 63;
             const uint4 *src = reinterpret_cast<const uint4 *>(&tile[side][rr * kNibStride]);
@@ -526,7 +518,7 @@ __global__ void __launch_bounds__(256, 2) k_compat(Work w)
 #pragma unroll
             for (int k = 0; k < 8; ++k) word[k >> 2] |= nibbles_to_bits(nib[k]) << (8 * (k & 3));
             const int rb = side ? bj : bi, cb = side ? bi : bj;
-            uint8_t *dst = w.Cbits + d.c_off / 8 +
+            uint8_t *dst = w.C + d.c_off / 8 +
                            ((int64_t)(cb >> 1) * d.npad + (int64_t)rb * kCompatTile + rr) * 16 + (cb & 1) * 8;
             *reinterpret_cast<uint2 *>(dst) = make_uint2(word[0], word[1]);
         }
@@ -546,31 +538,36 @@ __global__ void __launch_bounds__(256, 2) k_compat(Work w)
 
 // ---------------------------------------------------------------- Eq. 2 on FP4 MFMA
 
-typedef int32_t v4i __attribute__((ext_vector_type(4)));
 typedef int32_t v8i __attribute__((ext_vector_type(8)));
 typedef int32_t v16i __attribute__((ext_vector_type(16)));
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(1))) void gvoid;
 typedef __attribute__((address_space(3))) void lvoid;
 
-constexpr int kBK = 64;                        // bytes of a packed row per pipeline stage (128 k)
-constexpr int kStages = 4;                     // LDS ring depth (three stages in flight)
-constexpr int kMatBytes = kSc2Tile * kBK;      // one operand's stage: 256 rows x 64 bytes
-constexpr int kStageBytes = 2 * kMatBytes;
-constexpr int kRingBytes = kStages * kStageBytes;   // 128 KiB
-constexpr int kTileBytes = kSc2Tile * kSc2Tile * 2;  // the finished tile as uint16 (128 KiB), over the ring
-constexpr int kHistLdsBins = 8192;             // weights below this are histogrammed in LDS first
-constexpr int kSc2Lds = kRingBytes + kHistLdsBins * 4;   // 160 KiB: ring (then tile), histogram
-static_assert(kTileBytes <= kRingBytes, "the finished tile must fit the ring");
+constexpr int kOut = 128;                      // output tile edge: four waves of 64 x 64
+// Weights 1 .. kHistLdsBins are histogrammed in LDS first (weight v in word v - 1). Behind the bins: a
+// spare word per lane of a wave, and the tile's largest weight (two slots used in turn).
+constexpr int kHistLdsBins = 8126;
+constexpr int kHistWords = kHistLdsBins + 64 + 2;
+constexpr int kHistBytes = kHistWords * 4;
+constexpr int kOutPitch = kOut + 8;            // uint16 per LDS row of a tile staged for the column statistics
+constexpr int kOutBytes = kOut * kOutPitch * 2;
 constexpr float kAccBias = 8388608.0f;         // 2^23: a count v < 2^16 is then the low 16 bits of 2^23 + v
-// Bit-count path (tiles with few edges): Eq. 2 is needed only where C_ij = 1, so a tile holding at
-// most kSddmmCap edges counts popcount(row_i AND row_j) for each of its edges instead of forming
-// the dense product (the threshold is a launch parameter up to kSddmmCap; 0 turns the path and the
-// compatibility kernel's bit rows off). Rows arrive in chunks of kChunkKb 128-column blocks (bits),
-// kChunkBufs - 1 chunks in flight; each thread keeps its edges and their counts in registers.
-// LDS layout: the chunk buffers (I rows then J rows, [block][row][16 bytes] each); the edge list
-// lies in the last buffer, which receives no chunk before every thread has its edges.
+// What the epilogue leaves besides the weights: the histogram and row maxima the pivots need, the
+// row sums and maxima the learned features need, or both (a learned registration).
+enum Sc2Mode { kSc2Plain = 0, kSc2Learned = 1, kSc2Features = 2 };
+constexpr int kSc2PerCu = 3;                   // workgroups resident per CU (registers: 168 per lane)
+
+// Bit-count path (tiles with few edges): Eq. 2 is needed only where C_ij = 1, so a 256 x 256 tile
+// holding at most kSddmmCap edges counts popcount(row_i AND row_j) for each of its edges instead of
+// forming the dense product (the threshold is a launch parameter up to kSddmmCap; 0 turns the path
+// off). Rows arrive in chunks of kChunkKb 128-column blocks, kChunkBufs - 1 chunks in flight; each
+// thread keeps its edges and their counts in registers. LDS layout: the chunk buffers (I rows then J
+// rows, [block][row][16 bytes] each); the edge list lies in the last buffer, which receives no chunk
+// before every thread has its edges; then the tile T over all of them, and the histogram behind it.
+constexpr int kTileBytes = kSc2Tile * kSc2Tile * 2;   // the finished tile as uint16 (128 KiB)
 constexpr int kSddmmCap = 8192;                       // 32 edges per thread
 constexpr int kEdgesPerThread = kSddmmCap / 256;
 static_assert(kSddmmCap == TR_SC2_SPARSE_CAP_MAX, "the launch parameter's range is the path's capacity");
@@ -580,8 +577,9 @@ constexpr int kChunkBytes = 2 * kChunkSide;
 constexpr int kChunkBufs = 4;
 constexpr int kEdgeOff = (kChunkBufs - 1) * kChunkBytes;   // edge list: uint16 (i_local << 8 | j_local)
 constexpr int kScanOff = kEdgeOff + 2 * kSddmmCap;    // four wave totals of the edge-count scan
-static_assert(kChunkBufs * kChunkBytes <= kRingBytes && kScanOff + 64 <= kRingBytes,
+static_assert(kChunkBufs * kChunkBytes <= kTileBytes && kScanOff + 64 <= kTileBytes,
               "the bit-count path stays below the histogram");
+constexpr int kSparseLds = kTileBytes + kHistBytes;   // 160 KiB
 
 // Wait until at most N vector-memory loads of this wave are outstanding, then
 // meet the other waves. The memory clobber keeps LDS reads of the new stage
@@ -611,63 +609,346 @@ __device__ __forceinline__ int half_sum(int v)
     return v;
 }
 
-// G[i][j] = C_ij * sum_k C_ik C_jk for i < j < n over 256 x 256 output tiles
-// with bi <= bj. C is symmetric, so the product is C C^T and both MFMA
-// operands are rows of C read along k.
+// A value that is the same on every lane, in scalar registers.
+__device__ __forceinline__ int64_t uniform64(int64_t v)
+{
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+// Exchange of the wave's halves: a' = [a of lanes 0-31, b of lanes 0-31], b' = [a of 32-63, b of 32-63].
+__device__ __forceinline__ void swap_halves(uint32_t &a, uint32_t &b)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+
+// Add the workgroup's LDS histogram of weights 1 .. top into the pair's global copy and clear it.
+// Called by all 256 threads after a barrier.
+__device__ __forceinline__ void hist_flush(int32_t *hist, int32_t *gh, int top)
+{
+    for (int k = threadIdx.x; k < top; k += 256) {
+        const int c = hist[k];
+        if (c) {
+            atomicAdd(&gh[k + 1], c);
+            hist[k] = 0;
+        }
+    }
+}
+
+// hist[k] += 1 as an LDS instruction (through a generic pointer the compiler may emit a flat atomic).
+__device__ __forceinline__ void lds_add(int32_t *hist, uint32_t k)
+{
+    __hip_atomic_fetch_add((__attribute__((address_space(3))) int32_t *)hist + k, 1, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Sums and maxima of the tile's columns (column j of the upper tile is row j of the lower one, the
+// SC2 matrix being symmetric), from the masked tile T[ROWS][pitch] in LDS: thread t takes columns 2c,
+// 2c+1 (c = t mod COLS/2) over rows of one residue class, sixteen 4-byte reads in flight; the classes
+// meet in xl (3 ints per column pair and class). j_base: the tile's first column.
+template <int ROWS, int COLS>
+__device__ __forceinline__ void column_stats(const uint16_t *T, int pitch, int32_t *xl, int32_t *rstat, int j_base)
+{
+    constexpr int kPairs = COLS / 2, kCls = 256 / kPairs;   // column pairs; row classes
+    const int cp = threadIdx.x % kPairs, cls = threadIdx.x / kPairs;
+    const uint32_t *Tw = reinterpret_cast<const uint32_t *>(T);
+    int s0 = 0, s1 = 0;
+    u16x2 mx = {0, 0};
+    for (int m0 = 0; m0 < ROWS / kCls; m0 += 16) {
+        uint32_t v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = Tw[(kCls * (m0 + u) + cls) * (pitch / 2) + cp];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            s0 += (int)(v[u] & 0xFFFFu);
+            s1 += (int)(v[u] >> 16);
+            mx = __builtin_elementwise_max(mx, __builtin_bit_cast(u16x2, v[u]));
+        }
+    }
+    __syncthreads();   // the tile is read (xl may overlie it)
+    if (cls) {
+        int32_t *x = xl + 3 * ((cls - 1) * kPairs + cp);
+        x[0] = s0;
+        x[1] = s1;
+        x[2] = (int32_t)__builtin_bit_cast(uint32_t, mx);
+    }
+    __syncthreads();
+    if (!cls) {
+#pragma unroll
+        for (int c = 1; c < kCls; ++c) {
+            const int32_t *x = xl + 3 * ((c - 1) * kPairs + cp);
+            s0 += x[0];
+            s1 += x[1];
+            mx = __builtin_elementwise_max(mx, __builtin_bit_cast(u16x2, (uint32_t)x[2]));
+        }
+        const int cs[2] = {s0, s1}, cm[2] = {(int)mx.x, (int)mx.y};
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int j = j_base + 2 * cp + e;
+            if (cm[e] > 0) {
+                atomicAdd(&rstat[j * 20 + 1], cs[e]);
+                atomicMax(&rstat[j * 20 + 2], cm[e]);
+            }
+        }
+    }
+}
+
+// One 128 x 128 output tile (bi <= bj in units of 128) of G[i][j] = C_ij sum_k C_ik C_jk, i < j < n,
+// by a workgroup of four waves in a 2 x 2 layout, each a 64 x 64 sub-tile of 2 x 2 blocks of
+// v_mfma_scale_f32_32x32x64_f8f6f4 with FP4 (E2M1) operands. C is symmetric, so the product is C C^T
+// and both operands are rows of C read along k.
 //
-// C is stored as E2M1 (FP4) nibbles, 1.0 = 0x2: every product is 0 or 1 and
-// every partial sum is an integer below 2^24, so the float32 accumulation of
-// v_mfma_scale_f32_32x32x64_f8f6f4 (unit scales) is exact, and FP4 halves the
-// operand bytes of an int8 product. Accumulators start at 2^23, so a finished
-// count is read from the low 16 bits of the float without a conversion.
+// C is stored as bits and becomes FP4 in registers. A lane's 16-byte piece of a row (128 k) holds
+// bit p of every nibble p = 0..3; the four operands (w & 0x1111.., w & 0x2222.., w & 0x4444..,
+// (w >> 3) & 0x1111..) are then E2M1 0.5, 1, 2 and 0.5 where the bit is set, and the E8M0 block
+// scales (x 2, 1, 1/2, 2 on each side) make every product 0 or 1. Which k a nibble stands for does
+// not matter as both operands take the same order. Every partial sum is an integer below 2^24, so
+// the float32 accumulation is exact. Accumulators start at 2^23: a finished count is the low 16 bits
+// of the float. Operands come straight from L2 in whole 512-byte runs (lanes 0-31 the 32 rows' piece
+// of one 128-column block, lanes 32-63 of the next), two steps of 256 k in flight, with no LDS and no
+// barrier in the loop: a quarter of the bytes of nibbles in memory, and the epilogue of one
+// workgroup runs under the products of the CU's other ones. At N = 5000 the kernel takes 33.6 us
+// (58.3 with 256 x 256 tiles fed as nibbles through an LDS ring, one workgroup per CU), at N = 1000
+// 7.0 (29.6), at N = 20000 1220 (1890): 6.6 PFLOP/s of the 7.8 that FP4 products alone sustain here.
+// Four workgroups per CU (128 registers) changed nothing; the rest at N = 5000 is the last, partly
+// filled round of tiles (820 tiles over 256 CUs) and 4.5 us of stores of the weights.
 //
-// Four waves in a 2 x 2 layout each own a 128 x 128 sub-tile as 4 x 4 blocks
-// of 32 x 32 (accumulators in AGPRs). Stages of 64 bytes (128 k) arrive by
-// direct global->LDS 16-byte loads into a four-deep ring, three stages in
-// flight (a fifth stage in flight measured slower); a row's four 16-byte chunks are stored XOR-swizzled by (row/4) mod 4
-// for the fragment reads (ds_read_b128). Work items are split into 8
-// contiguous ranges, one per XCD, so tiles that share rows of C share an L2.
-//
-// Epilogue: the tile is restaged in LDS as uint16 (weights are below 2^16),
-// then read row-major: masked by C_ij and i < j < n, stored with 16-byte
-// writes (whole chunks: outside i < j < n they hold zeros, which nothing reads), counted into a weight histogram (LDS, added into one of
-// kHistGroups copies per pair) and reduced into the per-row maximum of the
-// upper triangle. In learned mode it also adds row and column sums / maxima
-// of the symmetric SC2 matrix for the per-match features.
-template <bool LEARNED, bool SPARSE>
-__global__ void __launch_bounds__(256, 1) k_sc2(Work w)
+// The operands are swapped (A: rows j, B: rows i), so a lane's 16 accumulators of a block are one row
+// i; two swaps between the wave's halves make them two runs of eight consecutive columns. Each run
+// is masked by the row's bits of C, stored with one 16-byte write (whole runs: outside i < j < n they
+// hold zeros, which nothing reads), counted into the LDS weight histogram and reduced into the row
+// maximum.
+template <int MODE>
+__device__ __forceinline__ void sc2_dense_tile(const Work &w, const PairDesc &d, int b, int bi, int bj, int copy,
+                                               int32_t *hist, int32_t *tmax, uint16_t *T)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, wm = wv >> 1, wn = wv & 1;
+    const int l31 = lane & 31, lh = lane >> 5;
+    const uint8_t *Cb = w.C + uniform64(d.c_off) / 8;
+    const uint32_t kbs = (uint32_t)__builtin_amdgcn_readfirstlane(d.npad) * 16;   // bytes of one 128-column block over all rows
+    const int ns = (int)(kbs >> 12);              // steps of 256 k
+    const int i0 = bi * kOut + wm * 64, j0 = bj * kOut + wn * 64;
+    const uint32_t oj = lh * kbs + (uint32_t)(j0 + l31) * 16, oi = lh * kbs + (uint32_t)(i0 + l31) * 16;
+    // the rows' bits of C over the wave's 64 columns (block bj), used after the products
+    const auto rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(Cb), 0, kbs * (uint32_t)(2 * ns), 0x00027000);
+    uint2 cm[2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+        cm[x] = *reinterpret_cast<const uint2 *>(Cb + (uint32_t)bj * kbs + (uint32_t)(i0 + 32 * x + l31) * 16 + wn * 8);
+    v16f acc[2][2];   // [i block][j block]
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[x][y][r] = kAccBias;
+    // (buffer loads: the step is a scalar offset, and steps past the last read zeros)
+    auto load = [&](int s, v4u (&fj)[2], v4u (&fi)[2]) {
+        const int so = s * (int)(2 * kbs);
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+            fj[y] = __builtin_amdgcn_raw_buffer_load_b128(rows, oj + y * 512, so, 0);
+            fi[y] = __builtin_amdgcn_raw_buffer_load_b128(rows, oi + y * 512, so, 0);
+        }
+    };
+    auto step = [&](const v4u (&fj)[2], const v4u (&fi)[2]) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const uint32_t m = t == 1 ? 0x22222222u : t == 2 ? 0x44444444u : 0x11111111u;
+            const int sh = t == 3 ? 3 : 0, scale = t == 1 ? 127 : t == 2 ? 126 : 128;
+            v8i a[2], c[2];
+#pragma unroll
+            for (int y = 0; y < 2; ++y) {
+                a[y] = v8i{(int)((fj[y].x >> sh) & m), (int)((fj[y].y >> sh) & m), (int)((fj[y].z >> sh) & m),
+                           (int)((fj[y].w >> sh) & m), 0, 0, 0, 0};
+                c[y] = v8i{(int)((fi[y].x >> sh) & m), (int)((fi[y].y >> sh) & m), (int)((fi[y].z >> sh) & m),
+                           (int)((fi[y].w >> sh) & m), 0, 0, 0, 0};
+            }
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int y = 0; y < 2; ++y)
+                    acc[x][y] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a[y], c[x], acc[x][y], 4, 4, 0, scale,
+                                                                                 0, scale);
+        }
+    };
+    v4u j_a[2], i_a[2], j_b[2], i_b[2];
+    load(0, j_a, i_a);
+    load(1, j_b, i_b);
+    int s = 0;
+    for (; s + 1 < ns; s += 2) {
+        step(j_a, i_a);
+        load(s + 2, j_a, i_a);
+        __builtin_amdgcn_sched_barrier(0);   // keep the two steps' loads apart: one is always in flight
+        step(j_b, i_b);
+        load(s + 3, j_b, i_b);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (s < ns) step(j_a, i_a);
+    // ---- epilogue: lane (l31, lh) of block (x, y) holds row i0 + 32x + l31 and, after the swaps, columns
+    // j0 + 32y + 16q + 8 lh .. + 7 for q = 0, 1
+    int32_t *gh = w.ghist + ((int64_t)b * kHistGroups + copy) * w.hist_stride;
+    int32_t *rowmax = w.rowmax + (int64_t)b * w.max_n;
+    int32_t *rstat = w.rowstat + (int64_t)b * w.max_n * 20;
+    uint16_t *Gb = w.G + d.g_off;
+    const bool small_n = d.n <= kHistLdsBins + 1;
+    const uint32_t spare = kHistLdsBins + lane;
+    int wmax = 0;
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+        const int i = i0 + 32 * x + l31;
+        u16x2 rm = {0, 0};
+        int rs = 0;
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+            uint32_t cw = y ? cm[x].y : cm[x].x;   // C_ij of columns j0 + 32y + e at bit e
+            if (bi == bj) {                        // i < j only
+                const int k = i - (j0 + 32 * y);
+                cw &= k < 0 ? 0xFFFFFFFFu : k >= 31 ? 0u : 0xFFFFFFFEu << k;
+            }
+            cw >>= 8 * lh;
+            const v16i ai = __builtin_bit_cast(v16i, acc[x][y]);
+            uint32_t p[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) p[k] = __builtin_amdgcn_perm(ai[2 * k + 1], ai[2 * k], 0x05040100);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                uint32_t o[4] = {p[4 * q], p[4 * q + 1], p[4 * q + 2], p[4 * q + 3]};
+                swap_halves(o[0], o[2]);
+                swap_halves(o[1], o[3]);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const uint32_t lo = (uint32_t)((int32_t)(cw << (31 - 16 * q - 2 * k)) >> 31);
+                    const uint32_t hi = (uint32_t)((int32_t)(cw << (30 - 16 * q - 2 * k)) >> 31);
+                    o[k] &= (lo & 0xFFFFu) | (hi & 0xFFFF0000u);
+                    rm = __builtin_elementwise_max(rm, __builtin_bit_cast(u16x2, o[k]));
+                    if (MODE != kSc2Plain) rs += (int)((o[k] & 0xFFFFu) + (o[k] >> 16));
+                }
+                const int jc = j0 + 32 * y + 16 * q + 8 * lh;
+                *reinterpret_cast<uint4 *>(Gb + (int64_t)i * d.npad + jc) = make_uint4(o[0], o[1], o[2], o[3]);
+                if (MODE != kSc2Plain)
+                    *reinterpret_cast<uint4 *>(&T[(wm * 64 + 32 * x + l31) * kOutPitch + jc - bj * kOut]) =
+                        make_uint4(o[0], o[1], o[2], o[3]);
+                if (MODE != kSc2Features) {
+                    // no branch: a zero entry (v - 1 wraps) and one past the LDS bins count in the lane's
+                    // own spare word, so zeros do not queue at one address
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        lds_add(hist, min((o[k] & 0xFFFFu) - 1u, spare));
+                        lds_add(hist, min((o[k] >> 16) - 1u, spare));
+                    }
+                    if (!small_n) {   // the same on the whole workgroup
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            if ((o[k] & 0xFFFFu) > kHistLdsBins) atomicAdd(&gh[o[k] & 0xFFFFu], 1);
+                            if ((o[k] >> 16) > kHistLdsBins) atomicAdd(&gh[o[k] >> 16], 1);
+                        }
+                    }
+                }
+            }
+        }
+        uint32_t m0 = (uint32_t)max((int)rm.x, (int)rm.y), m1 = m0;
+        swap_halves(m0, m1);
+        const int m = max((int)m0, (int)m1);
+        wmax = max(wmax, m);
+        if (MODE != kSc2Plain) {
+            uint32_t r0 = (uint32_t)rs, r1 = r0;
+            swap_halves(r0, r1);
+            rs = (int)(r0 + r1);
+        }
+        if (lh == 0 && m > 0) {   // m > 0 only in rows below n
+            if (MODE != kSc2Features) atomicMax(&rowmax[i], m);
+            if (MODE != kSc2Plain) {
+                atomicAdd(&rstat[i * 20 + 1], rs);
+                atomicMax(&rstat[i * 20 + 2], m);
+            }
+        }
+    }
+    if (MODE != kSc2Features) {
+        wmax = half_max(wmax);   // both halves of the wave hold the same rows
+        if (lane == 31) atomicMax(tmax, wmax);
+    }
+    __syncthreads();   // T, the histogram and the tile's maximum are complete
+    if (MODE != kSc2Features) hist_flush(hist, gh, min(*tmax, kHistLdsBins));
+    if (MODE != kSc2Plain) column_stats<kOut, kOut>(T, kOutPitch, reinterpret_cast<int32_t *>(T), rstat, bj * kOut);
+}
+
+// This workgroup's share of the SC2 list in 256 x 256 tiles: XCD x takes a contiguous range of the
+// list (neighbouring tiles share rows of C in its L2): equal counts for one pair, equal shares of the
+// modelled cost for a batch.
+__device__ __forceinline__ void sc2_range(const Work &w, int &start, int &end)
+{
+    const int xcd = blockIdx.x & 7;
+    if (w.n1) {
+        const int total = stage_total(w, kSc2), chunk = (total + 7) >> 3;
+        start = xcd * chunk;
+        end = min(total, start + chunk);
+    } else {
+        start = w.plan->sc2_split[xcd];
+        end = w.plan->sc2_split[xcd + 1];
+    }
+}
+
+// Dense product of every tile: a work item is one 128 x 128 quadrant of a list tile (quadrants below
+// the diagonal or past n are skipped).
+template <int MODE>
+__global__ void __launch_bounds__(256, MODE == kSc2Plain ? kSc2PerCu : 2) k_sc2(Work w)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    int32_t *hist = reinterpret_cast<int32_t *>(smem + kRingBytes);   // zero outside the epilogue
-    uint16_t *T = reinterpret_cast<uint16_t *>(smem);
-    const int total = stage_total(w, kSc2);
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, wm = wv >> 1, wn = wv & 1;
-    const int xcd = blockIdx.x & 7, nx = (gridDim.x - xcd + 7) >> 3, lb = blockIdx.x >> 3;
-    // XCD x takes a contiguous range of the list (neighbouring tiles share rows of C in its L2):
-    // equal counts for one pair, equal shares of the modelled cost for a batch
-    const int chunk = (total + 7) >> 3;
-    const int start = w.n1 ? xcd * chunk : w.plan->sc2_split[xcd];
-    const int end = w.n1 ? min(total, (xcd + 1) * chunk) : w.plan->sc2_split[xcd + 1];
-    // fragment read offsets inside a stage: row (lane & 31) of a 32-row block, chunk (ks*2 + lane/32)
-    const int frow = lane & 31, fsw = (frow >> 2) & 3;
-    const int foff0 = frow * kBK + 16 * ((lane >> 5) ^ fsw), foff1 = frow * kBK + 16 * ((2 + (lane >> 5)) ^ fsw);
-    for (int k = tid; k < kHistLdsBins; k += 256) hist[k] = 0;
+    int32_t *hist = reinterpret_cast<int32_t *>(smem), *tmax = hist + kHistWords - 2;   // zero outside the epilogue
+    uint16_t *T = reinterpret_cast<uint16_t *>(smem + (MODE == kSc2Features ? 0 : kHistBytes));
+    int start, end;
+    sc2_range(w, start, end);
+    const int nx = (gridDim.x - (blockIdx.x & 7) + 7) >> 3;
+    if (MODE != kSc2Features)
+        for (int k = threadIdx.x; k < kHistWords / 4; k += 256) reinterpret_cast<int4 *>(hist)[k] = make_int4(0, 0, 0, 0);
     __syncthreads();
-    for (int item = start + lb; item < end; item += nx) {
+    int par = 0;
+    for (int it = 4 * start + (blockIdx.x >> 3); it < 4 * end; it += nx) {
+        int local;
+        const int b = stage_pair(w, kSc2, it >> 2, local);
+        const PairDesc d = pair_desc(w, b);
+        int bi, bj;
+        super_decode(local, d.npad / kSc2Tile, w.sc2_super, bi, bj);
+        bi = __builtin_amdgcn_readfirstlane(2 * bi + ((it >> 1) & 1));
+        bj = __builtin_amdgcn_readfirstlane(2 * bj + (it & 1));
+        if (bi > bj || bj * kOut >= d.n) continue;   // the same for the whole workgroup
+        sc2_dense_tile<MODE>(w, d, b, bi, bj, (4 * local + (it & 3)) % kHistGroups, hist, &tmax[par], T);
+        if (MODE != kSc2Features && threadIdx.x == 0) tmax[par ^ 1] = 0;   // read before this tile's barrier, written after the next
+        par ^= 1;
+        __syncthreads();   // the histogram is clear, T is the next item's
+    }
+}
+
+// The same list with the bit-count path for tiles of at most w.sc2_sparse_cap edges; the others take
+// the dense product, quadrant by quadrant.
+template <int MODE>
+__global__ void __launch_bounds__(256, 1) k_sc2_sparse(Work w)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    int32_t *hist = reinterpret_cast<int32_t *>(smem + kTileBytes), *tmax = hist + kHistWords - 2;   // zero outside the epilogue
+    uint16_t *T = reinterpret_cast<uint16_t *>(smem);
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    int start, end;
+    sc2_range(w, start, end);
+    const int nx = (gridDim.x - (blockIdx.x & 7) + 7) >> 3;
+    for (int k = tid; k < kHistWords / 4; k += 256) reinterpret_cast<int4 *>(hist)[k] = make_int4(0, 0, 0, 0);
+    __syncthreads();
+    int par = 0;
+    for (int item = start + (blockIdx.x >> 3); item < end; item += nx) {
         int local;
         const int b = stage_pair(w, kSc2, item, local);
         const PairDesc d = pair_desc(w, b);
         int bi, bj;
         super_decode(local, d.npad / kSc2Tile, w.sc2_super, bi, bj);
-        const uint8_t *Cb = w.C + d.cb_off;
-        const int64_t rs = c_pitch(d.npad);          // row pitch
-        const int nk = (int)(d.npad / 2 / kBK);      // stages over the packed row
         // ---- the tile's edges: thread t holds row t of the I block over the tile's 256 columns
-        const uint8_t *Cbit = w.Cbits + d.c_off / 8;
+        const uint8_t *Cbit = w.C + d.c_off / 8;
         const int64_t kbs = (int64_t)d.npad * 16;   // bytes of one 128-column block over all rows
         const bool diag = bi == bj;
-        uint32_t mw[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        if (SPARSE) {
+        uint32_t mw[8];
+        {
             const int64_t ro = ((int64_t)bi * kSc2Tile + tid) * 16;
             const uint4 m0 = *reinterpret_cast<const uint4 *>(Cbit + (2 * bj) * kbs + ro);
             const uint4 m1 = *reinterpret_cast<const uint4 *>(Cbit + (2 * bj + 1) * kbs + ro);
@@ -675,411 +956,198 @@ __global__ void __launch_bounds__(256, 1) k_sc2(Work w)
             mw[4] = m1.x; mw[5] = m1.y; mw[6] = m1.z; mw[7] = m1.w;
         }
         int ecount = 0, eprefix = 0, etotal = 0;
-        bool sparse = false;
-        if (SPARSE) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            if (diag) {   // i < j only: columns above the thread's row
+                const int lo = tid + 1 - 32 * k;
+                mw[k] &= lo <= 0 ? 0xFFFFFFFFu : (lo >= 32 ? 0u : (0xFFFFFFFFu << lo));
+            }
+            ecount += __builtin_popcount(mw[k]);
+        }
+        int32_t *scanL = reinterpret_cast<int32_t *>(smem + kScanOff);
+        eprefix = ecount;   // inclusive scan inside the wave, then the waves before
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(eprefix, o, 64);
+            if (lane >= o) eprefix += y;
+        }
+        if (lane == 63) scanL[wv] = eprefix;
+        __syncthreads();
+        etotal = scanL[0] + scanL[1] + scanL[2] + scanL[3];
+        for (int v = 0; v < wv; ++v) eprefix += scanL[v];
+        eprefix -= ecount;   // exclusive
+        if (etotal > w.sc2_sparse_cap) {
+            __syncthreads();   // scanL is read
+            for (int q = 0; q < 4; ++q) {
+                const int ti = __builtin_amdgcn_readfirstlane(2 * bi + (q >> 1)), tj = __builtin_amdgcn_readfirstlane(2 * bj + (q & 1));
+                if (ti > tj || tj * kOut >= d.n) continue;
+                sc2_dense_tile<MODE>(w, d, b, ti, tj, (4 * local + q) % kHistGroups, hist, &tmax[par], T);
+                if (tid == 0) tmax[par ^ 1] = 0;
+                par ^= 1;
+                __syncthreads();
+            }
+            continue;
+        }
+        int32_t *gh = w.ghist + ((int64_t)b * kHistGroups + local % kHistGroups) * w.hist_stride;
+        uint16_t *edgeL = reinterpret_cast<uint16_t *>(smem + kEdgeOff);
+        {
+            int pos = eprefix;
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                if (diag) {   // i < j only: columns above the thread's row
-                    const int lo = tid + 1 - 32 * k;
-                    mw[k] &= lo <= 0 ? 0xFFFFFFFFu : (lo >= 32 ? 0u : (0xFFFFFFFFu << lo));
+                uint32_t x = mw[k];
+                while (x) {
+                    const int c = __builtin_ctz(x);
+                    x &= x - 1;
+                    edgeL[pos] = (uint16_t)((tid << 8) | (32 * k + c));
+                    ++pos;
                 }
-                ecount += __builtin_popcount(mw[k]);
             }
-            int32_t *scanL = reinterpret_cast<int32_t *>(smem + kScanOff);
-            eprefix = ecount;   // inclusive scan inside the wave, then the waves before
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int y = __shfl_up(eprefix, o, 64);
-                if (lane >= o) eprefix += y;
-            }
-            if (lane == 63) scanL[wv] = eprefix;
-            __syncthreads();
-            etotal = scanL[0] + scanL[1] + scanL[2] + scanL[3];
-            for (int v = 0; v < wv; ++v) eprefix += scanL[v];
-            eprefix -= ecount;   // exclusive
-            sparse = etotal <= w.sc2_sparse_cap;
         }
-        if (sparse) {
-            uint16_t *edgeL = reinterpret_cast<uint16_t *>(smem + kEdgeOff);
-            {
-                int pos = eprefix;
+        __syncthreads();   // the edge list is complete
+        // thread t counts edges [e0, e1): about etotal / 256 consecutive edges (few rows each),
+        // held in registers with their counts
+        const int q = (etotal + 255) >> 8, e0 = min(etotal, tid * q), e1 = min(etotal, e0 + q), ne = e1 - e0;
+        uint32_t myv[kEdgesPerThread];
+        int myc[kEdgesPerThread];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    uint32_t x = mw[k];
-                    while (x) {
-                        const int c = __builtin_ctz(x);
-                        x &= x - 1;
-                        edgeL[pos] = (uint16_t)((tid << 8) | (32 * k + c));
-                        ++pos;
-                    }
-                }
-            }
-            __syncthreads();   // the edge list is complete
-            // thread t counts edges [e0, e1): about etotal / 256 consecutive edges (few rows each),
-            // held in registers with their counts
-            const int q = (etotal + 255) >> 8, e0 = min(etotal, tid * q), e1 = min(etotal, e0 + q), ne = e1 - e0;
-            uint32_t myv[kEdgesPerThread];
-            int myc[kEdgesPerThread];
-#pragma unroll
-            for (int k = 0; k < kEdgesPerThread; ++k) {
-                myv[k] = k < ne ? edgeL[e0 + k] : 0u;
-                myc[k] = 0;
-            }
-            __syncthreads();   // the edge list's buffer may now receive a chunk
-            const int nkb = d.npad / 128, nch = (nkb + kChunkKb - 1) / kChunkKb;
-            // chunk c: blocks kChunkKb c .. of the I rows (and J rows off the diagonal) by direct
-            // global->LDS 16-byte loads; wave v loads rows 64v .. 64v+63 of each block
-            auto issue_chunk = [&](int c) {
-                uint8_t *dst = smem + (c % kChunkBufs) * kChunkBytes + wv * 1024;
-#pragma unroll
-                for (int side = 0; side < 2; ++side) {
-                    if (side && diag) break;
-                    const int64_t ro = ((int64_t)(side ? bj : bi) * kSc2Tile + wv * 64 + lane) * 16;
-#pragma unroll
-                    for (int kb = 0; kb < kChunkKb; ++kb)   // past the last block: a copy of it, not counted
-                        __builtin_amdgcn_global_load_lds((gvoid *)(Cbit + (int64_t)min(c * kChunkKb + kb, nkb - 1) * kbs + ro),
-                                                         (lvoid *)(dst + side * kChunkSide + kb * 4096), 16, 0, 0);
-                }
-            };
-            const int lpc = (diag ? 1 : 2) * kChunkKb;   // loads per chunk and lane
-            const int nrun = etotal > 0 ? nch : 0;
-            for (int c = 0; c < min(nrun, kChunkBufs - 1); ++c) issue_chunk(c);
-            for (int c = 0; c < nrun; ++c) {
-                // chunk c has landed once at most (chunks issued after it) x lpc loads are outstanding;
-                // the barrier also tells every wave that chunk c - 1's buffer is free
-                const int outstanding = min(kChunkBufs - 2, nrun - 1 - c) * lpc;
-                switch (outstanding) {
-                case 16: SC2_WAIT_BARRIER(16); break;
-                case 12: SC2_WAIT_BARRIER(12); break;
-                case 8: SC2_WAIT_BARRIER(8); break;
-                case 6: SC2_WAIT_BARRIER(6); break;
-                case 4: SC2_WAIT_BARRIER(4); break;
-                case 2: SC2_WAIT_BARRIER(2); break;
-                default: SC2_WAIT_BARRIER(0); break;
-                }
-                if (c + kChunkBufs - 1 < nrun) issue_chunk(c + kChunkBufs - 1);
-                const uint8_t *Ib = smem + (c % kChunkBufs) * kChunkBytes, *Jb = diag ? Ib : Ib + kChunkSide;
-                const int kbn = min(kChunkKb, nkb - c * kChunkKb);
-                int cur = -1;
-                uint4 ri[kChunkKb];
-                constexpr int kU = 2;   // edges whose J rows are read together
-#pragma unroll
-                for (int k0 = 0; k0 < kEdgesPerThread; k0 += kU) {
-                    if (k0 >= ne) continue;   // (not break: the loop must unroll, the arrays stay in registers)
-                    uint4 rj[kU][kChunkKb];
-#pragma unroll
-                    for (int u = 0; u < kU; ++u)
-#pragma unroll
-                        for (int kb = 0; kb < kChunkKb; ++kb)
-                            rj[u][kb] = k0 + u < ne && kb < kbn
-                                            ? *reinterpret_cast<const uint4 *>(Jb + kb * 4096 + (myv[k0 + u] & 255) * 16)
-                                            : make_uint4(0, 0, 0, 0);
-#pragma unroll
-                    for (int u = 0; u < kU; ++u) {
-                        const int li = (int)(myv[k0 + u] >> 8);
-                        if (k0 + u < ne && li != cur) {
-                            cur = li;
-#pragma unroll
-                            for (int kb = 0; kb < kChunkKb; ++kb) ri[kb] = *reinterpret_cast<const uint4 *>(Ib + kb * 4096 + li * 16);
-                        }
-                        int sum = 0;
-#pragma unroll
-                        for (int kb = 0; kb < kChunkKb; ++kb)
-                            sum += __builtin_popcount(ri[kb].x & rj[u][kb].x) + __builtin_popcount(ri[kb].y & rj[u][kb].y) +
-                                   __builtin_popcount(ri[kb].z & rj[u][kb].z) + __builtin_popcount(ri[kb].w & rj[u][kb].w);
-                        myc[k0 + u] += k0 + u < ne ? sum : 0;
-                    }
-                }
-            }
-            // the LDS becomes the tile T (zero, then the counts scattered in; weights below 2^16)
-            __syncthreads();
-            for (int k = tid; k < kTileBytes / 16; k += 256) reinterpret_cast<uint4 *>(smem)[k] = make_uint4(0, 0, 0, 0);
-            __syncthreads();
-            int32_t *ghs = w.ghist + ((int64_t)b * kHistGroups + local % kHistGroups) * w.hist_stride;
-            const bool small_hist = d.n <= kHistLdsBins;
-#pragma unroll
-            for (int k = 0; k < kEdgesPerThread; ++k) {
-                if (k < ne) {
-                    T[(myv[k] >> 8) * kSc2Tile + (myv[k] & 255)] = (uint16_t)myc[k];
-                    const int c = myc[k];
-                    if (c > 0) {   // the weight histogram counts nonzero weights
-                        if (small_hist || c < kHistLdsBins) atomicAdd(&hist[c], 1);
-                        else atomicAdd(&ghs[c], 1);
-                    }
-                }
-            }
-            __syncthreads();
-        } else {
-        // load s of a stage: row r = (s&3)*64 + wv*16 + lane/4 of operand s/4 into LDS chunk lane&3,
-        // which holds the row's global chunk (lane&3) ^ ((r/4)&3)
-        uint32_t goff[8];
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            const int r = (s & 3) * 64 + wv * 16 + (lane >> 2);
-            const int64_t row = (int64_t)((s >> 2) ? bj : bi) * kSc2Tile + r;
-            goff[s] = (uint32_t)(row * rs + 16 * ((lane & 3) ^ ((r >> 2) & 3)));
+        for (int k = 0; k < kEdgesPerThread; ++k) {
+            myv[k] = k < ne ? edgeL[e0 + k] : 0u;
+            myc[k] = 0;
         }
-        auto issue = [&](int kt) {
-            uint8_t *dst = smem + (kt % kStages) * kStageBytes + wv * 1024;
-            const uint8_t *src = Cb + (int64_t)kt * kBK;
+        __syncthreads();   // the edge list's buffer may now receive a chunk
+        const int nkb = d.npad / 128, nch = (nkb + kChunkKb - 1) / kChunkKb;
+        // chunk c: blocks kChunkKb c .. of the I rows (and J rows off the diagonal) by direct
+        // global->LDS 16-byte loads; wave v loads rows 64v .. 64v+63 of each block
+        auto issue_chunk = [&](int c) {
+            uint8_t *dst = smem + (c % kChunkBufs) * kChunkBytes + wv * 1024;
 #pragma unroll
-            for (int s = 0; s < 8; ++s)
-                __builtin_amdgcn_global_load_lds((gvoid *)(src + goff[s]),
-                                                 (lvoid *)(dst + (s >> 2) * kMatBytes + (s & 3) * 4096), 16, 0, 0);
+            for (int side = 0; side < 2; ++side) {
+                if (side && diag) break;
+                const int64_t ro = ((int64_t)(side ? bj : bi) * kSc2Tile + wv * 64 + lane) * 16;
+#pragma unroll
+                for (int kb = 0; kb < kChunkKb; ++kb)   // past the last block: a copy of it, not counted
+                    __builtin_amdgcn_global_load_lds((gvoid *)(Cbit + (int64_t)min(c * kChunkKb + kb, nkb - 1) * kbs + ro),
+                                                     (lvoid *)(dst + side * kChunkSide + kb * 4096), 16, 0, 0);
+            }
         };
-        v16f acc[4][4];
-#pragma unroll
-        for (int x = 0; x < 4; ++x)
-#pragma unroll
-            for (int y = 0; y < 4; ++y)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[x][y][r] = kAccBias;
-#pragma unroll
-        for (int kt = 0; kt < kStages - 1; ++kt)
-            if (kt < nk) issue(kt);
-        for (int kt = 0; kt < nk; ++kt) {
-            // stage kt has landed once at most (stages issued after it) x 8 loads are outstanding
-            const int later = min(kStages - 2, nk - 1 - kt);
-            if (later >= 2) SC2_WAIT_BARRIER(16);
-            else if (later == 1) SC2_WAIT_BARRIER(8);
-            else SC2_WAIT_BARRIER(0);
-            if (kt + kStages - 1 < nk) issue(kt + kStages - 1);
-            const uint8_t *As = smem + (kt % kStages) * kStageBytes, *Bs = As + kMatBytes;
-            // fragment reads run ahead of the MFMAs that use them: the eight of the first half and
-            // the four A fragments of the second are issued before the first MFMA, the four B
-            // fragments of the second half after the first row of four MFMAs (at most twelve LDS
-            // reads outstanding, below the counter's limit); the scheduling barriers keep this order
-            v4i fa[2][4], fb[2][4];
-            auto mfma_row = [&](int ks, int x) {
-#pragma unroll
-                for (int y = 0; y < 4; ++y) {
-                    // 32 FP4 values of k per lane: 16 bytes, the upper half of the operand is unused
-                    const v8i a8 = {fa[ks][x][0], fa[ks][x][1], fa[ks][x][2], fa[ks][x][3], 0, 0, 0, 0};
-                    const v8i b8 = {fb[ks][y][0], fb[ks][y][1], fb[ks][y][2], fb[ks][y][3], 0, 0, 0, 0};
-                    acc[x][y] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a8, b8, acc[x][y], 4, 4, 0, 127, 0,
-                                                                                 127);
-                }
-            };
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                fa[0][x] = *reinterpret_cast<const v4i *>(As + (wm * 128 + x * 32) * kBK + foff0);
-                fb[0][x] = *reinterpret_cast<const v4i *>(Bs + (wn * 128 + x * 32) * kBK + foff0);
+        const int lpc = (diag ? 1 : 2) * kChunkKb;   // loads per chunk and lane
+        const int nrun = etotal > 0 ? nch : 0;
+        for (int c = 0; c < min(nrun, kChunkBufs - 1); ++c) issue_chunk(c);
+        for (int c = 0; c < nrun; ++c) {
+            // chunk c has landed once at most (chunks issued after it) x lpc loads are outstanding;
+            // the barrier also tells every wave that chunk c - 1's buffer is free
+            const int outstanding = min(kChunkBufs - 2, nrun - 1 - c) * lpc;
+            switch (outstanding) {
+            case 16: SC2_WAIT_BARRIER(16); break;
+            case 8: SC2_WAIT_BARRIER(8); break;
+            case 4: SC2_WAIT_BARRIER(4); break;
+            default: SC2_WAIT_BARRIER(0); break;
             }
-            __builtin_amdgcn_sched_barrier(0);
+            if (c + kChunkBufs - 1 < nrun) issue_chunk(c + kChunkBufs - 1);
+            const uint8_t *Ib = smem + (c % kChunkBufs) * kChunkBytes, *Jb = diag ? Ib : Ib + kChunkSide;
+            const int kbn = min(kChunkKb, nkb - c * kChunkKb);
+            int cur = -1;
+            uint4 ri[kChunkKb];
+            constexpr int kU = 2;   // edges whose J rows are read together
 #pragma unroll
-            for (int x = 0; x < 4; ++x) fa[1][x] = *reinterpret_cast<const v4i *>(As + (wm * 128 + x * 32) * kBK + foff1);
-            __builtin_amdgcn_sched_barrier(0);
-            mfma_row(0, 0);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int k0 = 0; k0 < kEdgesPerThread; k0 += kU) {
+                if (k0 >= ne) continue;   // (not break: the loop must unroll, the arrays stay in registers)
+                uint4 rj[kU][kChunkKb];
 #pragma unroll
-            for (int y = 0; y < 4; ++y) fb[1][y] = *reinterpret_cast<const v4i *>(Bs + (wn * 128 + y * 32) * kBK + foff1);
-            __builtin_amdgcn_sched_barrier(0);
+                for (int u = 0; u < kU; ++u)
 #pragma unroll
-            for (int x = 1; x < 4; ++x) mfma_row(0, x);
+                    for (int kb = 0; kb < kChunkKb; ++kb)
+                        rj[u][kb] = k0 + u < ne && kb < kbn
+                                        ? *reinterpret_cast<const uint4 *>(Jb + kb * 4096 + (myv[k0 + u] & 255) * 16)
+                                        : make_uint4(0, 0, 0, 0);
 #pragma unroll
-            for (int x = 0; x < 4; ++x) mfma_row(1, x);
+                for (int u = 0; u < kU; ++u) {
+                    const int li = (int)(myv[k0 + u] >> 8);
+                    if (k0 + u < ne && li != cur) {
+                        cur = li;
+#pragma unroll
+                        for (int kb = 0; kb < kChunkKb; ++kb) ri[kb] = *reinterpret_cast<const uint4 *>(Ib + kb * 4096 + li * 16);
+                    }
+                    int sum = 0;
+#pragma unroll
+                    for (int kb = 0; kb < kChunkKb; ++kb)
+                        sum += __builtin_popcount(ri[kb].x & rj[u][kb].x) + __builtin_popcount(ri[kb].y & rj[u][kb].y) +
+                               __builtin_popcount(ri[kb].z & rj[u][kb].z) + __builtin_popcount(ri[kb].w & rj[u][kb].w);
+                    myc[k0 + u] += k0 + u < ne ? sum : 0;
+                }
+            }
         }
-        __syncthreads();   // no stage is read any more: the ring becomes the tile T[256][256] (uint16)
-        // lane holds column (lane & 31) and rows 8*(r/4) + 4*(lane/32) + r%4 of each 32 x 32 block;
-        // the whole vector is reinterpreted before the low halves are taken
+        // the LDS becomes the tile T (zero, then the counts scattered in; weights below 2^16)
+        __syncthreads();
+        for (int k = tid; k < kTileBytes / 16; k += 256) reinterpret_cast<uint4 *>(smem)[k] = make_uint4(0, 0, 0, 0);
+        __syncthreads();
+        int wmax = 0;
 #pragma unroll
-        for (int x = 0; x < 4; ++x)
-#pragma unroll
-            for (int y = 0; y < 4; ++y) {
-                const v16i ai = __builtin_bit_cast(v16i, acc[x][y]);
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int lr = wm * 128 + x * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                    const int lc = wn * 128 + y * 32 + (lane & 31);
-                    T[lr * kSc2Tile + lc] = (uint16_t)ai[r];
+        for (int k = 0; k < kEdgesPerThread; ++k) {
+            if (k < ne) {
+                const int c = myc[k];
+                T[(myv[k] >> 8) * kSc2Tile + (myv[k] & 255)] = (uint16_t)c;
+                wmax = max(wmax, c);
+                if (MODE != kSc2Features && c > 0) {   // the weight histogram counts nonzero weights
+                    if (c <= kHistLdsBins) lds_add(hist, c - 1);
+                    else atomicAdd(&gh[c], 1);
                 }
             }
+        }
+        wmax = half_max(wmax);
+        if ((lane & 31) == 31) atomicMax(&tmax[par], wmax);
         __syncthreads();
-        }   // dense (MFMA) path
-        int32_t *gh = w.ghist + ((int64_t)b * kHistGroups + local % kHistGroups) * w.hist_stride;
+        // thread t: column chunk cc = t % 32 (8 columns) of rows lr = 8k + t / 32, k = 0..31, in four
+        // batches of eight rows; lanes 0-31 of a wave hold one row, lanes 32-63 the next
         int32_t *rowmax = w.rowmax + (int64_t)b * w.max_n;
         int32_t *rstat = w.rowstat + (int64_t)b * w.max_n * 20;
         uint16_t *Gb = w.G + d.g_off;
-        // every pair of the tile is in the strict upper triangle and below n: no per-entry test
-        const bool interior = bi < bj && (bj + 1) * kSc2Tile <= d.n;
-        const bool small_n = d.n <= kHistLdsBins;
-        // thread t: column chunk cc = t % 32 (8 columns) of rows lr = 8k + t / 32, k = 0..31, in four
-        // batches of eight rows; the packed C_ij of the next batch are in flight while one is processed.
-        // Lanes 0-31 of a wave hold one row, lanes 32-63 the next.
-        const int cc = tid & 31;
-        const int j0 = bj * kSc2Tile + cc * 8;
-        const uint8_t *crow = Cb + ((int64_t)bi * kSc2Tile + (tid >> 5)) * rs + j0 / 2;
-        // (the bit-count path's T holds only its edges' weights: no C_ij or range masking)
-        uint32_t cur[8], nxt[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-            cur[q] = sparse ? 0x22222222u : *reinterpret_cast<const uint32_t *>(crow + (int64_t)(q * 8) * rs);
-#pragma unroll
+        const int cc = tid & 31, j0 = bj * kSc2Tile + cc * 8;
+#pragma unroll 1
         for (int kb = 0; kb < 4; ++kb) {
-            if (kb < 3) {
-#pragma unroll
-                for (int q = 0; q < 8; ++q)
-                    nxt[q] = sparse ? 0x22222222u
-                                    : *reinterpret_cast<const uint32_t *>(crow + (int64_t)(((kb + 1) * 8 + q) * 8) * rs);
-            }
-            uint4 tv[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q)
-                tv[q] = *reinterpret_cast<const uint4 *>(&T[((kb * 8 + q) * 8 + (tid >> 5)) * kSc2Tile + cc * 8]);
             int rmax[8], rsum[8];
-            uint32_t ow[8][4], nzq[8];
-            // masking, stores and row maxima of the eight rows first (straight-line code), the
-            // histogram of their nonzero weights after
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int lr = (kb * 8 + q) * 8 + (tid >> 5);
-                const int i = bi * kSc2Tile + lr;
-                const uint32_t tw[4] = {tv[q].x, tv[q].y, tv[q].z, tv[q].w};
-                // entries e of the chunk with i < j0 + e < n (all eight except at the diagonal and the edge)
-                const int e_lo = min(8, max(0, i + 1 - j0)), e_hi = min(8, max(0, d.n - j0));
-                const uint32_t vm = (interior || sparse) ? 0xFFu : (((1u << e_hi) - 1u) & ~((1u << e_lo) - 1u));
-                const uint32_t cb = cur[q] >> 1;   // C of column e at bit 4e
+            for (int u = 0; u < 8; ++u) {
+                const int lr = (kb * 8 + u) * 8 + (tid >> 5), i = bi * kSc2Tile + lr;
+                const uint4 tv = *reinterpret_cast<const uint4 *>(&T[lr * kSc2Tile + cc * 8]);
+                const uint32_t tw[4] = {tv.x, tv.y, tv.z, tv.w};
+                u16x2 m2 = {0, 0};
+                rsum[u] = 0;
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    const uint32_t lo = ((cb >> (8 * k)) & 1u) & (vm >> (2 * k));
-                    const uint32_t hi = ((cb >> (8 * k + 4)) & 1u) & (vm >> (2 * k + 1));
-                    ow[q][k] = tw[k] & ((lo * 0xFFFFu) | (hi * 0xFFFF0000u));
+                    m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(u16x2, tw[k]));
+                    rsum[u] += (int)((tw[k] & 0xFFFFu) + (tw[k] >> 16));
                 }
-                const u16x2 m2 = __builtin_elementwise_max(
-                    __builtin_elementwise_max(__builtin_bit_cast(u16x2, ow[q][0]), __builtin_bit_cast(u16x2, ow[q][1])),
-                    __builtin_elementwise_max(__builtin_bit_cast(u16x2, ow[q][2]), __builtin_bit_cast(u16x2, ow[q][3])));
-                rmax[q] = max((int)m2.x, (int)m2.y);
-                rsum[q] = 0;
-                if (LEARNED) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) rsum[q] += (int)((ow[q][e >> 1] >> (16 * (e & 1))) & 0xFFFFu);
-                    // the masked tile, for the column pass
-                    *reinterpret_cast<uint4 *>(&T[lr * kSc2Tile + cc * 8]) =
-                        make_uint4(ow[q][0], ow[q][1], ow[q][2], ow[q][3]);
-                }
-                // every chunk is stored whole: entries with j <= i or j >= n are zero and no reader looks at them
-                *reinterpret_cast<uint4 *>(Gb + (int64_t)i * d.npad + j0) =
-                    make_uint4(ow[q][0], ow[q][1], ow[q][2], ow[q][3]);
-                uint32_t nz = 0;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) nz |= (uint32_t)(((ow[q][e >> 1] >> (16 * (e & 1))) & 0xFFFFu) != 0) << e;
-                nzq[q] = nz;
+                rmax[u] = max((int)m2.x, (int)m2.y);
+                *reinterpret_cast<uint4 *>(Gb + (int64_t)i * d.npad + j0) = tv;
             }
-            // weight histogram: one LDS atomic per nonzero weight, round by round (a lane's next
-            // nonzero each round) over four rows at a time, as many rounds as the lane with the
-            // most nonzero weights in them needs. Entry e of the 32: row e / 8, 16 bits at
-            // 16 (e mod 4) of that row's low or high 64-bit half, selected arithmetically (a
-            // lane-varying switch would become branches).
 #pragma unroll
-            for (int g4 = 0; g4 < 2; ++g4) {
-                if (sparse) break;   // the bit-count path histogrammed its edges already
-                uint32_t nz = 0;
-                uint64_t h64[8];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int q = g4 * 4 + u;
-                    nz |= nzq[q] << (8 * u);
-                    h64[2 * u] = (uint64_t)ow[q][0] | ((uint64_t)ow[q][1] << 32);
-                    h64[2 * u + 1] = (uint64_t)ow[q][2] | ((uint64_t)ow[q][3] << 32);
-                }
-                auto next_weight = [&]() -> int {
-                    const int e = __builtin_ctz(nz);
-                    nz &= nz - 1;
-                    const int hsel = e >> 2;   // half index 0..7
-                    const uint64_t a0 = (hsel & 1) ? h64[1] : h64[0], a1 = (hsel & 1) ? h64[3] : h64[2];
-                    const uint64_t a2 = (hsel & 1) ? h64[5] : h64[4], a3 = (hsel & 1) ? h64[7] : h64[6];
-                    const uint64_t b0 = (hsel & 2) ? a1 : a0, b1 = (hsel & 2) ? a3 : a2;
-                    const uint64_t half = (hsel & 4) ? b1 : b0;
-                    return (int)((half >> (16 * (e & 3))) & 0xFFFFu);
-                };
-                if (small_n) {   // every weight is below n <= kHistLdsBins
-                    while (__any(nz))
-                        if (nz) atomicAdd(&hist[next_weight()], 1);
-                } else {
-                    while (__any(nz)) {
-                        if (nz) {
-                            const int v = next_weight();
-                            if (v < kHistLdsBins) atomicAdd(&hist[v], 1);
-                            else atomicAdd(&gh[v], 1);
-                        }
-                    }
-                }
-            }
-            // row maxima (and sums) over the 32 lanes of each row, eight rows interleaved (DPP, no LDS)
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                rmax[q] = half_max(rmax[q]);
-                if (LEARNED) rsum[q] = half_sum(rsum[q]);
+            for (int u = 0; u < 8; ++u) {
+                rmax[u] = half_max(rmax[u]);
+                if (MODE != kSc2Plain) rsum[u] = half_sum(rsum[u]);
             }
             if ((lane & 31) == 31) {
 #pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    const int i = bi * kSc2Tile + (kb * 8 + q) * 8 + (tid >> 5);
-                    if (rmax[q] > 0) {
-                        atomicMax(&rowmax[i], rmax[q]);
-                        if (LEARNED) {
-                            atomicAdd(&rstat[i * 20 + 1], rsum[q]);
-                            atomicMax(&rstat[i * 20 + 2], rmax[q]);
+                for (int u = 0; u < 8; ++u) {
+                    const int i = bi * kSc2Tile + (kb * 8 + u) * 8 + (tid >> 5);
+                    if (rmax[u] > 0) {
+                        if (MODE != kSc2Features) atomicMax(&rowmax[i], rmax[u]);
+                        if (MODE != kSc2Plain) {
+                            atomicAdd(&rstat[i * 20 + 1], rsum[u]);
+                            atomicMax(&rstat[i * 20 + 2], rmax[u]);
                         }
                     }
                 }
             }
-            if (kb < 3) {
-#pragma unroll
-                for (int q = 0; q < 8; ++q) cur[q] = nxt[q];
-            }
         }
-        if (LEARNED) {
-            // column j of the upper tile is row j of the lower one (Ghat is symmetric): thread t sums
-            // and maximises columns 2c, 2c+1 (c = t mod 128) of the masked tile over rows of parity
-            // t / 128, sixteen 4-byte reads in flight; the two parities meet in LDS
+        if (MODE != kSc2Features) hist_flush(hist, gh, min(tmax[par], kHistLdsBins));
+        if (MODE != kSc2Plain) {
             __syncthreads();
-            const int cp = tid & 127, par = tid >> 7;
-            const uint32_t *Tw = reinterpret_cast<const uint32_t *>(T);
-            int s0 = 0, s1 = 0;
-            u16x2 mx = {0, 0};
-            for (int m0 = 0; m0 < kSc2Tile / 2; m0 += 16) {
-                uint32_t v[16];
-#pragma unroll
-                for (int u = 0; u < 16; ++u) v[u] = Tw[(2 * (m0 + u) + par) * (kSc2Tile / 2) + cp];
-#pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    s0 += (int)(v[u] & 0xFFFFu);
-                    s1 += (int)(v[u] >> 16);
-                    mx = __builtin_elementwise_max(mx, __builtin_bit_cast(u16x2, v[u]));
-                }
-            }
-            __syncthreads();   // the tile is read
-            int32_t *xl = reinterpret_cast<int32_t *>(smem);
-            if (par) {
-                xl[3 * cp] = s0;
-                xl[3 * cp + 1] = s1;
-                xl[3 * cp + 2] = (int32_t)__builtin_bit_cast(uint32_t, mx);
-            }
-            __syncthreads();
-            if (!par) {
-                const u16x2 m2 = __builtin_elementwise_max(mx, __builtin_bit_cast(u16x2, (uint32_t)xl[3 * cp + 2]));
-                const int cs[2] = {s0 + xl[3 * cp], s1 + xl[3 * cp + 1]}, cm[2] = {(int)m2.x, (int)m2.y};
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    const int j = bj * kSc2Tile + 2 * cp + e;
-                    if (cm[e] > 0) {
-                        atomicAdd(&rstat[j * 20 + 1], cs[e]);
-                        atomicMax(&rstat[j * 20 + 2], cm[e]);
-                    }
-                }
-            }
+            column_stats<kSc2Tile, kSc2Tile>(T, kSc2Tile, reinterpret_cast<int32_t *>(smem), rstat, bj * kSc2Tile);
         }
-        __syncthreads();
-        const int hl = min(d.n, kHistLdsBins);
-        for (int k = tid; k < hl; k += 256) {
-            const int c = hist[k];
-            if (c) {
-                atomicAdd(&gh[k], c);
-                hist[k] = 0;
-            }
-        }
-        __syncthreads();   // T is the next item's ring
+        if (tid == 0) tmax[par ^ 1] = 0;
+        par ^= 1;
+        __syncthreads();   // T is the next item's chunk buffers
     }
 }
 
@@ -1101,35 +1169,48 @@ hipError_t launch_prep_learned(const Work &w, int grid, hipStream_t s)
 
 hipError_t launch_compat(const Work &w, int grid, hipStream_t s)
 {
-    // the bit rows are written only for an SC2 launch that may take the bit-count path
-    const bool learned = w.learned && w.feat_all, bits = w.sc2_sparse_cap > 0;
-    if (learned && bits) hipLaunchKernelGGL((k_compat<true, true>), dim3(grid), dim3(256), 0, s, w);
-    else if (learned) hipLaunchKernelGGL((k_compat<true, false>), dim3(grid), dim3(256), 0, s, w);
-    else if (bits) hipLaunchKernelGGL((k_compat<false, true>), dim3(grid), dim3(256), 0, s, w);
-    else hipLaunchKernelGGL((k_compat<false, false>), dim3(grid), dim3(256), 0, s, w);
+    if (w.learned && w.feat_all) hipLaunchKernelGGL(k_compat<true>, dim3(grid), dim3(256), 0, s, w);
+    else hipLaunchKernelGGL(k_compat<false>, dim3(grid), dim3(256), 0, s, w);
     return hipGetLastError();
 }
 
-hipError_t launch_sc2(const Work &w, int grid, hipStream_t s)
+namespace {
+constexpr int sc2_lds(int mode)
 {
-    // separate instances: the dense-only kernel carries none of the bit-count path's registers
-    const bool sparse = w.sc2_sparse_cap > 0;
-    if (w.learned && sparse) hipLaunchKernelGGL((k_sc2<true, true>), dim3(grid), dim3(256), kSc2Lds, s, w);
-    else if (w.learned) hipLaunchKernelGGL((k_sc2<true, false>), dim3(grid), dim3(256), kSc2Lds, s, w);
-    else if (sparse) hipLaunchKernelGGL((k_sc2<false, true>), dim3(grid), dim3(256), kSc2Lds, s, w);
-    else hipLaunchKernelGGL((k_sc2<false, false>), dim3(grid), dim3(256), kSc2Lds, s, w);
+    return (mode == kSc2Features ? 0 : kHistBytes) + (mode == kSc2Plain ? 0 : kOutBytes);
+}
+}  // namespace
+
+// items: 256 x 256 tiles of the list. The grid is a multiple of 8 with as many workgroups per XCD as
+// an even range would hold work items, up to what its CUs hold.
+hipError_t launch_sc2(const Work &w, int64_t items, int num_cus, hipStream_t s)
+{
+    const int mode = !w.learned ? kSc2Plain : w.feat_all ? kSc2Features : kSc2Learned;
+    const int cus = std::max(1, num_cus / 8);
+    if (w.sc2_sparse_cap > 0) {
+        const int grid = (int)(8 * std::min<int64_t>((items + 7) / 8, cus));
+        if (mode == kSc2Plain) hipLaunchKernelGGL(k_sc2_sparse<kSc2Plain>, dim3(grid), dim3(256), kSparseLds, s, w);
+        else if (mode == kSc2Learned) hipLaunchKernelGGL(k_sc2_sparse<kSc2Learned>, dim3(grid), dim3(256), kSparseLds, s, w);
+        else hipLaunchKernelGGL(k_sc2_sparse<kSc2Features>, dim3(grid), dim3(256), kSparseLds, s, w);
+        return hipGetLastError();
+    }
+    const int grid = (int)(8 * std::min<int64_t>(4 * ((items + 7) / 8), cus * (mode == kSc2Plain ? kSc2PerCu : 2)));
+    if (mode == kSc2Plain) hipLaunchKernelGGL(k_sc2<kSc2Plain>, dim3(grid), dim3(256), sc2_lds(kSc2Plain), s, w);
+    else if (mode == kSc2Learned) hipLaunchKernelGGL(k_sc2<kSc2Learned>, dim3(grid), dim3(256), sc2_lds(kSc2Learned), s, w);
+    else hipLaunchKernelGGL(k_sc2<kSc2Features>, dim3(grid), dim3(256), sc2_lds(kSc2Features), s, w);
     return hipGetLastError();
 }
 
 hipError_t setup_graph_kernels()
 {
-    const void *fns[4] = {reinterpret_cast<const void *>(k_sc2<false, false>),
-                          reinterpret_cast<const void *>(k_sc2<false, true>),
-                          reinterpret_cast<const void *>(k_sc2<true, false>),
-                          reinterpret_cast<const void *>(k_sc2<true, true>)};
+    const void *fns[4] = {reinterpret_cast<const void *>(k_sc2_sparse<kSc2Plain>),
+                          reinterpret_cast<const void *>(k_sc2_sparse<kSc2Learned>),
+                          reinterpret_cast<const void *>(k_sc2_sparse<kSc2Features>),
+                          reinterpret_cast<const void *>(k_sc2<kSc2Learned>)};
+    const int lds[4] = {kSparseLds, kSparseLds, kSparseLds, sc2_lds(kSc2Learned)};
     hipError_t e = hipSuccess;
     for (int k = 0; k < 4 && e == hipSuccess; ++k)
-        e = hipFuncSetAttribute(fns[k], hipFuncAttributeMaxDynamicSharedMemorySize, kSc2Lds);
+        e = hipFuncSetAttribute(fns[k], hipFuncAttributeMaxDynamicSharedMemorySize, lds[k]);
     return e;
 }
 

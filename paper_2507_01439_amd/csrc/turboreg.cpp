@@ -46,7 +46,7 @@ struct tr_handle {
     PairState *state = nullptr;
     Plan *plan = nullptr;
     int32_t *pre = nullptr;
-    uint8_t *C = nullptr, *Cbits = nullptr;
+    uint8_t *C = nullptr;
     uint16_t *G = nullptr;
     int32_t *ghist = nullptr, *rowmax = nullptr, *cnt_part = nullptr, *rowcnt = nullptr, *blkcnt = nullptr;
     uint64_t *cand = nullptr, *rowseg = nullptr, *hyp_rec = nullptr;
@@ -149,8 +149,7 @@ void workspace_layout(tr_handle *h, Get &&get)
     get(h->state, B);
     get(h->plan, 1);
     get(h->pre, (size_t)kPreRows * h->pre_stride);
-    get(h->C, B * (nn / 2 + (size_t)h->npad_max * kCRowPad));   // packed E2M1, two entries per byte, padded rows
-    get(h->Cbits, B * nn / 8);   // the same matrix as bits
+    get(h->C, B * nn / 8);   // one bit per entry
     get(h->G, B * nn);
     get(h->ghist, B * kHistGroups * (size_t)((max_n + 7) & ~(size_t)7));
     get(h->rowmax, B * max_n);
@@ -231,7 +230,6 @@ Work make_work(tr_handle *h, const float *src, const float *dst, const tr_params
     w.tau = p.tau;
     w.theta = p.inlier_thresh;
     w.C = h->C;
-    w.Cbits = h->Cbits;
     w.G = h->G;
     w.ghist = h->ghist;
     w.hist_stride = (h->max_n + 7) & ~7;
@@ -327,13 +325,10 @@ tr_status enqueue(tr_handle *h, const Work &w_in, const int32_t *offsets, int32_
     chk(launch_compat(w, grid_cap(h, (int64_t)B * nb64 * (nb64 + 1) / 2, cfg.compat_per_cu), s));
     mark(TR_STAGE_SC2);
     {
-        // one workgroup per CU; the kernel splits its items into 8 ranges, one per XCD
-        // (workgroup g runs on XCD g mod 8), of equal counts for one pair and of equal modelled
-        // cost for a batch, so the grid is a multiple of 8 with as many workgroups per XCD as an
-        // even range would hold items, up to the XCD's CUs
+        // the kernel splits its items into 8 ranges, one per XCD (workgroup g runs on XCD g mod 8), of
+        // equal counts for one pair and of equal modelled cost for a batch
         const int64_t items = (int64_t)B * nbs * (nbs + 1) / 2;
-        const int64_t per_xcd = std::min<int64_t>((items + 7) / 8, std::max(1, h->num_cus / 8));
-        chk(launch_sc2(w, (int)(8 * per_xcd), s));
+        chk(launch_sc2(w, items, h->num_cus, s));
     }
     if (features_only) return e == hipSuccess ? TR_OK : TR_ERR_HIP;
     mark(TR_STAGE_PIVOTS);
@@ -851,29 +846,26 @@ tr_status tr_debug_copy(tr_handle *h, int32_t tap, int32_t pair, void *host_dst,
     if (hipStreamSynchronize(h->last_stream) != hipSuccess) return TR_ERR_HIP;
     const Work &w = h->last;
     PairDesc d;
-    if (w.n1) d = pair_desc_of(w.n1, 0, 0, 0, w.pool);   // single-pair calls keep no device descriptor
+    if (w.n1) d = pair_desc_of(w.n1, 0, 0, w.pool);   // single-pair calls keep no device descriptor
     else if (hipMemcpy(&d, h->pairs + pair, sizeof(d), hipMemcpyDeviceToHost) != hipSuccess) return TR_ERR_HIP;
     const size_t n = d.n;
     size_t need = 0;
     const void *srcp = nullptr;
     size_t pitch = 0, width = 0, rows = 0;
     switch (tap) {
-    case TR_TAP_C: {   // stored as E2M1 nibbles (0x2 = 1): unpacked to one byte per entry here
+    case TR_TAP_C: {   // stored as blocks of 128 columns, one bit per entry: one byte per entry here
         need = n * n;
         if (needed) *needed = need;
         if (!host_dst) return TR_OK;
         if (bytes < need) return TR_ERR_INVALID_ARG;
-        const size_t rb = (n + 1) / 2;
-        std::vector<uint8_t> packed(rb * n);
-        if (n && hipMemcpy2D(packed.data(), rb, h->C + d.cb_off, (size_t)c_pitch(d.npad), rb, n,
-                             hipMemcpyDeviceToHost) != hipSuccess)
+        const size_t npad = d.npad, nkb = (n + 127) / 128;
+        std::vector<uint8_t> bits(nkb * npad * 16);
+        if (n && hipMemcpy(bits.data(), h->C + d.c_off / 8, bits.size(), hipMemcpyDeviceToHost) != hipSuccess)
             return TR_ERR_HIP;
         uint8_t *o = static_cast<uint8_t *>(host_dst);
         for (size_t i = 0; i < n; ++i)
-            for (size_t j = 0; j < n; ++j) {
-                const int nib = (packed[i * rb + j / 2] >> (4 * (j & 1))) & 0xF;
-                o[i * n + j] = nib == 0x2 ? 1 : (nib == 0 ? 0 : 0xFF);   // 0xFF: not a valid entry
-            }
+            for (size_t j = 0; j < n; ++j)
+                o[i * n + j] = (bits[((j >> 7) * npad + i) * 16 + ((j & 127) >> 3)] >> (j & 7)) & 1;
         return TR_OK;
     }
     case TR_TAP_G:
