@@ -9,7 +9,8 @@ namespace tr {
 
 constexpr int kSc2Tile = 256;     // SC2 work-list tile edge (four 128 x 128 output tiles); npad is a multiple
 constexpr int kHistGroups = 8;    // SC2 tiles add their weight histograms into this many copies per pair
-constexpr int kCompatTile = 64;   // tile edge of the compatibility kernel
+constexpr int kCompatTile = 128;  // tile edge of the compatibility list
+constexpr int kCompatMinRows = 8; // fewest rows of a tile one work item takes (Work::compat_rows)
 constexpr int kRowsPerItem = 4;   // rows per work item of the pivot scans (one per wave)
 constexpr int kPrepRows = 256;    // rows per work item of the prep / feature kernels
 constexpr int kRankSortMax = 4096; // candidate lists up to this size are ordered by a rank sort
@@ -84,7 +85,9 @@ struct Work {
     int32_t *ghist;           // max_batch x kHistGroups x hist_stride weight histograms (filled by the SC2 epilogue)
     int32_t hist_stride;      // max_n rounded up to 8 (16-byte aligned copies)
     int32_t *rowmax;          // max_batch x max_n: max_{j>i} G_ij (filled by the SC2 epilogue)
-    int32_t *cnt_part;        // per compatibility work item: (boundary pairs, edges, non-finite input)
+    int32_t compat_rows;      // rows of a compatibility tile per work item: 8, 16, 32, 64 or 128
+    uint32_t *cnt_part;       // per compatibility work item: edges (15 bits), boundary pairs << 15, non-finite
+                              // input << 30
     int32_t *rowcnt;          // max_batch x max_n: pairs of weight alpha per row (ordered path)
     uint64_t *rowseg;         // max_batch x max_n: bit s set if the row's s-th 512-column segment (counted
                               // from its first column j > i) holds a pair of weight alpha (ordered path)
@@ -200,10 +203,10 @@ __host__ __device__ inline PairDesc pair_desc_of(int32_t n, int32_t pt_off, int6
 __host__ __device__ inline int64_t stage_items(int stage, int32_t n, int32_t H)
 {
     const int64_t npad = (n + kSc2Tile - 1) / kSc2Tile * kSc2Tile;
-    const int64_t nb64 = npad / kCompatTile, nbs = npad / kSc2Tile;
+    const int64_t nbc = npad / kCompatTile, nbs = npad / kSc2Tile;
     switch (stage) {
     case kPrep: return (n + kPrepRows - 1) / kPrepRows;
-    case kCompat: return nb64 * (nb64 + 1) / 2;
+    case kCompat: return nbc * (nbc + 1) / 2;
     case kSc2: return nbs * (nbs + 1) / 2;
     case kRowBlk: return (n + kRowsPerItem - 1) / kRowsPerItem;
     default: return (int64_t)((H + kScoreHyp - 1) / kScoreHyp) * ((n + kScorePts - 1) / kScorePts);
@@ -324,7 +327,8 @@ __device__ inline void bitonic_sort_lds(uint64_t *keys, int P)
 hipError_t launch_plan(const Work &w, const int32_t *offsets, int32_t n_single, int32_t B,
                        int32_t max_n, PairDesc *pairs, PairState *state, Plan *plan, int32_t *pre,
                        hipStream_t s);
-hipError_t launch_compat(const Work &w, int grid, hipStream_t s);
+int compat_rows(int64_t tiles, int num_cus);
+hipError_t launch_compat(const Work &w, int64_t tiles, int cap, hipStream_t s);
 hipError_t launch_sc2(const Work &w, int64_t items, int num_cus, hipStream_t s);
 hipError_t launch_pivots(const Work &w, int B, int grid_rows, hipStream_t s);
 hipError_t launch_prep_learned(const Work &w, int grid, hipStream_t s);

@@ -297,6 +297,8 @@ __global__ void __launch_bounds__(256) k_prep_learned(Work w)
 
 // ---------------------------------------------------------------- Eq. 1
 
+typedef float v16f __attribute__((ext_vector_type(16)));
+
 
 constexpr int kNibStride = 32;    // LDS row stride of a packed 64-column tile (two entries per byte)
 
@@ -315,184 +317,320 @@ __device__ __forceinline__ uint32_t nibbles_to_bits(uint32_t x)
     return (x | (x >> 12)) & 0xFFu;
 }
 
-// Guard band of the fast compatibility test: v_sqrt_f32 is within a few ulps,
-// so |delta_fast - delta_exact| <= 2^-21 (|x| + |y|); a pair whose fast delta
-// lies within 2^-19 (|x| + |y|) + 2e-6 of tau is re-evaluated exactly, which
-// also covers every pair the boundary report counts (|delta - tau| < 1e-6).
-__device__ __forceinline__ bool near_tau(float la, float lb, float dl, float tau)
+// A value that is the same on every lane, in scalar registers.
+__device__ __forceinline__ int64_t uniform64(int64_t v)
 {
-    return __builtin_fabsf(dl - tau) <= __builtin_fmaf(la + lb, 0x1p-19f, 2e-6f) || !(dl == dl);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-// One 64 x 64 tile (bi <= bj) of C per work item. Each thread evaluates a
-// 4 x 4 block of pairs once: the plain path with the hardware square root and
-// a guard band around tau (any lane with a pair inside it redoes its 16 pairs
-// with the correctly rounded square root, so decisions are identical to the
-// exact evaluation); learned mode always evaluates exactly, because its delta
-// histogram needs the exact value. The tile and its transpose are staged in
-// LDS and written to both triangles with 16-byte stores. The next item's
-// points are loaded while the current one is computed. Per-tile counts
-// (boundary pairs, edges) go to a per-item slot, so no atomics are needed;
-// non-finite inputs are counted by the diagonal tiles (third slot), which also clear the
-// pair's weight histograms and row maxima for their rows.
-template <bool LEARNED>
-__global__ void __launch_bounds__(256, 2) k_compat(Work w)
+// Exchange of the wave's halves: a' = [a of lanes 0-31, b of lanes 0-31], b' = [a of 32-63, b of 32-63].
+__device__ __forceinline__ void swap_halves(uint32_t &a, uint32_t &b)
 {
-    __shared__ float px[2][64][3], py[2][64][3];
-    __shared__ __attribute__((aligned(16))) uint8_t tile[2][64 * kNibStride];
-    __shared__ int32_t hrow[LEARNED ? 64 : 1][17], hcol[LEARNED ? 64 : 1][17];
-    __shared__ int32_t red[4][3];
+    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+
+// Maximum over the wave of values >= 0 (as integers they order alike), in every lane.
+__device__ __forceinline__ float wave_fmax(float v)
+{
+    int m = __float_as_int(v);
+    m = max(m, __builtin_amdgcn_update_dpp(0, m, 0x111, 0xf, 0xf, false));   // row_shr:1
+    m = max(m, __builtin_amdgcn_update_dpp(0, m, 0x112, 0xf, 0xf, false));   // row_shr:2
+    m = max(m, __builtin_amdgcn_update_dpp(0, m, 0x114, 0xf, 0xf, false));   // row_shr:4
+    m = max(m, __builtin_amdgcn_update_dpp(0, m, 0x118, 0xf, 0xf, false));   // row_shr:8
+    m = max(m, __builtin_amdgcn_update_dpp(0, m, 0x142, 0xa, 0xf, false));   // row_bcast:15 into rows 1, 3
+    m = max(m, __builtin_amdgcn_update_dpp(0, m, 0x143, 0xc, 0xf, false));   // row_bcast:31 into rows 2, 3
+    return __int_as_float(__builtin_amdgcn_readlane(m, 63));
+}
+
+// One step of a 32 x 32 bit transpose across the 32 lanes of each half of the wave: lanes S apart
+// exchange the bits whose position differs in S (M: the positions with that bit clear).
+template <int S, uint32_t M>
+__device__ __forceinline__ uint32_t transpose_step(uint32_t x, int lane)
+{
+    const uint32_t y = (uint32_t)__builtin_amdgcn_ds_swizzle((int)x, (S << 10) | 0x1f);   // lane ^ S
+    const bool hi = lane & S;
+    const uint32_t z = __builtin_amdgcn_alignbit(y, y, hi ? S : 32 - S), mk = hi ? M : ~M;
+    return (z & mk) | (x & ~mk);
+}
+
+// Bit r of lane c becomes bit c of lane r, in each half of the wave.
+__device__ __forceinline__ uint32_t transpose32(uint32_t x, int lane)
+{
+    x = transpose_step<16, 0x0000FFFFu>(x, lane);
+    x = transpose_step<8, 0x00FF00FFu>(x, lane);
+    x = transpose_step<4, 0x0F0F0F0Fu>(x, lane);
+    x = transpose_step<2, 0x33333333u>(x, lane);
+    return transpose_step<1, 0x55555555u>(x, lane);
+}
+
+// C of 8 to 128 rows x 128 columns per work item, one wave per item and no workgroup barrier: a lane
+// holds two columns' points in registers, the rows' points (R <= 32 at a time) are broadcast from LDS (the
+// next row's read ahead), and each pair is evaluated once for both triangles. Off the diagonal an item
+// writes its rows and their transpose. A lane's decisions collect as one bit per row, so a column is an
+// R-bit word (the transpose's R / 8 bytes) and a bit transpose across lanes gives the rows' 16 bytes.
+//
+// With a = |x_i - x_j|^2, b = |y_i - y_j|^2, s = a + b, d = a - b, L = sqrt a + sqrt b, the test
+// |sqrt a - sqrt b| <= tau is for s >= tau^2 the sign of E = d^2 - 2 tau^2 s + tau^4 =
+// (delta^2 - tau^2)(L^2 - tau^2): no square root, and the sign bit shifts straight into the lane's word
+// (20 issue slots a pair; 26 with two hardware square roots). A guard makes every decision the exact one
+// (length32, correctly rounded roots). a and b carry 5 x 2^-24 relative, so E near delta = tau is off by
+// at most 12 x 2^-24 tau L s; the exact evaluation's own rounding moves delta by 3 x 2^-24 L, as much again
+// in E; the boundary report counts |delta - tau| < 1e-6, 4.4e-6 tau s in E. A row holding a pair with
+// |E| <= tau s (2^-18 L + 5e-6) + 2.1 tau^4 (L <= s / L0 + L0 / 2 for any L0; the last term covers the pairs
+// with s near or below tau^2, where E's sign says nothing) is evaluated exactly. Items with a non-finite or
+// huge point (beyond 1e8), and thresholds outside [1e-9, 1e8], are evaluated exactly throughout.
+//
+// Counts (edges, boundary pairs, non-finite input; the last by diagonal items) go to the item's slot. The
+// diagonal items clear the pair's weight histograms and row maxima for their rows, and with learned pivots
+// the SC2 row statistics and row marks.
+__global__ void __launch_bounds__(256) k_compat(Work w)
+{
+    __shared__ float4 rows[4][32][2];
     __shared__ SlotCache slots;
     const bool cached = slot_cache_fill(w, kCompat, slots);
     __syncthreads();
-    const int total = stage_total(w, kCompat);
-    const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15, lane = tid & 63, wv = tid >> 6;
+    const int ROWS = w.compat_rows, R = min(ROWS, 32), per = kCompatTile / ROWS, total = stage_total(w, kCompat) * per;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const float tau = w.tau, t2 = 2.0f * tau * tau, t4 = (tau * tau) * (tau * tau);
+    const bool odd_tau = !(tau >= 1e-9f && tau <= 1e8f);
+    if (w.n1 && blockIdx.x == 0 && tid == 0) {   // a single-pair call has no planner: reset its state here
+        PairState st = {};
+        st.status = TR_OK;
+        w.state[0] = st;
+    }
+    for (int item = blockIdx.x * 4 + wv; item < total; item += gridDim.x * 4) {
+        int local, bi, bj;
+        const int tile = item / per;
+        const int b = __builtin_amdgcn_readfirstlane(stage_pair_cached(w, kCompat, slots, cached, tile, local));
+        const PairDesc d = pair_desc(w, b);
+        const int n = __builtin_amdgcn_readfirstlane(d.n), npad = __builtin_amdgcn_readfirstlane(d.npad);
+        local = __builtin_amdgcn_readfirstlane(local);
+        tri_decode(local, npad / kCompatTile, bi, bj);
+        bi = __builtin_amdgcn_readfirstlane(bi);
+        bj = __builtin_amdgcn_readfirstlane(bj);
+        const int j0 = bj * kCompatTile + lane;
+        const bool diag = bi == bj;
+        const float *src = w.src + 3 * (int64_t)d.pt_off, *dst = w.dst + 3 * (int64_t)d.pt_off;
+        // past n a copy of the last point, whose decisions are masked
+        float3 x[2], y[2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const int jc = min(j0 + 64 * c, n - 1);
+            x[c] = *reinterpret_cast<const float3 *>(src + 3 * jc);
+            y[c] = *reinterpret_cast<const float3 *>(dst + 3 * jc);
+        }
+        auto wild_point = [](float3 q) { return !(__builtin_fabsf(q.x) + __builtin_fabsf(q.y) + __builtin_fabsf(q.z) < 1e8f); };
+        const bool wild_col = odd_tau || __any(wild_point(x[0]) || wild_point(x[1]) || wild_point(y[0]) || wild_point(y[1]));
+        float near_at[2];   // a lane past n is never near
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            near_at[c] = j0 + 64 * c < n ? 2.1f * t4 : -1.0f;
+            asm volatile("" : "+v"(near_at[c]));   // kept in its register, not formed again for each row
+        }
+        uint8_t *Cb = w.C + uniform64(d.c_off) / 8;
+        const uint32_t kbs = (uint32_t)npad * 16;   // bytes of one 128-column block over all rows
+        int nbnd = 0, nedge = 0;
+        bool any_bad = false;
+        const int first = (item - tile * per) * ROWS;   // the item's first row in the tile
+#pragma unroll 1
+        for (int rof = first; rof < first + ROWS; rof += R) {
+            const int i0 = bi * kCompatTile + rof;
+            // lanes 0-31 stage the rows' source points, lanes 32-63 their targets
+            const int ri = i0 + (lane & 31);
+            const float3 p = *reinterpret_cast<const float3 *>((lane >> 5 ? dst : src) + 3 * min(ri, n - 1));
+            const bool bad = diag && (lane & 31) < R && ri < n && !(isfinite(p.x) && isfinite(p.y) && isfinite(p.z));
+            rows[wv][lane & 31][lane >> 5] = make_float4(p.x, p.y, p.z, 0.0f);
+            const bool wild = wild_col || __any(wild_point(p));
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            const int nr = min(R, n - i0);   // rows below n
+            const int top = max((nr + 1) & ~1, 0) - 1;   // rows in pairs from the last one; one past n is masked
+            float4 a1 = rows[wv][max(top, 0)][0], q1 = rows[wv][max(top, 0)][1];
+            // L0: the largest |x_i - x_j| of one row, so that L0 is near the L of most pairs
+            const float lx = a1.x - x[0].x, ly = a1.y - x[0].y, lz = a1.z - x[0].z;
+            const float L0 = fmaxf(2.0f * __builtin_amdgcn_sqrtf(wave_fmax(wild ? 0.0f : lx * lx + ly * ly + lz * lz)), 16.0f * tau);
+            const float g1 = tau * 0x1p-18f / L0, g0 = tau * __builtin_fmaf(L0, 0x1p-19f, 5e-6f);
+            uint64_t self[2] = {0, 0};   // diagonal tile: the lane holding row 0's own match
+            if (diag) self[rof >> 6] = 1ull << (rof & 63);
+            uint32_t col[2] = {0, 0};    // bit r: pair (i0 + r, j)
+            auto row = [&](int r, const float4 &a, const float4 &q) {
+                float E[2];
+                uint64_t near = 0;
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const float ax = a.x - x[c].x, ay = a.y - x[c].y, az = a.z - x[c].z;
+                    const float bx = q.x - y[c].x, by = q.y - y[c].y, bz = q.z - y[c].z;
+                    float s1 = ax * ax, s2 = bx * bx;
+                    s1 = __builtin_fmaf(ay, ay, s1);
+                    s2 = __builtin_fmaf(by, by, s2);
+                    s1 = __builtin_fmaf(az, az, s1);
+                    s2 = __builtin_fmaf(bz, bz, s2);
+                    const float df = s1 - s2, s = s1 + s2;
+                    E[c] = __builtin_fmaf(df, df, -__builtin_fmaf(t2, s, -t4));
+                    near |= __ballot(__builtin_fmaf(-__builtin_fmaf(g1, s, g0), s, __builtin_fabsf(E[c])) <= near_at[c]) &
+                            ~(self[c] << r);
+                }
+                if (wild || near) {
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) {
+                        const float l1 = length32(a.x - x[c].x, a.y - x[c].y, a.z - x[c].z);
+                        const float l2 = length32(q.x - y[c].x, q.y - y[c].y, q.z - y[c].z);
+                        const float dl = __builtin_fabsf(l1 - l2);
+                        E[c] = dl <= tau ? -1.0f : 1.0f;
+                        const int j = j0 + 64 * c;
+                        if (i0 + r < j && j < n && r < nr) nbnd += __builtin_fabsf(dl - tau) < 1e-6f;
+                    }
+                }
+#pragma unroll
+                for (int c = 0; c < 2; ++c) col[c] = __builtin_amdgcn_alignbit(col[c], __float_as_uint(E[c]), 31);
+            };
+            for (int r = top; r > 0; r -= 2) {
+                const float4 a0 = rows[wv][r - 1][0], q0 = rows[wv][r - 1][1];
+                row(r, a1, q1);
+                a1 = rows[wv][max(r - 2, 0)][0];
+                q1 = rows[wv][max(r - 2, 0)][1];
+                row(r - 1, a0, q0);
+            }
+            const uint32_t live = nr >= 32 ? 0xFFFFFFFFu : nr <= 0 ? 0u : (1u << nr) - 1u;
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const int j = j0 + 64 * c, k = j - i0;   // diagonal tile: rows r < k lie above it, r == k on it
+                col[c] = j < n ? col[c] & live : 0u;
+                if (diag && k >= 0 && k < 32) col[c] &= ~(1u << k);
+                nedge += __builtin_popcount(!diag ? col[c] : k <= 0 ? 0u : k >= 32 ? col[c] : col[c] & ((1u << k) - 1u));
+            }
+            if (!diag) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    uint8_t *o = Cb + (uint32_t)bi * kbs + (uint32_t)(j0 + 64 * c) * 16 + rof / 8;
+                    if (R == 32) *reinterpret_cast<uint32_t *>(o) = col[c];
+                    else if (R == 16) *reinterpret_cast<uint16_t *>(o) = (uint16_t)col[c];
+                    else *o = (uint8_t)col[c];
+                }
+            }
+            // lane (r, h): columns 32 h .. of row r in c0, 64 + 32 h .. in c1; the halves' exchange leaves words
+            // 2 h and 2 h + 1 of the row's four
+            uint32_t c0 = transpose32(col[0], lane), c1 = transpose32(col[1], lane);
+            swap_halves(c0, c1);
+            if ((lane & 31) < R)
+                *reinterpret_cast<uint2 *>(Cb + (uint32_t)bj * kbs + (uint32_t)(i0 + (lane & 31)) * 16 + 8 * (lane >> 5)) =
+                    make_uint2(c0, c1);
+            any_bad = any_bad || __any(bad);
+            if (diag && (lane & 31) < R && ri < n) {
+#pragma unroll
+                for (int g = 0; g < kHistGroups; g += 2)
+                    w.ghist[((int64_t)b * kHistGroups + g + (lane >> 5)) * w.hist_stride + ri] = 0;
+                const int64_t rw = (int64_t)b * w.max_n + ri;
+                if (lane < 32) w.rowmax[rw] = 0;
+                if (w.learned && lane < 32) {   // the SC2 row statistics and the row marks
+                    w.rowstat[rw * 20 + 1] = 0;
+                    w.rowstat[rw * 20 + 2] = 0;
+                    w.mark[rw] = 0;
+                }
+            }
+        }
+        const int sums = wave_sum((nbnd << 15) | nedge);   // at most 16384 pairs each
+        if (lane == 0) w.cnt_part[item] = (uint32_t)sums | ((uint32_t)any_bad << 30);
+    }
+}
+
+// The same matrix with the features' accumulators (training): per match the degree and a 16-bin
+// histogram of delta, always with the correctly rounded square root. One 64 x 64 tile (bi <= bj, a
+// quadrant of a list tile) per workgroup, each thread a 4 x 4 block of pairs, LDS histograms of the
+// tile's rows and columns added to the matches' accumulators.
+__global__ void __launch_bounds__(256, 2) k_compat_features(Work w)
+{
+    constexpr int kTile = 64;
+    auto tile64 = [](int local, int quad, int nb, int &bi, int &bj) {
+        tri_decode(local, nb, bi, bj);
+        bi = 2 * bi + ((quad >> 1) & 1);
+        bj = 2 * bj + (quad & 1);
+        return bi <= bj;
+    };
+    __shared__ float px[2][64][3], py[2][64][3];
+    __shared__ __attribute__((aligned(16))) uint8_t tile[2][64 * kNibStride];
+    __shared__ int32_t hrow[64][17], hcol[64][17];
+    __shared__ SlotCache slots;
+    const bool cached = slot_cache_fill(w, kCompat, slots);
+    __syncthreads();
+    const int total = 4 * stage_total(w, kCompat);
+    const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
     const float tau = w.tau, q = tau * 0.25f;
     // prefetch registers: thread t < 128 holds point (t & 63) of side t >> 6
     float nx[3] = {0, 0, 0}, ny[3] = {0, 0, 0};
     auto fetch = [&](int item) {
         if (tid < 128 && item < total) {
             int local;
-            const int b = stage_pair_cached(w, kCompat, slots, cached, item, local);
+            const int b = stage_pair_cached(w, kCompat, slots, cached, item >> 2, local);
             const PairDesc d = pair_desc(w, b);
             int bi, bj;
-            tri_decode(local, d.npad / kCompatTile, bi, bj);
-            const int i = ((tid >> 6) ? bj : bi) * kCompatTile + (tid & 63);
+            tile64(local, item & 3, d.npad / kCompatTile, bi, bj);
+            const int i = ((tid >> 6) ? bj : bi) * kTile + (tid & 63);
             for (int k = 0; k < 3; ++k) {
                 nx[k] = i < d.n ? w.src[3 * (int64_t)(d.pt_off + i) + k] : 0.0f;
                 ny[k] = i < d.n ? w.dst[3 * (int64_t)(d.pt_off + i) + k] : 0.0f;
             }
         }
     };
-    if (w.n1 && blockIdx.x == 0 && tid == 0) {   // a single-pair call has no planner: reset its state here
-        PairState st = {};
-        st.status = TR_OK;
-        w.state[0] = st;
-    }
     fetch(blockIdx.x);
     for (int item = blockIdx.x; item < total; item += gridDim.x) {
         int local;
-        const int b = stage_pair_cached(w, kCompat, slots, cached, item, local);
+        const int b = stage_pair_cached(w, kCompat, slots, cached, item >> 2, local);
         const PairDesc d = pair_desc(w, b);
         int bi, bj;
-        tri_decode(local, d.npad / kCompatTile, bi, bj);
+        if (!tile64(local, item & 3, d.npad / kCompatTile, bi, bj)) {   // the same for the whole workgroup
+            fetch(item + gridDim.x);
+            continue;
+        }
         const bool diag = bi == bj;
-        bool bad = false;
         if (tid < 128) {
             const int side = tid >> 6, r = tid & 63;
             for (int k = 0; k < 3; ++k) {
                 px[side][r][k] = nx[k];
                 py[side][r][k] = ny[k];
-                bad |= diag && side == 0 && !(isfinite(nx[k]) && isfinite(ny[k]));
             }
         }
-        if (diag) {   // the diagonal tiles clear this pair's histogram copies and row maxima for their 64 rows
-            for (int k = tid; k < kHistGroups * 64; k += 256) {
-                const int i = bi * kCompatTile + (k & 63);
-                if (i < d.n) w.ghist[((int64_t)b * kHistGroups + (k >> 6)) * w.hist_stride + i] = 0;
-            }
-            if (tid < 64 && bi * kCompatTile + tid < d.n) {
-                const int64_t ri = (int64_t)b * w.max_n + bi * kCompatTile + tid;
-                w.rowmax[ri] = 0;
-                if (!LEARNED && w.learned) {   // pool-feature mode: the SC2 row statistics and the row marks
-                    w.rowstat[ri * 20 + 1] = 0;
-                    w.rowstat[ri * 20 + 2] = 0;
-                    w.mark[ri] = 0;
-                }
-            }
-        }
-        if (LEARNED) {
-            for (int k = tid; k < 64 * 17; k += 256) { hrow[k / 17][k % 17] = 0; hcol[k / 17][k % 17] = 0; }
-        }
-        const bool any_bad = __any(bad);
+        for (int k = tid; k < 64 * 17; k += 256) { hrow[k / 17][k % 17] = 0; hcol[k / 17][k % 17] = 0; }
         __syncthreads();
         fetch(item + gridDim.x);
         float dl[4][4];
-        bool need_exact = LEARNED;
-        if (!LEARNED) {
 #pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                const int r = ty * 4 + a;
+        for (int a = 0; a < 4; ++a) {
+            const int r = ty * 4 + a;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int c = tx * 4 + e;
-                    float s1 = (px[0][r][0] - px[1][c][0]) * (px[0][r][0] - px[1][c][0]);
-                    s1 = __builtin_fmaf(px[0][r][1] - px[1][c][1], px[0][r][1] - px[1][c][1], s1);
-                    s1 = __builtin_fmaf(px[0][r][2] - px[1][c][2], px[0][r][2] - px[1][c][2], s1);
-                    float s2 = (py[0][r][0] - py[1][c][0]) * (py[0][r][0] - py[1][c][0]);
-                    s2 = __builtin_fmaf(py[0][r][1] - py[1][c][1], py[0][r][1] - py[1][c][1], s2);
-                    s2 = __builtin_fmaf(py[0][r][2] - py[1][c][2], py[0][r][2] - py[1][c][2], s2);
-                    const float la = __builtin_amdgcn_sqrtf(s1), lb = __builtin_amdgcn_sqrtf(s2);
-                    dl[a][e] = __builtin_fabsf(la - lb);
-                    need_exact |= near_tau(la, lb, dl[a][e], tau);
-                }
-            }
-        }
-        if (__any(need_exact)) {
-            if (need_exact) {
-#pragma unroll
-                for (int a = 0; a < 4; ++a) {
-                    const int r = ty * 4 + a;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int c = tx * 4 + e;
-                        const float lx = length32(px[0][r][0] - px[1][c][0], px[0][r][1] - px[1][c][1],
-                                                  px[0][r][2] - px[1][c][2]);
-                        const float ly = length32(py[0][r][0] - py[1][c][0], py[0][r][1] - py[1][c][1],
-                                                  py[0][r][2] - py[1][c][2]);
-                        dl[a][e] = __builtin_fabsf(lx - ly);
-                    }
-                }
+            for (int e = 0; e < 4; ++e) {
+                const int c = tx * 4 + e;
+                const float lx = length32(px[0][r][0] - px[1][c][0], px[0][r][1] - px[1][c][1],
+                                          px[0][r][2] - px[1][c][2]);
+                const float ly = length32(py[0][r][0] - py[1][c][0], py[0][r][1] - py[1][c][1],
+                                          py[0][r][2] - py[1][c][2]);
+                dl[a][e] = __builtin_fabsf(lx - ly);
             }
         }
         uint32_t rowbits[4] = {0, 0, 0, 0}, colbits[4] = {0, 0, 0, 0};
-        int nbnd = 0, nedge = 0;
-        // every pair of an interior tile (bi < bj, both blocks below n) is live with i < j: the
-        // edges are the bits set, and a boundary pair (|delta - tau| < 1e-6) can only occur in a
-        // lane that took the exact path (the guard band is wider)
-        const bool interior = !LEARNED && bi < bj && (bj + 1) * kCompatTile <= d.n;
-        if (interior) {
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
+        for (int a = 0; a < 4; ++a) {
+            const int r = ty * 4 + a, i = bi * kTile + r;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const uint32_t bit = dl[a][e] <= tau ? 1u : 0u;
-                    rowbits[a] |= bit << (8 * e);
-                    colbits[e] |= bit << (8 * a);
-                }
-            nedge = __builtin_popcount(rowbits[0]) + __builtin_popcount(rowbits[1]) + __builtin_popcount(rowbits[2]) +
-                    __builtin_popcount(rowbits[3]);
-            if (need_exact) {
+            for (int e = 0; e < 4; ++e) {
+                const int c = tx * 4 + e, j = bj * kTile + c;
+                const bool live = i != j && i < d.n && j < d.n;
+                const uint32_t bit = (live && dl[a][e] <= tau) ? 1u : 0u;
+                rowbits[a] |= bit << (8 * e);
+                colbits[e] |= bit << (8 * a);
+                if (live) {
+                    int bin = 0;
 #pragma unroll
-                for (int a = 0; a < 4; ++a)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) nbnd += __builtin_fabsf(dl[a][e] - tau) < 1e-6f;
-            }
-        } else {
-#pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                const int r = ty * 4 + a, i = bi * kCompatTile + r;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int c = tx * 4 + e, j = bj * kCompatTile + c;
-                    const bool live = i != j && i < d.n && j < d.n;
-                    const uint32_t bit = (live && dl[a][e] <= tau) ? 1u : 0u;
-                    rowbits[a] |= bit << (8 * e);
-                    colbits[e] |= bit << (8 * a);
-                    if (live && i < j) {
-                        nbnd += __builtin_fabsf(dl[a][e] - tau) < 1e-6f;
-                        nedge += (int)bit;
-                    }
-                    if (LEARNED && live) {
-                        int bin = 0;
-#pragma unroll
-                        for (int k = 1; k < 16; ++k) bin += dl[a][e] >= (float)k * q;
-                        atomicAdd(&hrow[r][bin], 1);
-                        atomicAdd(&hrow[r][16], (int)bit);
-                        if (!diag) {
-                            atomicAdd(&hcol[c][bin], 1);
-                            atomicAdd(&hcol[c][16], (int)bit);
-                        }
+                    for (int k = 1; k < 16; ++k) bin += dl[a][e] >= (float)k * q;
+                    atomicAdd(&hrow[r][bin], 1);
+                    atomicAdd(&hrow[r][16], (int)bit);
+                    if (!diag) {
+                        atomicAdd(&hcol[c][bin], 1);
+                        atomicAdd(&hcol[c][16], (int)bit);
                     }
                 }
             }
@@ -503,9 +641,6 @@ __global__ void __launch_bounds__(256, 2) k_compat(Work w)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             *reinterpret_cast<uint16_t *>(&tile[1][(tx * 4 + e) * kNibStride + ty * 2]) = (uint16_t)pack_e2m1(colbits[e]);
-        nbnd = wave_sum(nbnd);
-        nedge = wave_sum(nedge);
-        if (lane == 0) { red[wv][0] = nbnd; red[wv][1] = nedge; red[wv][2] = any_bad; }
         __syncthreads();
         if (tid < (diag ? 64 : 128)) {
             // the rows as bits (threads 0-63: the tile's rows, 64-127: its transpose), 8 bytes per
@@ -519,16 +654,15 @@ __global__ void __launch_bounds__(256, 2) k_compat(Work w)
             for (int k = 0; k < 8; ++k) word[k >> 2] |= nibbles_to_bits(nib[k]) << (8 * (k & 3));
             const int rb = side ? bj : bi, cb = side ? bi : bj;
             uint8_t *dst = w.C + d.c_off / 8 +
-                           ((int64_t)(cb >> 1) * d.npad + (int64_t)rb * kCompatTile + rr) * 16 + (cb & 1) * 8;
+                           ((int64_t)(cb >> 1) * d.npad + (int64_t)rb * kTile + rr) * 16 + (cb & 1) * 8;
             *reinterpret_cast<uint2 *>(dst) = make_uint2(word[0], word[1]);
         }
-        if (tid < 3) w.cnt_part[3 * (int64_t)item + tid] = red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid];
-        if (LEARNED) {
+        {
             for (int k = tid; k < 64 * 17; k += 256) {
                 const int rr = k / 17, f = k % 17;
                 // feature slots: 0 degree, 3..18 histogram
                 const int slot = f == 16 ? 0 : 3 + f;
-                const int i = bi * kCompatTile + rr, j = bj * kCompatTile + rr;
+                const int i = bi * kTile + rr, j = bj * kTile + rr;
                 if (i < d.n && hrow[rr][f]) atomicAdd(&w.rowstat[((int64_t)b * w.max_n + i) * 20 + slot], hrow[rr][f]);
                 if (!diag && j < d.n && hcol[rr][f]) atomicAdd(&w.rowstat[((int64_t)b * w.max_n + j) * 20 + slot], hcol[rr][f]);
             }
@@ -540,7 +674,6 @@ __global__ void __launch_bounds__(256, 2) k_compat(Work w)
 
 typedef int32_t v8i __attribute__((ext_vector_type(8)));
 typedef int32_t v16i __attribute__((ext_vector_type(16)));
-typedef float v16f __attribute__((ext_vector_type(16)));
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(1))) void gvoid;
@@ -607,21 +740,6 @@ __device__ __forceinline__ int half_sum(int v)
     v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
     v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
     return v;
-}
-
-// A value that is the same on every lane, in scalar registers.
-__device__ __forceinline__ int64_t uniform64(int64_t v)
-{
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-
-// Exchange of the wave's halves: a' = [a of lanes 0-31, b of lanes 0-31], b' = [a of 32-63, b of 32-63].
-__device__ __forceinline__ void swap_halves(uint32_t &a, uint32_t &b)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-    a = r[0];
-    b = r[1];
 }
 
 // Add the workgroup's LDS histogram of weights 1 .. top into the pair's global copy and clear it.
@@ -1167,10 +1285,25 @@ hipError_t launch_prep_learned(const Work &w, int grid, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_compat(const Work &w, int grid, hipStream_t s)
+// Rows per work item (one wave) of the compatibility kernel, for a list of `tiles` tiles: long items
+// amortise the item's loads and transposes, short ones spread a short list over the CUs.
+// Measured at 8 / 16 / 32 / 64 / 128 rows (us): N = 300 6.1 / 6.8 / 9.4, N = 1000 6.0 / 7.3 / 9.8,
+// N = 2749 (253 tiles) 9.1 / 9.0 / 10.8, N = 5000 (820) 20.5 / 18.3 / 17.2 / 19.7 / 29.7, N = 20000 (12403)
+// 199 / 143 / 116 / 112 / 107, 256 pairs 1580 / 1091 / 856 / 800 / 750. (With 64 x 64 tiles per workgroup, two
+// square roots a pair and packing through LDS: 6.1, 6.8, 10.6, 22.6, 229 and 2060.)
+int compat_rows(int64_t tiles, int num_cus)
 {
-    if (w.learned && w.feat_all) hipLaunchKernelGGL(k_compat<true>, dim3(grid), dim3(256), 0, s, w);
-    else hipLaunchKernelGGL(k_compat<false>, dim3(grid), dim3(256), 0, s, w);
+    return tiles <= num_cus ? 8 : tiles <= 2 * num_cus ? 16 : tiles <= 16 * num_cus ? 32 : 128;
+}
+
+// tiles: 128 x 128 tiles of the list; cap: workgroups to launch at most.
+hipError_t launch_compat(const Work &w, int64_t tiles, int cap, hipStream_t s)
+{
+    const bool features = w.learned && w.feat_all;   // a workgroup per 64 x 64 quadrant there
+    const int64_t wgs = features ? 4 * tiles : (tiles * (kCompatTile / w.compat_rows) + 3) / 4;
+    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(wgs, cap));
+    if (features) hipLaunchKernelGGL(k_compat_features, dim3(grid), dim3(256), 0, s, w);
+    else hipLaunchKernelGGL(k_compat, dim3(grid), dim3(256), 0, s, w);
     return hipGetLastError();
 }
 

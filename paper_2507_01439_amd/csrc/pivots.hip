@@ -112,18 +112,18 @@ __global__ void __launch_bounds__(1024) k_thresh(Work w)
     // the later kernels of the call update them
     for (int k = threadIdx.x; k < w.tick_stride / kTickLine; k += 1024) w.tick[(int64_t)b * w.tick_stride + k * kTickLine] = 0;
     if (K <= 0) return;
-    // boundary pairs, edges and non-finite input of the pair, summed over its compatibility tiles;
-    // the first eight tiles per thread are loaded together with the histogram
+    // boundary pairs, edges and non-finite input of the pair, summed over its compatibility items;
+    // the first eight items per thread are loaded together with the histogram
     constexpr int kTiles = 8;
-    const int t0 = stage_first(w, kCompat, b), t1 = t0 + stage_count(w, kCompat, b);
+    const int per = kCompatTile / w.compat_rows;   // work items per list tile
+    const int t0 = per * stage_first(w, kCompat, b), t1 = t0 + per * stage_count(w, kCompat, b);
     int cc[3] = {0, 0, 0};
-    int tv[kTiles][3];
+    uint32_t tv[kTiles];
     auto load_tiles = [&](int tb) {
 #pragma unroll
         for (int u = 0; u < kTiles; ++u) {
             const int t = tb + 1024 * u;
-#pragma unroll
-            for (int f = 0; f < 3; ++f) tv[u][f] = t < t1 ? w.cnt_part[3 * (int64_t)t + f] : 0;
+            tv[u] = t < t1 ? w.cnt_part[t] : 0;
         }
     };
     load_tiles(t0 + (int)threadIdx.x);
@@ -155,9 +155,11 @@ __global__ void __launch_bounds__(1024) k_thresh(Work w)
     }
     for (int tb = t0 + (int)threadIdx.x;;) {
 #pragma unroll
-        for (int u = 0; u < kTiles; ++u)
-#pragma unroll
-            for (int f = 0; f < 3; ++f) cc[f] += tv[u][f];
+        for (int u = 0; u < kTiles; ++u) {
+            cc[0] += (tv[u] >> 15) & 0x7FFFu;
+            cc[1] += tv[u] & 0x7FFFu;
+            cc[2] |= tv[u] >> 30;
+        }
         tb += 1024 * kTiles;
         if (tb >= t1) break;
         load_tiles(tb);

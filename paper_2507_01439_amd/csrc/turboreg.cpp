@@ -48,7 +48,8 @@ struct tr_handle {
     int32_t *pre = nullptr;
     uint8_t *C = nullptr;
     uint16_t *G = nullptr;
-    int32_t *ghist = nullptr, *rowmax = nullptr, *cnt_part = nullptr, *rowcnt = nullptr, *blkcnt = nullptr;
+    uint32_t *cnt_part = nullptr;
+    int32_t *ghist = nullptr, *rowmax = nullptr, *rowcnt = nullptr, *blkcnt = nullptr;
     uint64_t *cand = nullptr, *rowseg = nullptr, *hyp_rec = nullptr;
     int32_t *tick = nullptr;
     int32_t tick_stride = 0, rec_stride = 0;
@@ -153,8 +154,7 @@ void workspace_layout(tr_handle *h, Get &&get)
     get(h->G, B * nn);
     get(h->ghist, B * kHistGroups * (size_t)((max_n + 7) & ~(size_t)7));
     get(h->rowmax, B * max_n);
-    const size_t nb64 = h->npad_max / kCompatTile;
-    get(h->cnt_part, B * nb64 * (nb64 + 1) / 2 * 3);   // boundary pairs, edges, non-finite flag
+    get(h->cnt_part, B * (size_t)stage_items(kCompat, h->npad_max, 0) * (kCompatTile / kCompatMinRows));
     get(h->rowcnt, B * max_n);
     get(h->blkcnt, B * h->nblk_stride);
     get(h->cand, B * kCollectRegions * h->pool_cap);
@@ -299,7 +299,7 @@ tr_status enqueue(tr_handle *h, const Work &w_in, const int32_t *offsets, int32_
     w.sc2_sparse_cap = cfg.sc2_sparse_cap;
     const bool profile = ev != nullptr;
     const int64_t npad = (max_n + kSc2Tile - 1) / kSc2Tile * kSc2Tile;
-    const int64_t nb64 = npad / kCompatTile, nbs = npad / kSc2Tile;
+    const int64_t nbs = npad / kSc2Tile;
     const int64_t rows_items = (int64_t)B * ((max_n + kRowsPerItem - 1) / kRowsPerItem);
     // an event opens each stage that launches a kernel (and one closes the last); a stage without
     // a kernel records nothing, so no interval is an empty pair of events
@@ -322,7 +322,9 @@ tr_status enqueue(tr_handle *h, const Work &w_in, const int32_t *offsets, int32_
     if (w.learned && w.feat_all)
         chk(launch_prep_learned(w, grid_cap(h, (int64_t)B * ((max_n + kPrepRows - 1) / kPrepRows), 8), s));
     mark(TR_STAGE_COMPAT);
-    chk(launch_compat(w, grid_cap(h, (int64_t)B * nb64 * (nb64 + 1) / 2, cfg.compat_per_cu), s));
+    const int64_t tiles = B * stage_items(kCompat, max_n, 0);
+    w.compat_rows = compat_rows(tiles, h->num_cus);
+    chk(launch_compat(w, tiles, h->num_cus * cfg.compat_per_cu, s));
     mark(TR_STAGE_SC2);
     {
         // the kernel splits its items into 8 ranges, one per XCD (workgroup g runs on XCD g mod 8), of
