@@ -17,10 +17,8 @@ struct MlpState {
     float *m = nullptr, *v = nullptr;   // Adam moments
     uint16_t *wbf16 = nullptr;   // bfloat16 copies of all parameters (biases are read in float32)
     int32_t step = 0;            // Adam step count
-    float *scratch = nullptr;    // per-sample activations and deltas for the backward pass
-    int64_t scratch_m = 0;       // samples the scratch holds
-    float *partial = nullptr;    // per-tile gradient partial sums
-    int64_t partial_tiles = 0;
+    int32_t num_cus = 256;
+    float *partial = nullptr;    // gradient partial sums, one set per workgroup (at most one per CU)
     float *grads = nullptr;      // kGradSlots
 };
 

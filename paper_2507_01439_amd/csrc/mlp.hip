@@ -1,7 +1,9 @@
 // Learned pivot scorer on gfx950: per-match features, a 19 -> 64 -> 64 -> 1
 // GELU MLP with bfloat16 weights and activations and float32 accumulation,
 // the learned pivot reorder with plain SC2 order as fallback, and the
-// training kernels (forward/backward, weight-gradient reduction, Adam).
+// training kernels (forward/backward with the weight gradients, reduction and Adam).
+#include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "mlp.h"
@@ -22,16 +24,10 @@ __device__ __forceinline__ uint16_t f2bf(float f)
 __device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 __device__ __forceinline__ float bfround(float f) { return bf2f(f2bf(f)); }
 
-// tanh-form GELU (Hendrycks & Gimpel 2016) and its derivative.
+// tanh-form GELU (Hendrycks & Gimpel 2016).
 __device__ __forceinline__ float gelu(float x)
 {
     return 0.5f * x * (1.0f + tanhf(kGeluC * (x + 0.044715f * x * x * x)));
-}
-
-__device__ __forceinline__ float gelu_grad(float x)
-{
-    const float th = tanhf(kGeluC * (x + 0.044715f * x * x * x));
-    return 0.5f * (1.0f + th) + 0.5f * x * (1.0f - th * th) * kGeluC * (1.0f + 3.0f * 0.044715f * x * x);
 }
 
 // Parameters in LDS as float32: the weights are the bfloat16 copies, the biases the master values.
@@ -459,230 +455,452 @@ __global__ void __launch_bounds__(256) k_mlp_forward(const uint16_t *feat, int64
 
 // ---------------------------------------------------------------- training
 
-// Scratch of a training step, for m samples rounded up to whole tiles (mp): A1, A2, D1, D2
-// (64 floats per sample each, tile-major as Scratch::at places them), then DS[mp] and LS[mp].
-constexpr int kTile = 256;   // samples per weight-gradient work item
-constexpr int kSub = 32;     // samples staged in LDS at a time
-constexpr int kSubPad = kSub + 1;   // LDS row stride: the rows a wave reads at one sample fall in distinct banks
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 
-// Per-sample rows of the backward pass, tile-major: the 64 entries of sample n in one of the four
-// arrays are at at(f, n), f < 64, so the kTile samples of a weight-gradient work item occupy one
-// contiguous block of 64 x kTile floats per array (consecutive samples stay consecutive).
-struct Scratch {
-    float *a1, *a2, *d1, *d2, *ds, *ls;
-    __device__ __forceinline__ int64_t at(int f, int64_t n) const
-    {
-        return (n / kTile) * (64 * kTile) + f * kTile + n % kTile;
+// GELU and its derivative with one exponential and one reciprocal: with u = c (x + 0.044715 x^3),
+// (1 + tanh u) / 2 = sigma(2u) = s, so gelu = x s and gelu' = s + x s (1 - s) 2 u'. No cancellation for
+// negative x (1 + tanh u loses its digits there); the tanh form's call is some forty instructions.
+__device__ __forceinline__ void gelu_both(float x, float &a, float &g)
+{
+    constexpr float kL = -2.0f * kGeluC * 1.4426950408889634f;   // exp(-2u) = 2^(kL (x + 0.044715 x^3))
+    const float x2 = x * x;
+    const float p = 1.0f + __builtin_amdgcn_exp2f(fminf(x * __builtin_fmaf(0.044715f * kL, x2, kL), 126.0f));
+    const float s0 = __builtin_amdgcn_rcpf(p), s = __builtin_fmaf(__builtin_fmaf(-p, s0, 1.0f), s0, s0);   // one Newton step
+    a = x * s;
+    g = __builtin_fmaf(__builtin_fmaf(-a, s, a), __builtin_fmaf(6.0f * 0.044715f * kGeluC, x2, 2.0f * kGeluC), s);
+}
+
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)   // round to nearest even
+{
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((v2f{lo, hi}), v2bf));
+}
+
+__device__ __forceinline__ float lo_bf16(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float hi_bf16(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
+
+__device__ __forceinline__ v16f mfma_bf16(v4u a, v4u b, v16f c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
+}
+
+// x and y as three bfloat16 terms each (8 + 8 + 8 bits: x = t[0] + t[1] + t[2] exactly, short of
+// underflow), packed in pairs.
+__device__ __forceinline__ void split3(float x, float y, uint32_t (&t)[3])
+{
+    const uint32_t xu = __float_as_uint(x), yu = __float_as_uint(y);
+    t[0] = __builtin_amdgcn_perm(yu, xu, 0x07060302);
+    const float x1 = x - __uint_as_float(xu & 0xFFFF0000u), y1 = y - __uint_as_float(yu & 0xFFFF0000u);
+    const uint32_t x1u = __float_as_uint(x1), y1u = __float_as_uint(y1);
+    t[1] = __builtin_amdgcn_perm(y1u, x1u, 0x07060302);
+    const float x2 = x1 - __uint_as_float(x1u & 0xFFFF0000u), y2 = y1 - __uint_as_float(y1u & 0xFFFF0000u);
+    t[2] = __builtin_amdgcn_perm(__float_as_uint(y2), __float_as_uint(x2), 0x07060302);
+}
+
+// Accumulator layout to operand layout: the eight packed words of a 32 x 32 block (word 2g + h: rows
+// 8g + 4 lh + 2h, + 1 of the lane's column) become the two 16-row operands (lane: rows 16s + 8 lh .. + 7).
+__device__ __forceinline__ void to_operand(uint32_t (&p)[8], v4u (&f)[2])
+{
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const auto r = __builtin_amdgcn_permlane32_swap(p[4 * s + h], p[4 * s + 2 + h], false, false);
+            f[s][h] = r[0];
+            f[s][2 + h] = r[1];
+        }
     }
+}
+
+__device__ __forceinline__ void wave_fence()   // LDS written by the wave's lanes is visible to all of them
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+constexpr int kSamples = 32;    // samples per wave step
+constexpr int kTPitch = 72;     // bfloat16 per LDS row of 64: 16-byte reads of eight rows fall in distinct banks
+constexpr int kXPitch = 40;     // per LDS row of 32
+constexpr int kTrainWaves = 4;  // waves per workgroup, one per SIMD
+constexpr int kSums = 26;       // float4 a lane brings to the workgroup's sum
+
+struct TrainWave {              // a wave's own LDS
+    uint16_t t[3][kSamples * kTPitch];   // [sample][unit]: the features, layer 1's activations, the three
+                                         // terms of layer 2's deltas, in turn
+    uint16_t xt[32 * kXPitch];           // [feature][sample]; row 19 holds ones, rows 20 .. zeros
+    float ds[kSamples];
 };
 
-// Samples the scratch holds for m: whole tiles.
-__host__ __device__ __forceinline__ int64_t scratch_samples(int64_t m) { return (m + kTile - 1) / kTile * kTile; }
+struct TrainWeights {           // the workgroup's
+    uint16_t w1[64 * kXPitch];  // [unit][feature]; columns 19-21 the bias as three bfloat16 terms, then zeros
+    uint16_t w2[64 * kTPitch], w2t[64 * kTPitch];   // [out][in] and [in][out]
+};
 
-__device__ __forceinline__ Scratch scratch_view(float *base, int64_t m)
-{
-    const int64_t mp = scratch_samples(m);
-    Scratch s;
-    s.a1 = base;
-    s.a2 = base + 64 * mp;
-    s.d1 = base + 128 * mp;
-    s.d2 = base + 192 * mp;
-    s.ds = base + 256 * mp;
-    s.ls = base + 257 * mp;
-    return s;
-}
+static_assert(kTrainWaves == 4, "the workgroup's sum adds four slots");
+constexpr size_t kStepLds = sizeof(TrainWeights) + kTrainWaves * sizeof(TrainWave);
+constexpr size_t kSumLds = (size_t)kTrainWaves * kSums * 64 * 16;
+constexpr size_t kTrainLds = kStepLds > kSumLds ? kStepLds : kSumLds;
 
-// Per sample: forward (bfloat16 activations), BCE-with-logits loss and the
-// deltas of the backward pass. ds is already divided by m (mean loss).
-__global__ void __launch_bounds__(256) k_mlp_fwdbwd(const uint16_t *feat, const uint8_t *labels, int64_t m,
-                                                    float *scratch, const uint16_t *wbf16, const float *w32)
+// Gradients (and loss) of the mean BCE-with-logits over m samples, one wave per 32 samples: forward,
+// backward and the weight gradients in one pass, nothing per sample in memory. Each layer is a
+// contraction on the matrix cores (v_mfma_f32_32x32x16_bf16, float32 sums). The weights, features and
+// activations are bfloat16, so the forward products are exact; the deltas stay float32: each is split
+// into three bfloat16 terms whose sum is the delta itself, and their three products run on the same
+// instruction. Against float64 the gradients' error is a third of the float32 multiply-adds' (1e-7 to 3e-7
+// relative over m = 2125 .. 200000, 4e-7 to 5e-7 before).
+//
+// Accumulators hold one unit per lane and 16 of the samples, (lane: unit l31 of a 32-block; entry r:
+// sample 8 (r / 4) + 4 lh + r % 4). With deltas and activations in that layout the weight gradients
+// (contractions over the samples) take their operands by exchanges between the wave's halves alone; the
+// two products over units (layer 2 forward, and back to layer 1) read them as [sample][unit] from the
+// wave's LDS. Ones beside the features make the layer-1 bias (three bfloat16 terms) and its gradient
+// columns of the same products.
+//
+// Waves step through the samples with their gradient sums in registers; the workgroup adds its waves'
+// sums pairwise through LDS and writes one partial, and k_mlp_reduce adds the partials, all in a fixed
+// order. At m = 65536 this and the reduction take 26.2 + 4.5 us, at m = 2125 16.4 + 4.0 (a thread per sample
+// with the activations and deltas in memory, weight gradients by a second kernel: 111.5 + 35.5 + 13.3 and
+// 92.6 + 30.1 + 4.7). What bounds it is vector issue (64 GELUs, their gradients and the splits per lane and
+// step) with one wave per SIMD: two waves per SIMD need at most 256 registers and spilled 230 (65 us).
+__global__ void __launch_bounds__(64 * kTrainWaves) k_mlp_train(const uint16_t *feat, const uint8_t *labels, int64_t m,
+                                                       const uint16_t *wbf16, const float *w32, float *partial)
 {
-    __shared__ MlpLds L;
-    load_params(L, wbf16, w32);
-    __syncthreads();
-    const Scratch S = scratch_view(scratch, m);
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    TrainWeights &W = *reinterpret_cast<TrainWeights *>(smem);
+    const int tid = threadIdx.x, lane = tid & 63, l31 = lane & 31, lh = lane >> 5;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    TrainWave &L = *reinterpret_cast<TrainWave *>(smem + sizeof(TrainWeights) + wv * sizeof(TrainWave));
+    const int64_t tiles = (m + kSamples - 1) / kSamples, stride = (int64_t)gridDim.x * kTrainWaves;
+    int64_t tile = (int64_t)blockIdx.x * kTrainWaves + wv;
     const float inv_m = 1.0f / (float)m;
-    for (int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x; n < m; n += (int64_t)gridDim.x * 256) {
-        float x[19];
+    // a step's features, fetched ahead: lane's sample xn, features xk .. xk + 9 (two-byte loads: a slice of a
+    // feature table need not be aligned further)
+    const int xn = lane >> 1, xk = 10 * (lane & 1);
+    uint16_t xv[10];
+    auto fetch = [&](int64_t t) {
+        const bool ok = t * kSamples + xn < m;
+        const uint16_t *f = feat + (t * kSamples + xn) * 19 + xk;
 #pragma unroll
-        for (int k = 0; k < 19; ++k) x[k] = bf2f(feat[n * 19 + k]);
-        // forward; gelu'(z1) and gelu'(z2) are parked in the D1 / D2 slots
-        float a1[64];
-#pragma unroll
-        for (int o = 0; o < 64; ++o) {
-            float acc = L.p[kB1 + o];
-#pragma unroll
-            for (int k = 0; k < 19; ++k) acc = __builtin_fmaf(L.p[kW1 + 19 * o + k], x[k], acc);
-            a1[o] = bfround(gelu(acc));
-            S.d1[S.at(o, n)] = gelu_grad(acc);
-        }
-        float s = L.p[kB3];
-#pragma unroll 2
-        for (int o = 0; o < 64; ++o) {
-            float acc = L.p[kB2 + o];
-#pragma unroll
-            for (int k = 0; k < 64; ++k) acc = __builtin_fmaf(L.p[kW2 + 64 * o + k], a1[k], acc);
-            const float a = bfround(gelu(acc));
-            S.a2[S.at(o, n)] = a;
-            S.d2[S.at(o, n)] = gelu_grad(acc);
-            s = __builtin_fmaf(L.p[kW3 + o], a, s);
-        }
-#pragma unroll
-        for (int o = 0; o < 64; ++o) S.a1[S.at(o, n)] = a1[o];
-        // loss and backward
-        const float y = labels[n] ? 1.0f : 0.0f;
-        const float loss = fmaxf(s, 0.0f) - s * y + log1pf(expf(-fabsf(s)));
-        const float ds = (1.0f / (1.0f + expf(-s)) - y) * inv_m;
-        float d2[64];
-#pragma unroll
-        for (int o = 0; o < 64; ++o) {
-            d2[o] = ds * L.p[kW3 + o] * S.d2[S.at(o, n)];
-            S.d2[S.at(o, n)] = d2[o];
-        }
-#pragma unroll 2
-        for (int k = 0; k < 64; ++k) {
-            float acc = 0.0f;
-#pragma unroll
-            for (int o = 0; o < 64; ++o) acc = __builtin_fmaf(L.p[kW2 + 64 * o + k], d2[o], acc);
-            S.d1[S.at(k, n)] = acc * S.d1[S.at(k, n)];
-        }
-        S.ds[n] = ds;
-        S.ls[n] = loss * inv_m;
-    }
-}
-
-typedef float v16f __attribute__((ext_vector_type(16)));
-
-// Partial sums over one tile of samples of every gradient (and the loss).
-// The weight gradients are contractions over the samples: dW2 = D2^T A1 and
-// dW1 = D1^T X on float32 MFMA (32 x 32 x 2, float32 products and sums): wave
-// w owns the 32 x 32 block (w / 2, w % 2) of dW2, waves 0 and 1 also the rows
-// 32 w .. 32 w + 31 of dW1 (19 of 32 columns used). Thread t also sums one of
-// the vectors (db1, db2, dW3, db3, loss) in sample order.
-__global__ void __launch_bounds__(256) k_mlp_wgrad(const uint16_t *feat, int64_t m, const float *scratch,
-                                                   float *partial)
-{
-    __shared__ float sa1[64][kSubPad], sa2[64][kSubPad], sd1[64][kSubPad], sd2[64][kSubPad], sx[19][kSubPad], sds[kSub],
-        sls[kSub];
-    const Scratch S = scratch_view(const_cast<float *>(scratch), m);
-    const int t = threadIdx.x, w = t >> 6, li = t & 31, lk = (t >> 5) & 1;
-    const int ob = w >> 1, kb = w & 1;   // this wave's dW2 block: rows 32 ob.., columns 32 kb..
-    const int64_t n0 = (int64_t)blockIdx.x * kTile;
-    v16f acc2 = {}, acc1 = {};
-    float gv = 0.0f;
-    // staging: thread t moves entries idx = t + 256 u (u < kStageIt) of each kSub-sample block,
-    // row f = idx / kSub, sample c = idx % kSub; a block's loads are all issued into registers
-    // before any is used, and the next block's while the current one is summed
-    constexpr int kStageIt = 64 * kSub / 256;
-    float va1[kStageIt], va2[kStageIt], vd1[kStageIt], vd2[kStageIt], vx[kStageIt], vq = 0.0f;
-    auto fetch = [&](int sub) {
-#pragma unroll
-        for (int u = 0; u < kStageIt; ++u) {
-            const int idx = t + 256 * u, f = idx / kSub, c = idx % kSub;
-            const int64_t n = n0 + sub + c;
-            const bool ok = n < m;
-            va1[u] = ok ? S.a1[S.at(f, n)] : 0.0f;
-            va2[u] = ok ? S.a2[S.at(f, n)] : 0.0f;
-            vd1[u] = ok ? S.d1[S.at(f, n)] : 0.0f;
-            vd2[u] = ok ? S.d2[S.at(f, n)] : 0.0f;
-            vx[u] = ok && f < 19 ? bf2f(feat[n * 19 + f]) : 0.0f;
-            if (f == 19) vq = ok ? S.ds[n] : 0.0f;   // rows 19 and 20 (delta, loss) fall to different threads
-            if (f == 20) vq = ok ? S.ls[n] : 0.0f;
-        }
+        for (int u = 0; u < 10; ++u) xv[u] = ok && xk + u < 19 ? f[u] : 0;
     };
-    fetch(0);
-    for (int sub = 0; sub < kTile; sub += kSub) {
-#pragma unroll
-        for (int u = 0; u < kStageIt; ++u) {
-            const int idx = t + 256 * u, f = idx / kSub, c = idx % kSub;
-            sa1[f][c] = va1[u];
-            sa2[f][c] = va2[u];
-            sd1[f][c] = vd1[u];
-            sd2[f][c] = vd2[u];
-            if (f < 19) sx[f][c] = vx[u];
-            if (f == 19) sds[c] = vq;
-            if (f == 20) sls[c] = vq;
+    fetch(tile);
+    // ---- weights
+    for (int k = tid; k < 64 * kXPitch; k += 64 * kTrainWaves) {
+        const int o = k / kXPitch, c = k % kXPitch;
+        uint16_t v = 0;
+        if (c < 19) v = wbf16[kW1 + 19 * o + c];
+        else if (c < 22) {
+            uint32_t t[3];
+            split3(w32[kB1 + o], 0.0f, t);
+            v = (uint16_t)t[c - 19];
         }
-        __syncthreads();
-        if (sub + kSub < kTile) fetch(sub + kSub);
-        // two samples per MFMA: lane (li, lk) supplies row li of the A block and column li of the
-        // B block at sample c0 + lk
-#pragma unroll
-        for (int c0 = 0; c0 < kSub; c0 += 2) {
-            acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(sd2[32 * ob + li][c0 + lk], sa1[32 * kb + li][c0 + lk], acc2, 0,
-                                                        0, 0);
-            if (w < 2)
-                acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(sd1[32 * w + li][c0 + lk], li < 19 ? sx[li][c0 + lk] : 0.0f,
-                                                            acc1, 0, 0, 0);
-        }
-        // the vector sums, one per thread, over the block's samples in order (the branch is taken
-        // once per block, so each thread's reads are issued together)
-        if (t < 64) {
-#pragma unroll
-            for (int c = 0; c < kSub; ++c) gv += sd1[t][c];
-        } else if (t < 128) {
-#pragma unroll
-            for (int c = 0; c < kSub; ++c) gv += sd2[t - 64][c];
-        } else if (t < 192) {
-#pragma unroll
-            for (int c = 0; c < kSub; ++c) gv = __builtin_fmaf(sds[c], sa2[t - 128][c], gv);
-        } else if (t == 192) {
-#pragma unroll
-            for (int c = 0; c < kSub; ++c) gv += sds[c];
-        } else if (t == 193) {
-#pragma unroll
-            for (int c = 0; c < kSub; ++c) gv += sls[c];
-        }
-        __syncthreads();
+        W.w1[k] = v;
     }
+    for (int k = tid; k < 64 * 8; k += 64 * kTrainWaves) {
+        const int o = k >> 3, c = 8 * (k & 7);
+        const uint4 v = *reinterpret_cast<const uint4 *>(wbf16 + kW2 + 64 * o + c);
+        *reinterpret_cast<uint4 *>(&W.w2[o * kTPitch + c]) = v;
+        const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) W.w2t[(c + e) * kTPitch + o] = (uint16_t)(u[e >> 1] >> (16 * (e & 1)));
+    }
+    float w3[2], b2[2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        w3[b] = bf2f(wbf16[kW3 + 32 * b + l31]);
+        b2[b] = w32[kB2 + 32 * b + l31];
+    }
+    const float b3 = w32[kB3];
+    for (int k = lane; k < 13 * 32; k += 64) L.xt[(19 + (k >> 5)) * kXPitch + (k & 31)] = k < 32 ? 0x3F80 : 0;
+    __syncthreads();
+    auto frag = [&](const uint16_t *t, int pitch, int row, int s) {   // columns 16s + 8 lh .. + 7 of a row
+        return *reinterpret_cast<const v4u *>(&t[row * pitch + 16 * s + 8 * lh]);
+    };
+    v16f dw2[2][2] = {}, dw1[2] = {};
+    float db2[2] = {0, 0}, dw3[2] = {0, 0}, db3 = 0.0f, loss = 0.0f;
+    // this lane's sample after the logits' reduction over units (lanes 2k, 2k + 1 hold the same one)
+    const int mr = l31 >> 1, ms = 8 * (mr >> 2) + 4 * lh + (mr & 3);
+    for (; tile < tiles; tile += stride) {
+        const int64_t n0 = tile * kSamples;
+        const bool live = n0 + ms < m;
+        const float y = live && labels[n0 + ms] ? 1.0f : 0.0f;
+        // ---- features to LDS
+        uint16_t *X = L.t[0];
+#pragma unroll
+        for (int u = 0; u < 10; ++u) {
+            if (u < 9 || xk == 0) {
+                X[xn * kXPitch + xk + u] = xv[u];
+                L.xt[(xk + u) * kXPitch + xn] = xv[u];
+            }
+        }
+        if (lane < 32) {   // the ones beside the features, zeros behind
+            X[lane * kXPitch + 19] = 0x3F80;
+            *reinterpret_cast<uint2 *>(&X[lane * kXPitch + 20]) = make_uint2(0x3F803F80u, 0u);
+            *reinterpret_cast<uint4 *>(&X[lane * kXPitch + 24]) = make_uint4(0, 0, 0, 0);
+        }
+        wave_fence();
+        if (tile + stride < tiles) fetch(tile + stride);
+        // ---- layer 1: z1[n][o], a1 = bf16(gelu(z1)) packed by sample pairs, g1 = gelu'(z1)
+        float g1[2][16];
+        uint32_t a1[2][8];
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            v16f z = {};
+#pragma unroll
+            for (int s = 0; s < 2; ++s) z = mfma_bf16(frag(X, kXPitch, l31, s), frag(W.w1, kXPitch, 32 * b + l31, s), z);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                float p, q;
+                gelu_both(z[2 * k], p, g1[b][2 * k]);
+                gelu_both(z[2 * k + 1], q, g1[b][2 * k + 1]);
+                a1[b][k] = pack_bf16(p, q);
+            }
+        }
+        // entry pair k of a lane: samples 8 (k / 2) + 4 lh + 2 (k % 2), + 1
+        auto put = [&](uint16_t *t, int b, const uint32_t (&p)[8]) {   // to [sample][unit]
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                uint16_t *o = &t[(8 * (k >> 1) + 4 * lh + 2 * (k & 1)) * kTPitch + 32 * b + l31];
+                o[0] = (uint16_t)p[k];
+                o[kTPitch] = (uint16_t)(p[k] >> 16);
+            }
+        };
+        v4u fa[2][2];   // a1 as the operand of dW2
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            put(L.t[1], b, a1[b]);
+            to_operand(a1[b], fa[b]);
+        }
+        wave_fence();
+        // ---- layer 2 and the logit
+        float g2[2][16];
+        uint32_t a2[2][8];
+        {
+            v16f z[2];
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) z[b][r] = b2[b];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const v4u a = frag(L.t[1], kTPitch, l31, s);
+#pragma unroll
+                for (int b = 0; b < 2; ++b) z[b] = mfma_bf16(a, frag(W.w2, kTPitch, 32 * b + l31, s), z[b]);
+            }
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    float p, q;
+                    gelu_both(z[b][2 * k], p, g2[b][2 * k]);
+                    gelu_both(z[b][2 * k + 1], q, g2[b][2 * k + 1]);
+                    a2[b][k] = pack_bf16(p, q);
+                }
+        }
+        float pr[16];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            pr[2 * k] = __builtin_fmaf(w3[1], lo_bf16(a2[1][k]), w3[0] * lo_bf16(a2[0][k]));
+            pr[2 * k + 1] = __builtin_fmaf(w3[1], hi_bf16(a2[1][k]), w3[0] * hi_bf16(a2[0][k]));
+        }
+        // sums over the 32 units, halving the samples a lane holds at each exchange: lane l31 ends with
+        // sample entry l31 / 2
+        auto fold = [&](auto cnt, auto xo) {
+            constexpr int c = decltype(cnt)::value, x = decltype(xo)::value;
+            const bool up = l31 & x;
+#pragma unroll
+            for (int k = 0; k < c; ++k) {
+                const float keep = up ? pr[c + k] : pr[k], send = up ? pr[k] : pr[c + k];
+                pr[k] = keep + __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(send), (x << 10) | 0x1f));
+            }
+        };
+        fold(std::integral_constant<int, 8>{}, std::integral_constant<int, 16>{});
+        fold(std::integral_constant<int, 4>{}, std::integral_constant<int, 8>{});
+        fold(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
+        fold(std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{});
+        const float s = b3 + (pr[0] + __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(pr[0]), (1 << 10) | 0x1f)));
+        const float ds_n = live ? (1.0f / (1.0f + expf(-s)) - y) * inv_m : 0.0f;
+        if (!(lane & 1)) {
+            L.ds[ms] = ds_n;
+            db3 += ds_n;
+            if (live) loss += (fmaxf(s, 0.0f) - s * y + log1pf(expf(-fabsf(s)))) * inv_m;
+        }
+        wave_fence();
+        float ds[16];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const float4 v = *reinterpret_cast<const float4 *>(&L.ds[8 * g + 4 * lh]);
+            ds[4 * g] = v.x; ds[4 * g + 1] = v.y; ds[4 * g + 2] = v.z; ds[4 * g + 3] = v.w;
+        }
+        // ---- layer 2's deltas d2 = ds w3 gelu'(z2) in three terms; dW3, db2, dW2 = d2^T a1
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            uint32_t p[3][8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                dw3[b] = __builtin_fmaf(ds[2 * k], lo_bf16(a2[b][k]), dw3[b]);
+                dw3[b] = __builtin_fmaf(ds[2 * k + 1], hi_bf16(a2[b][k]), dw3[b]);
+                const float x = ds[2 * k] * w3[b] * g2[b][2 * k], z = ds[2 * k + 1] * w3[b] * g2[b][2 * k + 1];
+                db2[b] += x;
+                db2[b] += z;
+                uint32_t t[3];
+                split3(x, z, t);
+                p[0][k] = t[0];
+                p[1][k] = t[1];
+                p[2][k] = t[2];
+            }
+#pragma unroll
+            for (int q = 2; q >= 0; --q) {
+                put(L.t[q], b, p[q]);
+                v4u f[2];
+                to_operand(p[q], f);
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int kb = 0; kb < 2; ++kb) dw2[b][kb] = mfma_bf16(f[h], fa[kb][h], dw2[b][kb]);
+            }
+        }
+        wave_fence();
+        // ---- back to layer 1: d1 = (d2 W2) gelu'(z1); dW1 (and db1) = d1^T x
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+            v16f z = {};
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const v4u wf = frag(W.w2t, kTPitch, 32 * kb + l31, t);
+#pragma unroll
+                for (int q = 2; q >= 0; --q) z = mfma_bf16(frag(L.t[q], kTPitch, l31, t), wf, z);
+            }
+            uint32_t p[3][8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                uint32_t t[3];
+                split3(z[2 * k] * g1[kb][2 * k], z[2 * k + 1] * g1[kb][2 * k + 1], t);
+                p[0][k] = t[0];
+                p[1][k] = t[1];
+                p[2][k] = t[2];
+            }
+#pragma unroll
+            for (int q = 2; q >= 0; --q) {
+                v4u f[2];
+                to_operand(p[q], f);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) dw1[kb] = mfma_bf16(f[h], frag(L.xt, kXPitch, l31, h), dw1[kb]);
+            }
+        }
+        wave_fence();   // the wave's LDS is the next step's
+    }
+    // ---- the workgroup's sum: the waves' sums in LDS, then each thread adds its entries and writes the partial
+    float4 *slots = reinterpret_cast<float4 *>(smem);
+    auto give = [&]() {
+        float4 *o = slots + wv * kSums * 64 + lane;
+        auto four = [&](int at, float a, float b, float c, float d) { o[at * 64] = make_float4(a, b, c, d); };
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+                    four(8 * b + 4 * kb + g, dw2[b][kb][4 * g], dw2[b][kb][4 * g + 1], dw2[b][kb][4 * g + 2],
+                         dw2[b][kb][4 * g + 3]);
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                four(16 + 4 * b + g, dw1[b][4 * g], dw1[b][4 * g + 1], dw1[b][4 * g + 2], dw1[b][4 * g + 3]);
+        four(24, db2[0], db2[1], dw3[0], dw3[1]);
+        four(25, db3, loss, 0.0f, 0.0f);
+    };
+    __syncthreads();   // the steps' LDS is free
+    give();
+    __syncthreads();
+    auto total = [&](int e) {
+        const float4 a = slots[e], b = slots[e + kSums * 64], c = slots[e + 2 * kSums * 64], d = slots[e + 3 * kSums * 64];
+        return make_float4((a.x + b.x) + (c.x + d.x), (a.y + b.y) + (c.y + d.y), (a.z + b.z) + (c.z + d.z),
+                           (a.w + b.w) + (c.w + d.w));
+    };
     float *out = partial + (int64_t)blockIdx.x * kGradSlots;
-    // block entry (i, j) of register r in lane (li, lk): i = 8 (r / 4) + 4 lk + r % 4, j = li
+    for (int at = wv; at < 24; at += kTrainWaves) {   // rows o .. o + 3 of a weight gradient
+        const float4 v = total(at * 64 + lane);
+        const float e[4] = {v.x, v.y, v.z, v.w};
+        const int b = at < 16 ? at >> 3 : (at >> 2) & 1, o = 32 * b + 8 * (at & 3) + 4 * lh, k = 32 * ((at >> 2) & 1) + l31;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int i = 8 * (r >> 2) + 4 * lk + (r & 3);
-        out[kW2 + 64 * (32 * ob + i) + 32 * kb + li] = acc2[r];
-        if (w < 2 && li < 19) out[kW1 + 19 * (32 * w + i) + li] = acc1[r];
+        for (int j = 0; j < 4; ++j) {
+            if (at < 16) out[kW2 + 64 * (o + j) + k] = e[j];
+            else if (l31 < 19) out[kW1 + 19 * (o + j) + l31] = e[j];
+            else if (l31 == 19) out[kB1 + o + j] = e[j];
+        }
     }
-    if (t < 64) out[kB1 + t] = gv;
-    else if (t < 128) out[kB2 + t - 64] = gv;
-    else if (t < 192) out[kW3 + t - 128] = gv;
-    else if (t == 192) out[kB3] = gv;
-    else if (t == 193) out[TR_MLP_NPARAM] = gv;
+    if (wv == 0 && !lh) {   // a unit's two halves of the samples
+        const float4 v = total(24 * 64 + lane), u = total(24 * 64 + 32 + lane);
+        out[kB2 + lane] = v.x + u.x;
+        out[kB2 + 32 + lane] = v.y + u.y;
+        out[kW3 + lane] = v.z + u.z;
+        out[kW3 + 32 + lane] = v.w + u.w;
+    }
+    if (wv == 1) {
+        float4 v = total(25 * 64 + lane);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            v.x += __shfl_xor(v.x, o, 64);
+            v.y += __shfl_xor(v.y, o, 64);
+        }
+        if (lane == 0) {
+            out[kB3] = v.x;
+            out[TR_MLP_NPARAM] = v.y;
+        }
+    }
 }
 
-// Sum the tiles' partials in tile order (deterministic); the loads of kReduceBatch tiles are
-// issued together, then added one after another.
+// Adam's step for one parameter (float32 master weight, bfloat16 copy).
+struct AdamArgs {
+    float *w, *mo, *ve;
+    uint16_t *wbf16;
+    float lr, c1, c2;
+};
+
+// Sum of the workgroups' partials per gradient slot, in a fixed order: four quarters of the list in
+// order, then the quarters; kReduceBatch loads are issued together. With ADAM the parameter is
+// updated at once.
 constexpr int kReduceBatch = 32;
-__global__ void __launch_bounds__(256) k_mlp_reduce(const float *partial, int64_t tiles, float *grads, float *loss)
+template <bool ADAM>
+__global__ void __launch_bounds__(256) k_mlp_reduce(const float *partial, int parts, float *grads, float *loss,
+                                                    AdamArgs ad)
 {
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= kGradSlots) return;
+    __shared__ float quarter[4][64];
+    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6, p = blockIdx.x * 64 + lane;
+    const int per = (parts + 3) / 4, t0 = q * per, t1 = min(parts, t0 + per);
     float acc = 0.0f;
-    for (int64_t t0 = 0; t0 < tiles; t0 += kReduceBatch) {
+    for (int t = t0; t < t1; t += kReduceBatch) {
         float v[kReduceBatch];
 #pragma unroll
-        for (int u = 0; u < kReduceBatch; ++u) v[u] = t0 + u < tiles ? partial[(t0 + u) * kGradSlots + p] : 0.0f;
-#pragma unroll
         for (int u = 0; u < kReduceBatch; ++u)
-            if (t0 + u < tiles) acc += v[u];
+            v[u] = t + u < t1 && p < kGradSlots ? partial[(int64_t)(t + u) * kGradSlots + p] : 0.0f;
+#pragma unroll
+        for (int u = 0; u < kReduceBatch; ++u) acc += v[u];
     }
-    if (p < TR_MLP_NPARAM) grads[p] = acc;
-    else if (loss) *loss = acc;
-}
-
-__global__ void __launch_bounds__(256) k_adam(float *w, float *mo, float *ve, uint16_t *wbf16, const float *g,
-                                              float lr, float c1, float c2)
-{
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= TR_MLP_NPARAM) return;
-    const float gp = g[p];
-    const float m = 0.9f * mo[p] + 0.1f * gp;
-    const float v = 0.999f * ve[p] + 0.001f * gp * gp;
-    mo[p] = m;
-    ve[p] = v;
-    const float nw = w[p] - lr * (m / c1) / (sqrtf(v / c2) + 1e-8f);
-    w[p] = nw;
-    wbf16[p] = f2bf(nw);
+    quarter[q][lane] = acc;
+    __syncthreads();
+    if (q != 0 || p >= kGradSlots) return;
+    const float g = (quarter[0][lane] + quarter[1][lane]) + (quarter[2][lane] + quarter[3][lane]);
+    if (p == TR_MLP_NPARAM) {
+        if (loss) *loss = g;
+        return;
+    }
+    grads[p] = g;
+    if (ADAM) {
+        const float m = 0.9f * ad.mo[p] + 0.1f * g;
+        const float v = 0.999f * ad.ve[p] + 0.001f * g * g;
+        ad.mo[p] = m;
+        ad.ve[p] = v;
+        const float nw = ad.w[p] - ad.lr * (m / ad.c1) / (sqrtf(v / ad.c2) + 1e-8f);
+        ad.w[p] = nw;
+        ad.wbf16[p] = f2bf(nw);
+    }
 }
 
 __global__ void k_to_bf16(const float *w, uint16_t *wbf16, int n)
@@ -697,34 +915,16 @@ int grid_for(int64_t m)
     return (int)(g < 4096 ? (g > 0 ? g : 1) : 4096);
 }
 
-hipError_t ensure_scratch(MlpState *s, int64_t m)
-{
-    if (s->scratch_m < m) {
-        if (s->scratch) hipFree(s->scratch);
-        s->scratch = nullptr;
-        s->scratch_m = 0;
-        hipError_t e = hipMalloc(&s->scratch, sizeof(float) * 258 * (size_t)scratch_samples(m));
-        if (e != hipSuccess) return e;
-        s->scratch_m = m;
-    }
-    const int64_t tiles = (m + kTile - 1) / kTile;
-    if (s->partial_tiles < tiles) {
-        if (s->partial) hipFree(s->partial);
-        s->partial = nullptr;
-        s->partial_tiles = 0;
-        hipError_t e = hipMalloc(&s->partial, sizeof(float) * kGradSlots * (size_t)tiles);
-        if (e != hipSuccess) return e;
-        s->partial_tiles = tiles;
-    }
-    return hipSuccess;
-}
-
 }  // namespace
 
 hipError_t setup_mlp_kernels()
 {
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(k_reorder), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               TR_MAX_POOL * (int)sizeof(uint64_t));
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_reorder),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, TR_MAX_POOL * (int)sizeof(uint64_t));
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_mlp_train), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)kTrainLds);
+    return e;
 }
 
 hipError_t mlp_create(MlpState *s)
@@ -734,13 +934,18 @@ hipError_t mlp_create(MlpState *s)
     if (e == hipSuccess) e = hipMalloc(&s->v, sizeof(float) * TR_MLP_NPARAM);
     if (e == hipSuccess) e = hipMalloc(&s->wbf16, sizeof(uint16_t) * TR_MLP_NPARAM);
     if (e == hipSuccess) e = hipMalloc(&s->grads, sizeof(float) * kGradSlots);
+    int device = 0, cus = 0;
+    if (e == hipSuccess) e = hipGetDevice(&device);
+    if (e == hipSuccess && hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && cus > 0)
+        s->num_cus = cus;
+    if (e == hipSuccess) e = hipMalloc(&s->partial, sizeof(float) * kGradSlots * (size_t)s->num_cus);
     return e;
 }
 
 void mlp_release(MlpState *s)
 {
     for (void *p : {(void *)s->w32, (void *)s->m, (void *)s->v, (void *)s->wbf16, (void *)s->grads,
-                    (void *)s->scratch, (void *)s->partial})
+                    (void *)s->partial})
         if (p) hipFree(p);
     *s = MlpState();
 }
@@ -773,30 +978,43 @@ hipError_t mlp_forward(MlpState *s, const uint16_t *feat, int64_t m, float *scor
     return hipGetLastError();
 }
 
+namespace {
+
+// Partials of the gradients over m samples, one per workgroup (*parts of them, at most one per CU).
+hipError_t launch_train(MlpState *s, const uint16_t *feat, const uint8_t *labels, int64_t m, int *parts, hipStream_t st)
+{
+    const int64_t tiles = (m + kSamples - 1) / kSamples;
+    *parts = (int)std::min<int64_t>((tiles + kTrainWaves - 1) / kTrainWaves, s->num_cus);
+    hipLaunchKernelGGL(k_mlp_train, dim3(*parts), dim3(64 * kTrainWaves), kTrainLds, st, feat, labels, m, s->wbf16, s->w32,
+                       s->partial);
+    return hipGetLastError();
+}
+
+}  // namespace
+
 hipError_t mlp_grads(MlpState *s, const uint16_t *feat, const uint8_t *labels, int64_t m, float *grads, float *loss,
                      hipStream_t st)
 {
-    hipError_t e = ensure_scratch(s, m);
+    int parts = 0;
+    const hipError_t e = launch_train(s, feat, labels, m, &parts, st);
     if (e != hipSuccess) return e;
-    const int64_t tiles = (m + kTile - 1) / kTile;
-    hipLaunchKernelGGL(k_mlp_fwdbwd, dim3(grid_for(m)), dim3(256), 0, st, feat, labels, m, s->scratch, s->wbf16,
-                       s->w32);
-    hipLaunchKernelGGL(k_mlp_wgrad, dim3((unsigned)tiles), dim3(256), 0, st, feat, m, s->scratch, s->partial);
-    hipLaunchKernelGGL(k_mlp_reduce, dim3((kGradSlots + 255) / 256), dim3(256), 0, st, s->partial, tiles, grads, loss);
+    hipLaunchKernelGGL(k_mlp_reduce<false>, dim3((kGradSlots + 63) / 64), dim3(256), 0, st, s->partial, parts, grads, loss,
+                       AdamArgs{});
     return hipGetLastError();
 }
 
 hipError_t mlp_train_step(MlpState *s, const uint16_t *feat, const uint8_t *labels, int64_t m, float lr, float *loss,
                           hipStream_t st)
 {
-    hipError_t e = mlp_grads(s, feat, labels, m, s->grads, loss, st);
+    int parts = 0;
+    const hipError_t e = launch_train(s, feat, labels, m, &parts, st);
     if (e != hipSuccess) return e;
     s->step += 1;
     // bias corrections 1 - beta^t in float64: in float32, 1 - 0.999^t loses ~3e-5 relative to
     // cancellation at small t, which would move every early step by as much
     const float c1 = (float)(1.0 - pow(0.9, (double)s->step)), c2 = (float)(1.0 - pow(0.999, (double)s->step));
-    hipLaunchKernelGGL(k_adam, dim3((TR_MLP_NPARAM + 255) / 256), dim3(256), 0, st, s->w32, s->m, s->v, s->wbf16,
-                       s->grads, lr, c1, c2);
+    hipLaunchKernelGGL(k_mlp_reduce<true>, dim3((kGradSlots + 63) / 64), dim3(256), 0, st, s->partial, parts, s->grads,
+                       loss, AdamArgs{s->w32, s->m, s->v, s->wbf16, lr, c1, c2});
     return hipGetLastError();
 }
 
