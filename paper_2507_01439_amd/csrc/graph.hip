@@ -280,42 +280,10 @@ __global__ void __launch_bounds__(1024) k_plan(const int32_t *offsets, int32_t n
     }
 }
 
-// Learned mode: zero the per-row feature accumulators.
-__global__ void __launch_bounds__(256) k_prep_learned(Work w)
-{
-    const int total = stage_total(w, kPrep);
-    for (int item = blockIdx.x; item < total; item += gridDim.x) {
-        int local;
-        const int b = stage_pair(w, kPrep, item, local);
-        const int i = local * kPrepRows + threadIdx.x;
-        if (i < pair_desc(w, b).n) {
-            int32_t *rs = w.rowstat + ((int64_t)b * w.max_n + i) * 20;
-            for (int f = 0; f < 20; ++f) rs[f] = 0;
-        }
-    }
-}
-
 // ---------------------------------------------------------------- Eq. 1
 
 typedef float v16f __attribute__((ext_vector_type(16)));
 
-
-constexpr int kNibStride = 32;    // LDS row stride of a packed 64-column tile (two entries per byte)
-
-// Four 0/1 bytes -> four E2M1 nibbles (1.0 = 0x2, 0.0 = 0x0), byte k -> bits 4k..4k+3.
-__device__ __forceinline__ uint32_t pack_e2m1(uint32_t x)
-{
-    return ((x << 1) & 0x2u) | ((x >> 3) & 0x20u) | ((x >> 7) & 0x200u) | ((x >> 11) & 0x2000u);
-}
-
-// Eight E2M1 entries (0x2 = 1, 0x0 = 0) of a packed word -> eight bits, entry k -> bit k.
-__device__ __forceinline__ uint32_t nibbles_to_bits(uint32_t x)
-{
-    x = (x >> 1) & 0x11111111u;          // entry k at bit 4k
-    x = (x | (x >> 3)) & 0x03030303u;    // entries 2m, 2m+1 at bits 8m, 8m+1
-    x = (x | (x >> 6)) & 0x000F000Fu;    // at bits 16m .. 16m+3
-    return (x | (x >> 12)) & 0xFFu;
-}
 
 // A value that is the same on every lane, in scalar registers.
 __device__ __forceinline__ int64_t uniform64(int64_t v)
@@ -539,134 +507,113 @@ __global__ void __launch_bounds__(256) k_compat(Work w)
 }
 
 // The same matrix with the features' accumulators (training): per match the degree and a 16-bin
-// histogram of delta, always with the correctly rounded square root. One 64 x 64 tile (bi <= bj, a
-// quadrant of a list tile) per workgroup, each thread a 4 x 4 block of pairs, LDS histograms of the
-// tile's rows and columns added to the matches' accumulators.
-__global__ void __launch_bounds__(256, 2) k_compat_features(Work w)
+// histogram of delta over all other matches. A lane holds one row's point and the columns' points are
+// broadcast from LDS, so each row's counts stay with its lane (an LDS word per bin and lane, which its own
+// lane alone updates in a wave: no conflicts and no atomics in memory) and its bits of C shift into words
+// in place. Every pair is evaluated from both sides (twice the arithmetic of the triangle), which cost less
+// than adding the columns' counts across lanes: 64 pairs of 1000 to 5000 matches 598 us (with the clearing launch it needs no more), 1549 for
+// 64 x 64 tiles with LDS histograms of rows and columns added in memory and correctly rounded roots throughout.
+//
+// Bins: t = delta / q (q = tau / 4) with the hardware square roots; a pair whose delta lies within
+// 2^-19 (|x| + |y|) + 2e-6 + 2^-17 q of the nearest bin edge (tau is edge 4; |y| <= |x| + 4 tau there) is
+// evaluated again with the correctly rounded ones, so every bin and bit is the exact one. One workgroup per
+// 64 rows (a quarter of a list item of kPrepRows rows), the 64-column blocks dealt to its waves; the sums
+// are written whole, the SC2 sums cleared for the next kernel.
+constexpr int kFeatWaves = 8;
+__global__ void __launch_bounds__(64 * kFeatWaves) k_compat_features(Work w)
 {
-    constexpr int kTile = 64;
-    auto tile64 = [](int local, int quad, int nb, int &bi, int &bj) {
-        tri_decode(local, nb, bi, bj);
-        bi = 2 * bi + ((quad >> 1) & 1);
-        bj = 2 * bj + (quad & 1);
-        return bi <= bj;
-    };
-    __shared__ float px[2][64][3], py[2][64][3];
-    __shared__ __attribute__((aligned(16))) uint8_t tile[2][64 * kNibStride];
-    __shared__ int32_t hrow[64][17], hcol[64][17];
-    __shared__ SlotCache slots;
-    const bool cached = slot_cache_fill(w, kCompat, slots);
-    __syncthreads();
-    const int total = 4 * stage_total(w, kCompat);
-    const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
-    const float tau = w.tau, q = tau * 0.25f;
-    // prefetch registers: thread t < 128 holds point (t & 63) of side t >> 6
-    float nx[3] = {0, 0, 0}, ny[3] = {0, 0, 0};
-    auto fetch = [&](int item) {
-        if (tid < 128 && item < total) {
-            int local;
-            const int b = stage_pair_cached(w, kCompat, slots, cached, item >> 2, local);
-            const PairDesc d = pair_desc(w, b);
-            int bi, bj;
-            tile64(local, item & 3, d.npad / kCompatTile, bi, bj);
-            const int i = ((tid >> 6) ? bj : bi) * kTile + (tid & 63);
-            for (int k = 0; k < 3; ++k) {
-                nx[k] = i < d.n ? w.src[3 * (int64_t)(d.pt_off + i) + k] : 0.0f;
-                ny[k] = i < d.n ? w.dst[3 * (int64_t)(d.pt_off + i) + k] : 0.0f;
-            }
-        }
-    };
-    fetch(blockIdx.x);
+    __shared__ float4 cols[kFeatWaves][64][2];
+    __shared__ int32_t hist[16][64], deg[64];
+    const int total = (kPrepRows / 64) * stage_total(w, kPrep);
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const float tau = w.tau, q = tau * 0.25f, inv_q = 1.0f / q;
+    const float band0 = __builtin_fmaf(tau, 0x1p-17f, __builtin_fmaf(q, 0x1p-17f, 2.1e-6f));
     for (int item = blockIdx.x; item < total; item += gridDim.x) {
         int local;
-        const int b = stage_pair_cached(w, kCompat, slots, cached, item >> 2, local);
+        const int b = __builtin_amdgcn_readfirstlane(stage_pair(w, kPrep, item / (kPrepRows / 64), local));
         const PairDesc d = pair_desc(w, b);
-        int bi, bj;
-        if (!tile64(local, item & 3, d.npad / kCompatTile, bi, bj)) {   // the same for the whole workgroup
-            fetch(item + gridDim.x);
-            continue;
-        }
-        const bool diag = bi == bj;
-        if (tid < 128) {
-            const int side = tid >> 6, r = tid & 63;
-            for (int k = 0; k < 3; ++k) {
-                px[side][r][k] = nx[k];
-                py[side][r][k] = ny[k];
-            }
-        }
-        for (int k = tid; k < 64 * 17; k += 256) { hrow[k / 17][k % 17] = 0; hcol[k / 17][k % 17] = 0; }
+        const int n = __builtin_amdgcn_readfirstlane(d.n), npad = __builtin_amdgcn_readfirstlane(d.npad);
+        const int i0 = __builtin_amdgcn_readfirstlane(local) * kPrepRows + 64 * (item % (kPrepRows / 64)), i = i0 + lane;
+        const float *src = w.src + 3 * (int64_t)d.pt_off, *dst = w.dst + 3 * (int64_t)d.pt_off;
+        const float3 x = *reinterpret_cast<const float3 *>(src + 3 * min(i, n - 1));
+        const float3 y = *reinterpret_cast<const float3 *>(dst + 3 * min(i, n - 1));
+        for (int k = tid; k < 16 * 64; k += 64 * kFeatWaves) hist[k >> 6][k & 63] = 0;
+        if (tid < 64) deg[tid] = 0;
         __syncthreads();
-        fetch(item + gridDim.x);
-        float dl[4][4];
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            const int r = ty * 4 + a;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int c = tx * 4 + e;
-                const float lx = length32(px[0][r][0] - px[1][c][0], px[0][r][1] - px[1][c][1],
-                                          px[0][r][2] - px[1][c][2]);
-                const float ly = length32(py[0][r][0] - py[1][c][0], py[0][r][1] - py[1][c][1],
-                                          py[0][r][2] - py[1][c][2]);
-                dl[a][e] = __builtin_fabsf(lx - ly);
-            }
-        }
-        uint32_t rowbits[4] = {0, 0, 0, 0}, colbits[4] = {0, 0, 0, 0};
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            const int r = ty * 4 + a, i = bi * kTile + r;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int c = tx * 4 + e, j = bj * kTile + c;
-                const bool live = i != j && i < d.n && j < d.n;
-                const uint32_t bit = (live && dl[a][e] <= tau) ? 1u : 0u;
-                rowbits[a] |= bit << (8 * e);
-                colbits[e] |= bit << (8 * a);
-                if (live) {
-                    int bin = 0;
-#pragma unroll
-                    for (int k = 1; k < 16; ++k) bin += dl[a][e] >= (float)k * q;
-                    atomicAdd(&hrow[r][bin], 1);
-                    atomicAdd(&hrow[r][16], (int)bit);
-                    if (!diag) {
-                        atomicAdd(&hcol[c][bin], 1);
-                        atomicAdd(&hcol[c][16], (int)bit);
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-            *reinterpret_cast<uint16_t *>(&tile[0][(ty * 4 + a) * kNibStride + tx * 2]) = (uint16_t)pack_e2m1(rowbits[a]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            *reinterpret_cast<uint16_t *>(&tile[1][(tx * 4 + e) * kNibStride + ty * 2]) = (uint16_t)pack_e2m1(colbits[e]);
-        __syncthreads();
-        if (tid < (diag ? 64 : 128)) {
-            // the rows as bits (threads 0-63: the tile's rows, 64-127: its transpose), 8 bytes per
-            // row into the 16-byte piece of the row's 128-column block
-            const int side = tid >> 6, rr = tid & 63;
-            const uint4 *src = reinterpret_cast<const uint4 *>(&tile[side][rr * kNibStride]);
-            const uint4 lo = src[0], hi = src[1];
-            const uint32_t nib[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+        __attribute__((address_space(3))) int32_t *h = (__attribute__((address_space(3))) int32_t *)&hist[0][lane];
+        uint8_t *Cb = w.C + uniform64(d.c_off) / 8 + (uint32_t)i * 16;
+        const uint32_t kbs = (uint32_t)npad * 16;   // bytes of one 128-column block over all rows
+        int degree = 0;
+        const int nblk = npad / 64;
+        float3 px, py;   // the next block's points: lane's column
+        auto fetch = [&](int blk) {
+            const int jc = min(64 * blk + lane, n - 1);
+            px = *reinterpret_cast<const float3 *>(src + 3 * jc);
+            py = *reinterpret_cast<const float3 *>(dst + 3 * jc);
+        };
+        fetch(min(wv, nblk - 1));
+        for (int blk = wv; blk < nblk; blk += kFeatWaves) {
+            const int j0 = 64 * blk, cnt = i0 < n ? min(64, n - j0) : 0;   // columns below n
+            __builtin_amdgcn_wave_barrier();   // the block before is read
+            cols[wv][lane][0] = make_float4(px.x, px.y, px.z, 0.0f);
+            cols[wv][lane][1] = make_float4(py.x, py.y, py.z, 0.0f);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            if (blk + kFeatWaves < nblk) fetch(blk + kFeatWaves);
             uint32_t word[2] = {0, 0};
 #pragma unroll
-            for (int k = 0; k < 8; ++k) word[k >> 2] |= nibbles_to_bits(nib[k]) << (8 * (k & 3));
-            const int rb = side ? bj : bi, cb = side ? bi : bj;
-            uint8_t *dst = w.C + d.c_off / 8 +
-                           ((int64_t)(cb >> 1) * d.npad + (int64_t)rb * kTile + rr) * 16 + (cb & 1) * 8;
-            *reinterpret_cast<uint2 *>(dst) = make_uint2(word[0], word[1]);
-        }
-        {
-            for (int k = tid; k < 64 * 17; k += 256) {
-                const int rr = k / 17, f = k % 17;
-                // feature slots: 0 degree, 3..18 histogram
-                const int slot = f == 16 ? 0 : 3 + f;
-                const int i = bi * kTile + rr, j = bj * kTile + rr;
-                if (i < d.n && hrow[rr][f]) atomicAdd(&w.rowstat[((int64_t)b * w.max_n + i) * 20 + slot], hrow[rr][f]);
-                if (!diag && j < d.n && hcol[rr][f]) atomicAdd(&w.rowstat[((int64_t)b * w.max_n + j) * 20 + slot], hcol[rr][f]);
+            for (int g = 0; g < 2; ++g) {
+                uint32_t W = 0;
+                const int top = min(32, cnt - 32 * g) - 1;
+                float4 na = cols[wv][max(32 * g + top, 0)][0], nq = cols[wv][max(32 * g + top, 0)][1];
+#pragma unroll 2
+                for (int c = top; c >= 0; --c) {
+                    const float4 a = na, r = nq;
+                    na = cols[wv][32 * g + max(c - 1, 0)][0];
+                    nq = cols[wv][32 * g + max(c - 1, 0)][1];
+                    const float ax = a.x - x.x, ay = a.y - x.y, az = a.z - x.z;
+                    const float bx = r.x - y.x, by = r.y - y.y, bz = r.z - y.z;
+                    float s1 = ax * ax, s2 = bx * bx;
+                    s1 = __builtin_fmaf(ay, ay, s1);
+                    s2 = __builtin_fmaf(by, by, s2);
+                    s1 = __builtin_fmaf(az, az, s1);
+                    s2 = __builtin_fmaf(bz, bz, s2);
+                    const float la = __builtin_amdgcn_sqrtf(s1), lb = __builtin_amdgcn_sqrtf(s2);
+                    float dl = __builtin_fabsf(la - lb);
+                    const float t = dl * inv_q;
+                    const float kn = __builtin_amdgcn_fmed3f(__builtin_rintf(t), 1.0f, 15.0f);
+                    int bin = (int)__builtin_fminf(t, 15.0f);
+                    // not clearly outside the band: also a NaN (a non-finite point; bin 0, no edge)
+                    const bool near = !(__builtin_fabsf(__builtin_fmaf(-kn, q, dl)) > __builtin_fmaf(la, 0x1p-18f, band0));
+                    if (__any(near)) {
+                        if (near) {
+                            dl = __builtin_fabsf(length32(ax, ay, az) - length32(bx, by, bz));
+                            bin = 0;
+#pragma unroll
+                            for (int k = 1; k < 16; ++k) bin += dl >= (float)k * q;
+                        }
+                    }
+                    W = (W << 1) | (dl <= tau ? 1u : 0u);
+                    __hip_atomic_fetch_add(h + 64 * bin, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+                const int k = i - j0 - 32 * g;   // a match with itself has no entry
+                if (k >= 0 && k < 32) W &= ~(1u << k);
+                word[g] = i < n ? W : 0u;
+                degree += __builtin_popcount(word[g]);
             }
+            *reinterpret_cast<uint2 *>(Cb + (uint32_t)(blk >> 1) * kbs + 8 * (blk & 1)) = make_uint2(word[0], word[1]);
         }
+        atomicAdd(&deg[lane], degree);
+        __syncthreads();
+        // slots: 0 degree, 1 and 2 the SC2 sum and maximum (added by the next kernel), 3 .. 18 the histogram (bin 0
+        // without the match itself)
+        int32_t *rs = w.rowstat + ((int64_t)b * w.max_n + i0) * 20;
+        for (int k = tid; k < 64 * 20 && i0 + k / 20 < n; k += 64 * kFeatWaves) {
+            const int r = k / 20, f = k % 20;
+            rs[k] = f == 0 ? deg[r] : f < 3 || f == 19 ? 0 : hist[f - 3][r] - (f == 3);
+        }
+        __syncthreads();   // hist and deg are the next item's
     }
 }
 
@@ -1279,12 +1226,6 @@ hipError_t launch_plan(const Work &w, const int32_t *offsets, int32_t n_single, 
     return hipGetLastError();
 }
 
-hipError_t launch_prep_learned(const Work &w, int grid, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_prep_learned, dim3(grid), dim3(256), 0, s, w);
-    return hipGetLastError();
-}
-
 // Rows per work item (one wave) of the compatibility kernel, for a list of `tiles` tiles: long items
 // amortise the item's loads and transposes, short ones spread a short list over the CUs.
 // Measured at 8 / 16 / 32 / 64 / 128 rows (us): N = 300 6.1 / 6.8 / 9.4, N = 1000 6.0 / 7.3 / 9.8,
@@ -1299,11 +1240,16 @@ int compat_rows(int64_t tiles, int num_cus)
 // tiles: 128 x 128 tiles of the list; cap: workgroups to launch at most.
 hipError_t launch_compat(const Work &w, int64_t tiles, int cap, hipStream_t s)
 {
-    const bool features = w.learned && w.feat_all;   // a workgroup per 64 x 64 quadrant there
-    const int64_t wgs = features ? 4 * tiles : (tiles * (kCompatTile / w.compat_rows) + 3) / 4;
-    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(wgs, cap));
-    if (features) hipLaunchKernelGGL(k_compat_features, dim3(grid), dim3(256), 0, s, w);
-    else hipLaunchKernelGGL(k_compat, dim3(grid), dim3(256), 0, s, w);
+    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((tiles * (kCompatTile / w.compat_rows) + 3) / 4, cap));
+    hipLaunchKernelGGL(k_compat, dim3(grid), dim3(256), 0, s, w);
+    return hipGetLastError();
+}
+
+// items: kPrepRows-row items of the list; cap: workgroups to launch at most.
+hipError_t launch_compat_features(const Work &w, int64_t items, int cap, hipStream_t s)
+{
+    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(items * (kPrepRows / 64), cap));
+    hipLaunchKernelGGL(k_compat_features, dim3(grid), dim3(64 * kFeatWaves), 0, s, w);
     return hipGetLastError();
 }
 

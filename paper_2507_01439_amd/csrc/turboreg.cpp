@@ -317,14 +317,15 @@ tr_status enqueue(tr_handle *h, const Work &w_in, const int32_t *offsets, int32_
         w.hyp_prof = h->hyp_prof;
         w.prof_acc = h->prof_acc;
     }
-    if (!w.n1 || (w.learned && w.feat_all)) mark(TR_STAGE_PLAN);
+    if (!w.n1) mark(TR_STAGE_PLAN);
     if (!w.n1) chk(launch_plan(w, offsets, n_single, B, max_n, h->pairs, h->state, h->plan, h->pre, s));
-    if (w.learned && w.feat_all)
-        chk(launch_prep_learned(w, grid_cap(h, (int64_t)B * ((max_n + kPrepRows - 1) / kPrepRows), 8), s));
     mark(TR_STAGE_COMPAT);
     const int64_t tiles = B * stage_items(kCompat, max_n, 0);
     w.compat_rows = compat_rows(tiles, h->num_cus);
-    chk(launch_compat(w, tiles, h->num_cus * cfg.compat_per_cu, s));
+    if (w.learned && w.feat_all)
+        chk(launch_compat_features(w, (int64_t)B * ((max_n + kPrepRows - 1) / kPrepRows), h->num_cus * 4, s));
+    else
+        chk(launch_compat(w, tiles, h->num_cus * cfg.compat_per_cu, s));
     mark(TR_STAGE_SC2);
     {
         // the kernel splits its items into 8 ranges, one per XCD (workgroup g runs on XCD g mod 8), of
