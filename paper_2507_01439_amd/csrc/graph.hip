@@ -511,8 +511,8 @@ __global__ void __launch_bounds__(256) k_compat(Work w)
 // broadcast from LDS, so each row's counts stay with its lane (an LDS word per bin and lane, which its own
 // lane alone updates in a wave: no conflicts and no atomics in memory) and its bits of C shift into words
 // in place. Every pair is evaluated from both sides (twice the arithmetic of the triangle), which cost less
-// than adding the columns' counts across lanes: 64 pairs of 1000 to 5000 matches 598 us (with the clearing launch it needs no more), 1549 for
-// 64 x 64 tiles with LDS histograms of rows and columns added in memory and correctly rounded roots throughout.
+// than adding the columns' counts across lanes: 598 us for 64 pairs of 1000 to 5000 matches; 64 x 64 tiles
+// with LDS histograms of rows and columns, added in memory, and correctly rounded roots throughout took 1549.
 //
 // Bins: t = delta / q (q = tau / 4) with the hardware square roots; a pair whose delta lies within
 // 2^-19 (|x| + |y|) + 2e-6 + 2^-17 q of the nearest bin edge (tau is edge 4; |y| <= |x| + 4 tau there) is
