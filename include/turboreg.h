@@ -170,7 +170,8 @@ typedef struct {
     int32_t sc2_super;      /* SC2 tile walk: side of the super-tiles (in 256 x 256
                                output tiles) whose tiles run close together, 1..16  */
     int32_t compat_per_cu;  /* compatibility work items launched per CU, 1..16     */
-    int32_t hyp_ppw;        /* pivots per hypothesis work item: 4, 8, 12 or 16     */
+    int32_t hyp_ppw;        /* pivots per hypothesis work item: 4, 8, 12 or 16 (at
+                               most: fewer where that would leave CUs idle)        */
     int32_t hyp_per_cu;     /* hypothesis workgroups launched per CU, 1..16        */
     int32_t sc2_sparse_cap; /* SC2 output tiles (256 x 256) with at most this many
                                edges count common neighbours per edge from bit rows

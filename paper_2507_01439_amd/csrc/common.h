@@ -19,7 +19,7 @@ constexpr int kScorePts = 256;    // points per scoring work item (staged in LDS
 // Counters that many workgroups update with device-scope atomics are spread out: same-address
 // device atomics are served one after another, so one shared counter serialises the stage.
 constexpr int kCollectRegions = 8; // pivot collection: one pool region and counter per XCD
-constexpr int kHypGroup = 16;     // clique-search items per first-level ticket
+constexpr int kHypGroup = 32;     // clique-search items per first-level ticket
 constexpr int kTickLine = 32;     // int32 per counter: one counter per 128-byte line
 constexpr int kTickHyp0 = kCollectRegions;      // first clique-search group ticket
 constexpr int kFusedPool = 512;   // learned pools up to this size are reordered inside the hypothesis kernel
@@ -99,7 +99,7 @@ struct Work {
                               // counters, then one ticket per group of kHypGroup clique-search items
     int32_t tick_stride;
     uint64_t *hyp_rec;        // max_batch x rec_stride: per clique-search item, its best key and valid count
-    int32_t rec_stride;       // 2 x the most clique-search items of a pair (k1_cap / 4, rounded up)
+    int32_t rec_stride;       // 2 x the most clique-search items of a pair (k1_cap)
     int32_t pool_cap;
     int32_t *pivots_plain;    // max_batch x pool_cap x 3
     int32_t *pivots;          // pivots the clique search uses: max_batch x piv_stride x 3
@@ -332,7 +332,7 @@ hipError_t launch_compat(const Work &w, int64_t tiles, int cap, hipStream_t s);
 hipError_t launch_compat_features(const Work &w, int64_t items, int cap, hipStream_t s);
 hipError_t launch_sc2(const Work &w, int64_t items, int num_cus, hipStream_t s);
 hipError_t launch_pivots(const Work &w, int B, int grid_rows, hipStream_t s);
-hipError_t launch_hyp(const Work &w, int B, int ppw, int grid, hipStream_t s);
+hipError_t launch_hyp(const Work &w, int B, int ppw, int grid, int num_cus, hipStream_t s);
 hipError_t launch_fit_triplets(const float *src, const float *dst, int n, const int32_t *tri, int T, float *poses,
                                int32_t *ok, int grid, hipStream_t s);
 hipError_t launch_score_poses(const float *src, const float *dst, int n, const float *poses, int P, float theta,

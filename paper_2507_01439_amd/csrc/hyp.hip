@@ -226,21 +226,43 @@ __device__ __forceinline__ uint32_t clique_key(uint32_t T, uint32_t z)
     return (T << 15) + (32767u - z);
 }
 
+// One DPP move of v (lanes that receive nothing read 0).
+template <int CTRL, int RMASK>
+__device__ __forceinline__ uint32_t dpp_u(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, RMASK, 0xf, false);
+}
+
+// Maximum over the wave, the same on every lane (DPP steps of a few cycles each; through LDS shuffles each of
+// the six steps waits some hundred, and a pivot takes K2 of these one after another).
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, o, 64));
-    return v;
+    v = max(v, dpp_u<0x111, 0xf>(v));   // row_shr:1
+    v = max(v, dpp_u<0x112, 0xf>(v));   // row_shr:2
+    v = max(v, dpp_u<0x114, 0xf>(v));   // row_shr:4
+    v = max(v, dpp_u<0x118, 0xf>(v));   // row_shr:8
+    v = max(v, dpp_u<0x142, 0xa>(v));   // row_bcast:15 into rows 1, 3
+    v = max(v, dpp_u<0x143, 0xc>(v));   // row_bcast:31 into rows 2, 3
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+template <int CTRL, int RMASK>
+__device__ __forceinline__ uint64_t max_dpp_u64(uint64_t v)
+{
+    const uint64_t u = ((uint64_t)dpp_u<CTRL, RMASK>((uint32_t)(v >> 32)) << 32) | dpp_u<CTRL, RMASK>((uint32_t)v);
+    return u > v ? u : v;
 }
 
 __device__ __forceinline__ uint64_t wave_max_u64(uint64_t v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const uint64_t u = __shfl_xor(v, o, 64);
-        v = u > v ? u : v;
-    }
-    return v;
+    v = max_dpp_u64<0x111, 0xf>(v);
+    v = max_dpp_u64<0x112, 0xf>(v);
+    v = max_dpp_u64<0x114, 0xf>(v);
+    v = max_dpp_u64<0x118, 0xf>(v);
+    v = max_dpp_u64<0x142, 0xa>(v);
+    v = max_dpp_u64<0x143, 0xc>(v);
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), 63) << 32) |
+           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 63);
 }
 
 template <int KMAX>
@@ -318,11 +340,22 @@ __device__ int clique_search(const Work &w, const PairDesc &d, int b, int p, con
                     }
                 }
             } else if (wij > 0) {
-                for (int z = lane; z < d.n; z += 64) {
-                    if (z == i || z == j) continue;
-                    const int giz = i < z ? G[i * npad + z] : G[(int64_t)z * npad + i];
-                    const int gjz = j < z ? G[(int64_t)j * npad + z] : G[(int64_t)z * npad + j];
-                    if (giz > 0 && gjz > 0) top_insert<KMAX>(top, clique_key((uint32_t)(giz + gjz), (uint32_t)z));
+                // sixteen third vertices per lane in flight: below i or j they are a column of the upper
+                // triangle, a line each (a load at a time took two thirds of the kernel at N = 2749)
+                for (int z0 = lane; z0 < d.n; z0 += 64 * 16) {
+                    int gi[16], gj[16];
+#pragma unroll
+                    for (int u = 0; u < 16; ++u) {
+                        const int z = min(z0 + 64 * u, d.n - 1);
+                        gi[u] = G[i < z ? i * npad + z : (int64_t)z * npad + i];
+                        gj[u] = G[j < z ? (int64_t)j * npad + z : (int64_t)z * npad + j];
+                    }
+#pragma unroll
+                    for (int u = 0; u < 16; ++u) {
+                        const int z = z0 + 64 * u;
+                        const bool ok = z < d.n && z != i && z != j && gi[u] > 0 && gj[u] > 0;
+                        top_insert<KMAX>(top, ok ? clique_key((uint32_t)(gi[u] + gj[u]), (uint32_t)z) : 0u);
+                    }
                 }
             }
         }
@@ -630,6 +663,21 @@ __global__ void __launch_bounds__(64 * NW) k_hyp(Work w, int B, int ppw)
                 o[2] = piv_l[tid][2];
             }
         }
+        // four matches per thread per step; the first step's loads are issued before the wave's last fits, the
+        // next step's before a step's residuals are formed
+        float x[4][3], y[4][3];
+        auto load4 = [&](int k0) {
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const int64_t gi = d.pt_off + max(min(k0 + NT * m, d.n - 1), 0);
+#pragma unroll
+                for (int f = 0; f < 3; ++f) {
+                    x[m][f] = w.src[3 * gi + f];
+                    y[m][f] = w.dst[3 * gi + f];
+                }
+            }
+        };
+        if (wv >= ppw && d.n > 0) load4(tid);   // no pivot: straight to the scoring
         for (int r = 0; r < (ppw + NW - 1) / NW; ++r) {
             const int lp = r * NW + wv, p = g * ppw + lp;
             if (lp >= ppw) break;   // the same on the whole wave
@@ -637,6 +685,7 @@ __global__ void __launch_bounds__(64 * NW) k_hyp(Work w, int B, int ppw)
             const int32_t *pv = w.rank_in_hyp ? &piv_l[lp][0] : w.pivots + ((int64_t)b * w.piv_stride + p) * 3;
             if (p < w.k1) z = clique_search<KMAX>(w, d, b, p, pv, lane, pi, pj);
             if (w.hyp_prof && tid == 0) ts1 = __builtin_amdgcn_s_memrealtime();
+            if (lp + NW >= ppw && d.n > 0) load4(tid);
             if (lane < w.k2) {
                 float pose[12];
                 const bool ok = p < w.k1 && fit_pose(w, d, pi, pj, z, pose);
@@ -658,21 +707,7 @@ __global__ void __launch_bounds__(64 * NW) k_hyp(Work w, int B, int ppw)
             }
             int cu[8] = {0, 0, 0, 0, 0, 0, 0, 0};
             float su[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // error-based scores (METRIC only)
-            // four matches per thread per step; the next step's loads are issued before this
-            // step's residuals are formed
-            float x[4][3], y[4][3];
-            auto load4 = [&](int k0) {
-#pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    const int64_t gi = d.pt_off + min(k0 + NT * m, d.n - 1);
-#pragma unroll
-                    for (int f = 0; f < 3; ++f) {
-                        x[m][f] = w.src[3 * gi + f];
-                        y[m][f] = w.dst[3 * gi + f];
-                    }
-                }
-            };
-            load4(tid);
+            if (h0 > 0) load4(tid);
             for (int k0 = tid; k0 < d.n; k0 += 4 * NT) {
                 float cx[4][3], cy[4][3];
 #pragma unroll
@@ -771,7 +806,7 @@ __global__ void __launch_bounds__(64 * NW) k_hyp(Work w, int B, int ppw)
             const int gsz = min(kHypGroup, ipp - grp * kHypGroup);
             int32_t *gt = w.tick + (int64_t)b * w.tick_stride + (kTickHyp0 + grp) * kTickLine;
             bool l = __hip_atomic_fetch_add(gt, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gsz - 1;
-            if (l)
+            if (l && ngrp > 1)
                 l = __hip_atomic_fetch_add(&w.state[b].done, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) ==
                     ngrp - 1;
             last = l;
@@ -894,11 +929,13 @@ hipError_t setup_hyp_kernels()
     return hipSuccess;
 }
 
-// ppw: pivots per work item, a multiple of 4 up to 16 (the LDS pose slots);
-// grid: workgroups to launch (capped at the number of items).
-hipError_t launch_hyp(const Work &w, int B, int ppw, int grid, hipStream_t s)
+// ppw: pivots per work item, a multiple of 4 up to 16 (the LDS pose slots), less where that leaves CUs idle
+// and an item would still make more than one pass of eight poses over the matches (N = 2749, K1 = 250, K2 = 8:
+// 63 items of 4 pivots 53 us, 250 of one 32); grid: workgroups to launch (capped at the number of items).
+hipError_t launch_hyp(const Work &w, int B, int ppw, int grid, int num_cus, hipStream_t s)
 {
     if (ppw < 4 || ppw > 16 || ppw % 4) return hipErrorInvalidValue;
+    while (ppw > 1 && ppw * w.k2 > 8 && B * ((w.k1 + ppw - 1) / ppw) < num_cus) ppw /= 2;
     const int total = B * ((w.k1 + ppw - 1) / ppw);
     grid = max(1, min(total, grid));
     const bool small = w.k2 <= 2;

@@ -133,7 +133,7 @@ void size_handle(tr_handle *h, int32_t max_n, int32_t max_batch, int32_t max_k1,
     h->k1_cap = max_k1;
     h->h_cap = max_k1 * max_k2;
     h->nblk_stride = (max_n + kRowsPerItem - 1) / kRowsPerItem;
-    const int items = (max_k1 + 3) / 4;   // clique-search work items of a pair (at least 4 pivots each)
+    const int items = max_k1;   // most clique-search work items of a pair (at least one pivot each)
     h->rec_stride = 2 * items;
     h->tick_stride = (kTickHyp0 + (items + kHypGroup - 1) / kHypGroup) * kTickLine;
     h->pre_stride = max_batch + 1;
@@ -343,7 +343,7 @@ tr_status enqueue(tr_handle *h, const Work &w_in, const int32_t *offsets, int32_
     }
     mark(TR_STAGE_CLIQUES);
     // cliques, their poses, their inlier counts and (last workgroup per pair) the selection
-    chk(launch_hyp(w, B, cfg.hyp_ppw, h->num_cus * cfg.hyp_per_cu, s));
+    chk(launch_hyp(w, B, cfg.hyp_ppw, h->num_cus * cfg.hyp_per_cu, h->num_cus, s));
     mark(TR_NUM_STAGES);
     if (e != hipSuccess) {
         std::fprintf(stderr, "turboreg: launch failed: %s\n", hipGetErrorString(e));
