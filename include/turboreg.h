@@ -173,10 +173,11 @@ typedef struct {
     int32_t hyp_ppw;        /* pivots per hypothesis work item: 4, 8, 12 or 16 (at
                                most: fewer where that would leave CUs idle)        */
     int32_t hyp_per_cu;     /* hypothesis workgroups launched per CU, 1..16        */
-    int32_t sc2_sparse_cap; /* SC2 output tiles (256 x 256) with at most this many
-                               edges count common neighbours per edge from bit rows
-                               instead of the dense product; 0 = every tile takes
-                               the product. 0..TR_SC2_SPARSE_CAP_MAX             */
+    int32_t sc2_sparse_cap; /* SC2 output tiles with at most this many edges per
+                               256 x 256 entries count common neighbours per edge
+                               from bit rows instead of the dense product; 0 = the
+                               library's rule (tiles of few edges, in calls of pairs
+                               beyond 8192 matches). 0..TR_SC2_SPARSE_CAP_MAX    */
 } tr_tuning;
 
 /* Configuration of the group of (max_n, B). TR_ERR_INVALID_ARG for max_n < 3, B < 1. */

@@ -26,7 +26,7 @@ constexpr int kFusedPool = 512;   // learned pools up to this size are reordered
 
 // Work-list stages whose per-pair item counts depend on N_b; each has a
 // prefix array of B+1 entries in Work::pre, over the pairs in cost order.
-enum Stage { kPrep = 0, kCompat, kSc2, kRowBlk, kScore, kNumPrefix };
+enum Stage { kPrep = 0, kCompat, kSc2, kSp, kRowBlk, kScore, kNumPrefix };
 // Rows of Work::pre after the stage prefixes: the cost order (slot -> pair), its inverse.
 constexpr int kOrderRow = kNumPrefix, kSlotRow = kNumPrefix + 1, kPreRows = kNumPrefix + 2;
 
@@ -76,8 +76,10 @@ struct Work {
     int32_t H;                // k1 * k2 hypotheses per pair
     int32_t graph;
     int32_t sc2_super;        // SC2 tile walk: super-tile side in output tiles (launch configuration)
-    int32_t sc2_sparse_cap;   // SC2 tiles with at most this many edges take the bit-count path; 0: none
-                              // does (launch configuration)
+    int32_t sp_tile;          // tile edge of the SC2 bit-count kernel
+    int32_t sp_limit;         // most edges of a tile it takes
+    int32_t *sp_list;         // the tiles it left to the dense kernel: their number, its next tile, its list
+                              // items; null where it is not launched
     float tau, theta;
     uint8_t *C;               // C arena, one bit per entry: per pair npad x npad bits in blocks of 128 columns,
                               // [column / 128][row][16 bytes] (bit c % 8 of byte (c % 128) / 8); offset c_off / 8
@@ -200,7 +202,7 @@ __host__ __device__ inline PairDesc pair_desc_of(int32_t n, int32_t pt_off, int6
     return d;
 }
 
-__host__ __device__ inline int64_t stage_items(int stage, int32_t n, int32_t H)
+__host__ __device__ inline int64_t stage_items(int stage, int32_t n, int32_t H, int32_t sp)
 {
     const int64_t npad = (n + kSc2Tile - 1) / kSc2Tile * kSc2Tile;
     const int64_t nbc = npad / kCompatTile, nbs = npad / kSc2Tile;
@@ -208,6 +210,7 @@ __host__ __device__ inline int64_t stage_items(int stage, int32_t n, int32_t H)
     case kPrep: return (n + kPrepRows - 1) / kPrepRows;
     case kCompat: return nbc * (nbc + 1) / 2;
     case kSc2: return nbs * (nbs + 1) / 2;
+    case kSp: { const int64_t nb = (n + sp - 1) / sp; return nb * (nb + 1) / 2; }   // bit-count tiles of edge sp
     case kRowBlk: return (n + kRowsPerItem - 1) / kRowsPerItem;
     default: return (int64_t)((H + kScoreHyp - 1) / kScoreHyp) * ((n + kScorePts - 1) / kScorePts);
     }
@@ -220,7 +223,7 @@ __host__ __device__ inline int64_t stage_items(int stage, int32_t n, int32_t H)
 // derives everything from n1; a batch reads the device plan.
 __device__ __forceinline__ int stage_total(const Work &w, int stage)
 {
-    return w.n1 ? (int)stage_items(stage, w.n1, w.H) : w.plan->total[stage];
+    return w.n1 ? (int)stage_items(stage, w.n1, w.H, w.sp_tile) : w.plan->total[stage];
 }
 
 // The pair in slot k of the cost order (kernels with one workgroup, or a fixed number, per
@@ -280,7 +283,7 @@ __device__ __forceinline__ int stage_first(const Work &w, int stage, int b)
 
 __device__ __forceinline__ int stage_count(const Work &w, int stage, int b)
 {
-    if (w.n1) return (int)stage_items(stage, w.n1, w.H);
+    if (w.n1) return (int)stage_items(stage, w.n1, w.H, w.sp_tile);
     const int k = w.pre[kSlotRow * w.pre_stride + b];
     return w.pre[stage * w.pre_stride + k + 1] - w.pre[stage * w.pre_stride + k];
 }
@@ -330,6 +333,8 @@ hipError_t launch_plan(const Work &w, const int32_t *offsets, int32_t n_single, 
 int compat_rows(int64_t tiles, int num_cus);
 hipError_t launch_compat(const Work &w, int64_t tiles, int cap, hipStream_t s);
 hipError_t launch_compat_features(const Work &w, int64_t items, int cap, hipStream_t s);
+int sparse_tile(int64_t B, int32_t n, int num_cus);
+hipError_t launch_sc2_sparse(const Work &w, int64_t tiles, int num_cus, hipStream_t s);
 hipError_t launch_sc2(const Work &w, int64_t items, int num_cus, hipStream_t s);
 hipError_t launch_pivots(const Work &w, int B, int grid_rows, hipStream_t s);
 hipError_t launch_hyp(const Work &w, int B, int ppw, int grid, int num_cus, hipStream_t s);

@@ -5,6 +5,7 @@
 
 #include "common.h"
 
+
 namespace tr {
 namespace {
 
@@ -35,31 +36,21 @@ __device__ __forceinline__ void tri_decode(int t, int nb, int &bi, int &bj)
 // launch parameter (the autotuner's); the order does not change any result.
 __device__ __forceinline__ void super_decode(int t, int nb, int sup, int &bi, int &bj)
 {
-    const int ns = (nb + sup - 1) / sup;
-    for (int I = 0; I < ns; ++I) {
-        const int r0 = I * sup, r1 = min(nb, r0 + sup);
-        for (int J = I; J < ns; ++J) {
-            const int c0 = J * sup, c1 = min(nb, c0 + sup);
-            int cnt;
-            if (I == J) { const int s = r1 - r0; cnt = s * (s + 1) / 2; }
-            else cnt = (r1 - r0) * (c1 - c0);
-            if (t < cnt) {
-                if (I == J) {
-                    // triangle of side s: row r holds s - r tiles
-                    int r = 0, s = r1 - r0;
-                    while (t >= s - r) { t -= s - r; ++r; }
-                    bi = r0 + r;
-                    bj = bi + t;
-                } else {
-                    bi = r0 + t / (c1 - c0);
-                    bj = c0 + t % (c1 - c0);
-                }
-                return;
-            }
-            t -= cnt;
-        }
+    // a super-row holds whole tile rows, so the tiles before it are those before its first row
+    tri_decode(t, nb, bi, bj);
+    const int I = bi / sup, r0 = I * sup, s = min(nb, r0 + sup) - r0;
+    t -= r0 * (2 * nb - r0 + 1) / 2;
+    if (t < s * (s + 1) / 2) {   // the diagonal super-tile, a triangle of side s
+        tri_decode(t, s, bi, bj);
+        bi += r0;
+        bj += r0;
+        return;
     }
-    bi = bj = 0;   // not reached for t < nb (nb + 1) / 2
+    t -= s * (s + 1) / 2;
+    const int J = t / (s * sup), c0 = r0 + sup * (J + 1), c = min(nb, c0 + sup) - c0;   // only the last is narrower
+    t -= J * s * sup;
+    bi = r0 + t / c;
+    bj = c0 + t % c;
 }
 
 // ---------------------------------------------------------------- planning
@@ -128,7 +119,7 @@ __device__ __forceinline__ int snake_slot(int p, int B)
 // the work-item counts of every stage and their prefix sums over that order; the XCD ranges of
 // the SC2 list, equal in modelled cost.
 __global__ void __launch_bounds__(1024) k_plan(const int32_t *offsets, int32_t n_single, int32_t B,
-                                               int32_t max_n, int32_t pool, int32_t H,
+                                               int32_t max_n, int32_t pool, int32_t H, int32_t sp,
                                                PairDesc *pairs, PairState *state, Plan *plan,
                                                int32_t *pre, int32_t pre_stride)
 {
@@ -166,7 +157,7 @@ __global__ void __launch_bounds__(1024) k_plan(const int32_t *offsets, int32_t n
         int32_t n, pt;
         const bool ok = size_of(b, n, pt);
         const int32_t npad = ok ? (n + kSc2Tile - 1) / kSc2Tile * kSc2Tile : 0;
-        int64_t v[2] = {(int64_t)npad * npad, ok ? stage_items(kSc2, n, H) * sc2_unit(npad) : 0}, excl[2], tot[2];
+        int64_t v[2] = {(int64_t)npad * npad, ok ? stage_items(kSc2, n, H, sp) * sc2_unit(npad) : 0}, excl[2], tot[2];
         block_scan_multi<2>(v, excl, tot, lds1);
         if (b < B) {
             PairDesc d = pair_desc_of(n, pt, excl[0] + acarry, pool);
@@ -251,7 +242,7 @@ __global__ void __launch_bounds__(1024) k_plan(const int32_t *offsets, int32_t n
         const int32_t n = valid_n(b);
         const bool ok = n > 0;
         int64_t cnt[NV], excl[NV], tot[NV];
-        for (int s = 0; s < kNumPrefix; ++s) cnt[s] = ok ? stage_items(s, n, H) : 0;
+        for (int s = 0; s < kNumPrefix; ++s) cnt[s] = ok ? stage_items(s, n, H, sp) : 0;
         cnt[kScore] = ok ? cnt[kScore] : (b < B);   // an invalid pair's one (empty) scoring item writes its record
         const int32_t npad = ok ? (n + kSc2Tile - 1) / kSc2Tile * kSc2Tile : 0;
         cnt[kNumPrefix] = ok ? cnt[kSc2] * sc2_unit(npad) : 0;
@@ -358,6 +349,7 @@ __global__ void __launch_bounds__(256) k_compat(Work w)
 {
     __shared__ float4 rows[4][32][2];
     __shared__ SlotCache slots;
+    if (w.sp_list && blockIdx.x == 0 && threadIdx.x < 2) w.sp_list[threadIdx.x] = 0;   // counted up by k_sc2_sparse
     const bool cached = slot_cache_fill(w, kCompat, slots);
     __syncthreads();
     const int ROWS = w.compat_rows, R = min(ROWS, 32), per = kCompatTile / ROWS, total = stage_total(w, kCompat) * per;
@@ -524,6 +516,7 @@ __global__ void __launch_bounds__(64 * kFeatWaves) k_compat_features(Work w)
 {
     __shared__ float4 cols[kFeatWaves][64][2];
     __shared__ int32_t hist[16][64], deg[64];
+    if (w.sp_list && blockIdx.x == 0 && threadIdx.x < 2) w.sp_list[threadIdx.x] = 0;   // counted up by k_sc2_sparse
     const int total = (kPrepRows / 64) * stage_total(w, kPrep);
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const float tau = w.tau, q = tau * 0.25f, inv_q = 1.0f / q;
@@ -640,33 +633,7 @@ constexpr float kAccBias = 8388608.0f;         // 2^23: a count v < 2^16 is then
 enum Sc2Mode { kSc2Plain = 0, kSc2Learned = 1, kSc2Features = 2 };
 constexpr int kSc2PerCu = 3;                   // workgroups resident per CU (registers: 168 per lane)
 
-// Bit-count path (tiles with few edges): Eq. 2 is needed only where C_ij = 1, so a 256 x 256 tile
-// holding at most kSddmmCap edges counts popcount(row_i AND row_j) for each of its edges instead of
-// forming the dense product (the threshold is a launch parameter up to kSddmmCap; 0 turns the path
-// off). Rows arrive in chunks of kChunkKb 128-column blocks, kChunkBufs - 1 chunks in flight; each
-// thread keeps its edges and their counts in registers. LDS layout: the chunk buffers (I rows then J
-// rows, [block][row][16 bytes] each); the edge list lies in the last buffer, which receives no chunk
-// before every thread has its edges; then the tile T over all of them, and the histogram behind it.
-constexpr int kTileBytes = kSc2Tile * kSc2Tile * 2;   // the finished tile as uint16 (128 KiB)
-constexpr int kSddmmCap = 8192;                       // 32 edges per thread
-constexpr int kEdgesPerThread = kSddmmCap / 256;
-static_assert(kSddmmCap == TR_SC2_SPARSE_CAP_MAX, "the launch parameter's range is the path's capacity");
-constexpr int kChunkKb = 4;                           // 512 columns of C per chunk
-constexpr int kChunkSide = kChunkKb * kSc2Tile * 16;  // 16 KiB: one side's 256 rows of a chunk
-constexpr int kChunkBytes = 2 * kChunkSide;
-constexpr int kChunkBufs = 4;
-constexpr int kEdgeOff = (kChunkBufs - 1) * kChunkBytes;   // edge list: uint16 (i_local << 8 | j_local)
-constexpr int kScanOff = kEdgeOff + 2 * kSddmmCap;    // four wave totals of the edge-count scan
-static_assert(kChunkBufs * kChunkBytes <= kTileBytes && kScanOff + 64 <= kTileBytes,
-              "the bit-count path stays below the histogram");
-constexpr int kSparseLds = kTileBytes + kHistBytes;   // 160 KiB
-
-// Wait until at most N vector-memory loads of this wave are outstanding, then
-// meet the other waves. The memory clobber keeps LDS reads of the new stage
-// after it; unlike __syncthreads it does not drain the later stages in flight.
-#define SC2_WAIT_BARRIER(N) asm volatile("s_waitcnt vmcnt(" #N ")\n\ts_barrier" ::: "memory")
-
-// Maximum / sum over each half of the wave (lanes 0-31, 32-63), left in lanes 31 and 63: prefix
+// Maximum over each half of the wave (lanes 0-31, 32-63), left in lanes 31 and 63: prefix
 // steps inside each 16-lane DPP row, then the last lane of rows 0 and 2 joins rows 1 and 3.
 // Inputs are >= 0, so lanes that receive no value (they read 0) do not change a maximum.
 __device__ __forceinline__ int half_max(int v)
@@ -679,21 +646,11 @@ __device__ __forceinline__ int half_max(int v)
     return v;
 }
 
-__device__ __forceinline__ int half_sum(int v)
-{
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
-    return v;
-}
-
 // Add the workgroup's LDS histogram of weights 1 .. top into the pair's global copy and clear it.
-// Called by all 256 threads after a barrier.
+// Called by all threads after a barrier.
 __device__ __forceinline__ void hist_flush(int32_t *hist, int32_t *gh, int top)
 {
-    for (int k = threadIdx.x; k < top; k += 256) {
+    for (int k = threadIdx.x; k < top; k += blockDim.x) {
         const int c = hist[k];
         if (c) {
             atomicAdd(&gh[k + 1], c);
@@ -965,254 +922,338 @@ __global__ void __launch_bounds__(256, MODE == kSc2Plain ? kSc2PerCu : 2) k_sc2(
     int32_t *hist = reinterpret_cast<int32_t *>(smem), *tmax = hist + kHistWords - 2;   // zero outside the epilogue
     uint16_t *T = reinterpret_cast<uint16_t *>(smem + (MODE == kSc2Features ? 0 : kHistBytes));
     int start, end;
-    sc2_range(w, start, end);
-    const int nx = (gridDim.x - (blockIdx.x & 7) + 7) >> 3;
+    const int nx = (gridDim.x - (blockIdx.x & 7) + 7) >> 3, m = w.sp_tile / kOut;
+    if (w.sp_list) {   // the tiles that the bit-count kernel left, dealt to the XCDs
+        start = 0;
+        end = (w.sp_list[0] - (int)(blockIdx.x & 7) + 7) / 8 * m * m;
+    } else {
+        sc2_range(w, start, end);
+        start *= 4;
+        end *= 4;
+    }
     if (MODE != kSc2Features)
         for (int k = threadIdx.x; k < kHistWords / 4; k += 256) reinterpret_cast<int4 *>(hist)[k] = make_int4(0, 0, 0, 0);
     __syncthreads();
     int par = 0;
-    for (int it = 4 * start + (blockIdx.x >> 3); it < 4 * end; it += nx) {
-        int local;
-        const int b = stage_pair(w, kSc2, it >> 2, local);
+    for (int it = start + (blockIdx.x >> 3); it < end; it += nx) {
+        int local, b, bi, bj;
+        if (w.sp_list) {
+            const int q = it % (m * m);
+            b = stage_pair(w, kSp, w.sp_list[2 + it / (m * m) * 8 + (blockIdx.x & 7)], local);
+            tri_decode(local, (pair_desc(w, b).n + w.sp_tile - 1) / w.sp_tile, bi, bj);
+            bi = __builtin_amdgcn_readfirstlane(m * bi + q / m);
+            bj = __builtin_amdgcn_readfirstlane(m * bj + q % m);
+        } else {
+            b = stage_pair(w, kSc2, it >> 2, local);
+            super_decode(local, pair_desc(w, b).npad / kSc2Tile, w.sc2_super, bi, bj);
+            bi = __builtin_amdgcn_readfirstlane(2 * bi + ((it >> 1) & 1));
+            bj = __builtin_amdgcn_readfirstlane(2 * bj + (it & 1));
+        }
         const PairDesc d = pair_desc(w, b);
-        int bi, bj;
-        super_decode(local, d.npad / kSc2Tile, w.sc2_super, bi, bj);
-        bi = __builtin_amdgcn_readfirstlane(2 * bi + ((it >> 1) & 1));
-        bj = __builtin_amdgcn_readfirstlane(2 * bj + (it & 1));
         if (bi > bj || bj * kOut >= d.n) continue;   // the same for the whole workgroup
-        sc2_dense_tile<MODE>(w, d, b, bi, bj, (4 * local + (it & 3)) % kHistGroups, hist, &tmax[par], T);
+        sc2_dense_tile<MODE>(w, d, b, bi, bj, it % kHistGroups, hist, &tmax[par], T);
         if (MODE != kSc2Features && threadIdx.x == 0) tmax[par ^ 1] = 0;   // read before this tile's barrier, written after the next
         par ^= 1;
         __syncthreads();   // the histogram is clear, T is the next item's
     }
 }
 
-// The same list with the bit-count path for tiles of at most w.sc2_sparse_cap edges; the others take
-// the dense product, quadrant by quadrant.
+// ---- the same weights by counting bits, for tiles with few edges
+//
+// Eq. 2 is needed only where C_ij = 1, so an S x S tile (S = 256 .. 1024) with few edges counts
+// popcount(row_i AND row_j) for each of them. The rows' bits stream through LDS in 128-column blocks, S rows of
+// I and S rows of J, 16 bytes each, one block counted and three in flight. Edges are listed row by row in runs
+// of four of one row; a thread holds up to five runs, packed LDS offsets and counts in registers, and per block
+// and run reads row i's piece once and four rows j. More runs than the threads hold take another pass over the
+// rows. Of sixteen waves one feeds the buffers (its waits count its own loads, so stores never stand before a
+// block), one writes the tile's zeros to G meanwhile, fourteen count; then the weights are stored over the zeros
+// and go to the histogram and the row statistics, which take the buffers' place in LDS. Tiles with too many
+// edges go to a list that k_sc2 works off next.
+//
+// What bounds it: the LDS reads of rows j, 16 lanes at a time at random rows of 16 bank groups, on average three
+// deep (counters: 10.6 cycles an instruction, 4 without conflicts; N = 20000 has 250 of its 330 us per tile in
+// them). Measured at 1.3 % edges: N = 20000 375 us where k_sc2 takes 1230, sixteen such pairs 4.6 ms (18.7 ms with
+// 256 x 256 tiles, edges in 64-byte pieces and a tile staged in LDS for the store). Software-pipelined reads with
+// a barrier per two blocks: 395; all sixteen waves feeding, zeroing and counting: 392; a read of row i per edge
+// where it changes instead of runs: 618 (16 edges a thread); one lane order by bank class: three to ten
+// percent fewer conflicts for as much work before.
+constexpr int kSpThreads = 1024, kSpWaves = kSpThreads / 64;
+constexpr int kSpCount = 14 * 64;                  // threads of the counting waves
+constexpr int kRuns = 5;                           // runs per counting thread: four edges of one row each
+constexpr int kSpCap = kSpCount * kRuns;           // runs of a pass
+constexpr int kSpMax = 1024;                       // largest tile edge
+constexpr int kSpSide = kSpMax * 16;               // one block's rows of I or J
+constexpr int kSpBufs = 4;                         // blocks in LDS: one counted, three in flight
+constexpr int kSpRing = kSpBufs * 2 * kSpSide;     // before and after the counting other data
+constexpr int kSpStat = kHistBytes;                // row maxima; with learned statistics also column maxima, sums
+// Weights up to kSpLow (most, where a tile has few edges) count in copies by lane: on few bins 64 lanes' adds queue.
+constexpr int kSpLow = 255, kSpCopies = 16, kSpPitch = kSpLow + 2;
+constexpr int kSpLowAt = kSpStat + 4 * kSpMax * 4;
+constexpr int kSpZero = kSpLowAt / 4 + kSpCopies * kSpPitch;   // words cleared before the weights are collected
+constexpr int kSpLds = kSpRing + 8 * kSpWaves + 16;
+static_assert(kSpCap * 16 <= kSpRing && 4 * kSpZero <= kSpRing && kSpZero % 4 == 0, "LDS layout of the bit-count kernel");
+
+// Wait until at most n vector-memory operations of this wave are outstanding (n is rounded down).
+__device__ __forceinline__ void wait_vm(int n)
+{
+    if (n >= 56) asm volatile("s_waitcnt vmcnt(56)" ::: "memory");
+    else if (n >= 48) asm volatile("s_waitcnt vmcnt(48)" ::: "memory");
+    else if (n >= 32) asm volatile("s_waitcnt vmcnt(32)" ::: "memory");
+    else if (n >= 16) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+    else if (n >= 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
 template <int MODE>
-__global__ void __launch_bounds__(256, 1) k_sc2_sparse(Work w)
+__global__ void __launch_bounds__(kSpThreads) k_sc2_sparse(Work w)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    int32_t *hist = reinterpret_cast<int32_t *>(smem + kTileBytes), *tmax = hist + kHistWords - 2;   // zero outside the epilogue
-    uint16_t *T = reinterpret_cast<uint16_t *>(smem);
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    int start, end;
-    sc2_range(w, start, end);
-    const int nx = (gridDim.x - (blockIdx.x & 7) + 7) >> 3;
-    for (int k = tid; k < kHistWords / 4; k += 256) reinterpret_cast<int4 *>(hist)[k] = make_int4(0, 0, 0, 0);
-    __syncthreads();
-    int par = 0;
-    for (int item = start + (blockIdx.x >> 3); item < end; item += nx) {
+    typedef __attribute__((address_space(3))) const uint8_t lds8;
+    typedef __attribute__((address_space(3))) const v4u ldsv;
+    int32_t *hist = reinterpret_cast<int32_t *>(smem), *tmax = hist + kHistWords - 2;
+    int32_t *rmax = reinterpret_cast<int32_t *>(smem + kSpStat), *cmax = rmax + kSpMax, *rsum = cmax + kSpMax,
+            *csum = rsum + kSpMax;
+    int32_t *scan = reinterpret_cast<int32_t *>(smem + kSpRing);
+    uint32_t *list = reinterpret_cast<uint32_t *>(smem);
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int S = w.sp_tile, total = stage_total(w, kSp);
+    for (int item = blockIdx.x, next; item < total; item = next) {
         int local;
-        const int b = stage_pair(w, kSc2, item, local);
+        const int b = __builtin_amdgcn_readfirstlane(stage_pair(w, kSp, item, local));
         const PairDesc d = pair_desc(w, b);
+        const int n = __builtin_amdgcn_readfirstlane(d.n), npad = __builtin_amdgcn_readfirstlane(d.npad);
+        local = __builtin_amdgcn_readfirstlane(local);
         int bi, bj;
-        super_decode(local, d.npad / kSc2Tile, w.sc2_super, bi, bj);
-        // ---- the tile's edges: thread t holds row t of the I block over the tile's 256 columns
-        const uint8_t *Cbit = w.C + d.c_off / 8;
-        const int64_t kbs = (int64_t)d.npad * 16;   // bytes of one 128-column block over all rows
+        tri_decode(local, (n + S - 1) / S, bi, bj);
+        bi = __builtin_amdgcn_readfirstlane(bi);
+        bj = __builtin_amdgcn_readfirstlane(bj);
         const bool diag = bi == bj;
-        uint32_t mw[8];
-        {
-            const int64_t ro = ((int64_t)bi * kSc2Tile + tid) * 16;
-            const uint4 m0 = *reinterpret_cast<const uint4 *>(Cbit + (2 * bj) * kbs + ro);
-            const uint4 m1 = *reinterpret_cast<const uint4 *>(Cbit + (2 * bj + 1) * kbs + ro);
-            mw[0] = m0.x; mw[1] = m0.y; mw[2] = m0.z; mw[3] = m0.w;
-            mw[4] = m1.x; mw[5] = m1.y; mw[6] = m1.z; mw[7] = m1.w;
-        }
-        int ecount = 0, eprefix = 0, etotal = 0;
+        const int i0 = bi * S, j0 = bj * S, nkb = npad / 128;
+        const uint8_t *Cb = w.C + uniform64(d.c_off) / 8;
+        const uint32_t kbs = (uint32_t)npad * 16;   // bytes of one 128-column block over all rows
+        // ---- the tile's edges: thread t has row i0 + t over the tile's columns
+        int row = tid;
+        asm volatile("" : "+v"(row));   // what depends on it is not kept over the tiles: registers are short
+        const bool has_row = row < S && i0 + row < npad;
+        auto row_bits = [&](int kb) {   // the row's 128 columns j0 + 128 kb ..; on the diagonal tile i < j only
+            v4u v = {0, 0, 0, 0};
+            if (has_row && 128 * kb < S && j0 + 128 * kb < npad) {
+                v = *reinterpret_cast<const v4u *>(Cb + (uint32_t)(j0 / 128 + kb) * kbs + (uint32_t)(i0 + row) * 16);
+                if (diag) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            if (diag) {   // i < j only: columns above the thread's row
-                const int lo = tid + 1 - 32 * k;
-                mw[k] &= lo <= 0 ? 0xFFFFFFFFu : (lo >= 32 ? 0u : (0xFFFFFFFFu << lo));
+                    for (int e = 0; e < 4; ++e) {
+                        const int k = row - 128 * kb - 32 * e;   // bits above the row's own
+                        v[e] &= k < 0 ? 0xFFFFFFFFu : k >= 31 ? 0u : 0xFFFFFFFEu << k;
+                    }
+                }
             }
-            ecount += __builtin_popcount(mw[k]);
+            return v;
+        };
+        int mine = 0;
+#pragma unroll
+        for (int kb = 0; kb < kSpMax / 128; ++kb) {
+            const v4u v = row_bits(kb);
+            mine += __builtin_popcount(v.x) + __builtin_popcount(v.y) + __builtin_popcount(v.z) + __builtin_popcount(v.w);
         }
-        int32_t *scanL = reinterpret_cast<int32_t *>(smem + kScanOff);
-        eprefix = ecount;   // inclusive scan inside the wave, then the waves before
+        const int runs = (mine + 3) / 4;
+        int incl = runs, sum = mine;   // inclusive scan of the runs inside the wave, then the waves before
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
-            const int y = __shfl_up(eprefix, o, 64);
-            if (lane >= o) eprefix += y;
+            const int y = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += y;
+            sum += __shfl_xor(sum, o, 64);
         }
-        if (lane == 63) scanL[wv] = eprefix;
+        if (lane == 63) {
+            scan[2 * wv] = incl;
+            scan[2 * wv + 1] = sum;
+        }
+        if (tid == 0) scan[2 * kSpWaves] = gridDim.x + atomicAdd(&w.sp_list[1], 1);   // whoever is free takes the next tile
         __syncthreads();
-        etotal = scanL[0] + scanL[1] + scanL[2] + scanL[3];
-        for (int v = 0; v < wv; ++v) eprefix += scanL[v];
-        eprefix -= ecount;   // exclusive
-        if (etotal > w.sc2_sparse_cap) {
-            __syncthreads();   // scanL is read
-            for (int q = 0; q < 4; ++q) {
-                const int ti = __builtin_amdgcn_readfirstlane(2 * bi + (q >> 1)), tj = __builtin_amdgcn_readfirstlane(2 * bj + (q & 1));
-                if (ti > tj || tj * kOut >= d.n) continue;
-                sc2_dense_tile<MODE>(w, d, b, ti, tj, (4 * local + q) % kHistGroups, hist, &tmax[par], T);
-                if (tid == 0) tmax[par ^ 1] = 0;
-                par ^= 1;
-                __syncthreads();
-            }
+        int first = incl - runs, all = 0, edges = 0;
+#pragma unroll
+        for (int v = 0; v < kSpWaves; ++v) {
+            const int c = scan[2 * v];
+            first += v < wv ? c : 0;
+            all += c;
+            edges += scan[2 * v + 1];
+        }
+        next = __builtin_amdgcn_readfirstlane(scan[2 * kSpWaves]);
+        all = __builtin_amdgcn_readfirstlane(all);
+        edges = __builtin_amdgcn_readfirstlane(edges);
+        const bool take = edges <= w.sp_limit;
+        if (!take) {   // the same for the whole workgroup: the dense kernel's
+            if (tid == 0) w.sp_list[2 + atomicAdd(&w.sp_list[0], 1)] = item;
+            __syncthreads();
             continue;
         }
+        uint16_t *Gb = w.G + d.g_off;
         int32_t *gh = w.ghist + ((int64_t)b * kHistGroups + local % kHistGroups) * w.hist_stride;
-        uint16_t *edgeL = reinterpret_cast<uint16_t *>(smem + kEdgeOff);
-        {
-            int pos = eprefix;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                uint32_t x = mw[k];
-                while (x) {
-                    const int c = __builtin_ctz(x);
-                    x &= x - 1;
-                    edgeL[pos] = (uint16_t)((tid << 8) | (32 * k + c));
-                    ++pos;
-                }
-            }
-        }
-        __syncthreads();   // the edge list is complete
-        // thread t counts edges [e0, e1): about etotal / 256 consecutive edges (few rows each),
-        // held in registers with their counts
-        const int q = (etotal + 255) >> 8, e0 = min(etotal, tid * q), e1 = min(etotal, e0 + q), ne = e1 - e0;
-        uint32_t myv[kEdgesPerThread];
-        int myc[kEdgesPerThread];
-#pragma unroll
-        for (int k = 0; k < kEdgesPerThread; ++k) {
-            myv[k] = k < ne ? edgeL[e0 + k] : 0u;
-            myc[k] = 0;
-        }
-        __syncthreads();   // the edge list's buffer may now receive a chunk
-        const int nkb = d.npad / 128, nch = (nkb + kChunkKb - 1) / kChunkKb;
-        // chunk c: blocks kChunkKb c .. of the I rows (and J rows off the diagonal) by direct
-        // global->LDS 16-byte loads; wave v loads rows 64v .. 64v+63 of each block
-        auto issue_chunk = [&](int c) {
-            uint8_t *dst = smem + (c % kChunkBufs) * kChunkBytes + wv * 1024;
-#pragma unroll
-            for (int side = 0; side < 2; ++side) {
-                if (side && diag) break;
-                const int64_t ro = ((int64_t)(side ? bj : bi) * kSc2Tile + wv * 64 + lane) * 16;
-#pragma unroll
-                for (int kb = 0; kb < kChunkKb; ++kb)   // past the last block: a copy of it, not counted
-                    __builtin_amdgcn_global_load_lds((gvoid *)(Cbit + (int64_t)min(c * kChunkKb + kb, nkb - 1) * kbs + ro),
-                                                     (lvoid *)(dst + side * kChunkSide + kb * 4096), 16, 0, 0);
+        // zeros of the tile: rows from, from + step, .. below to (a wave), up to column npad
+        const int zrows = min(S, n - i0), zcols = min(S, npad - j0);
+        auto zeros = [&](int from, int to, int step) {
+            for (int r = from; r < to; r += step) {
+                uint16_t *p = Gb + (int64_t)(i0 + r) * npad + j0;
+                for (int c = 8 * lane; c < zcols; c += 512) *reinterpret_cast<uint4 *>(p + c) = make_uint4(0, 0, 0, 0);
             }
         };
-        const int lpc = (diag ? 1 : 2) * kChunkKb;   // loads per chunk and lane
-        const int nrun = etotal > 0 ? nch : 0;
-        for (int c = 0; c < min(nrun, kChunkBufs - 1); ++c) issue_chunk(c);
-        for (int c = 0; c < nrun; ++c) {
-            // chunk c has landed once at most (chunks issued after it) x lpc loads are outstanding;
-            // the barrier also tells every wave that chunk c - 1's buffer is free
-            const int outstanding = min(kChunkBufs - 2, nrun - 1 - c) * lpc;
-            switch (outstanding) {
-            case 16: SC2_WAIT_BARRIER(16); break;
-            case 8: SC2_WAIT_BARRIER(8); break;
-            case 4: SC2_WAIT_BARRIER(4); break;
-            default: SC2_WAIT_BARRIER(0); break;
-            }
-            if (c + kChunkBufs - 1 < nrun) issue_chunk(c + kChunkBufs - 1);
-            const uint8_t *Ib = smem + (c % kChunkBufs) * kChunkBytes, *Jb = diag ? Ib : Ib + kChunkSide;
-            const int kbn = min(kChunkKb, nkb - c * kChunkKb);
-            int cur = -1;
-            uint4 ri[kChunkKb];
-            constexpr int kU = 2;   // edges whose J rows are read together
-#pragma unroll
-            for (int k0 = 0; k0 < kEdgesPerThread; k0 += kU) {
-                if (k0 >= ne) continue;   // (not break: the loop must unroll, the arrays stay in registers)
-                uint4 rj[kU][kChunkKb];
-#pragma unroll
-                for (int u = 0; u < kU; ++u)
-#pragma unroll
-                    for (int kb = 0; kb < kChunkKb; ++kb)
-                        rj[u][kb] = k0 + u < ne && kb < kbn
-                                        ? *reinterpret_cast<const uint4 *>(Jb + kb * 4096 + (myv[k0 + u] & 255) * 16)
-                                        : make_uint4(0, 0, 0, 0);
-#pragma unroll
-                for (int u = 0; u < kU; ++u) {
-                    const int li = (int)(myv[k0 + u] >> 8);
-                    if (k0 + u < ne && li != cur) {
-                        cur = li;
-#pragma unroll
-                        for (int kb = 0; kb < kChunkKb; ++kb) ri[kb] = *reinterpret_cast<const uint4 *>(Ib + kb * 4096 + li * 16);
-                    }
-                    int sum = 0;
-#pragma unroll
-                    for (int kb = 0; kb < kChunkKb; ++kb)
-                        sum += __builtin_popcount(ri[kb].x & rj[u][kb].x) + __builtin_popcount(ri[kb].y & rj[u][kb].y) +
-                               __builtin_popcount(ri[kb].z & rj[u][kb].z) + __builtin_popcount(ri[kb].w & rj[u][kb].w);
-                    myc[k0 + u] += k0 + u < ne ? sum : 0;
-                }
-            }
-        }
-        // the LDS becomes the tile T (zero, then the counts scattered in; weights below 2^16)
-        __syncthreads();
-        for (int k = tid; k < kTileBytes / 16; k += 256) reinterpret_cast<uint4 *>(smem)[k] = make_uint4(0, 0, 0, 0);
-        __syncthreads();
-        int wmax = 0;
-#pragma unroll
-        for (int k = 0; k < kEdgesPerThread; ++k) {
-            if (k < ne) {
-                const int c = myc[k];
-                T[(myv[k] >> 8) * kSc2Tile + (myv[k] & 255)] = (uint16_t)c;
-                wmax = max(wmax, c);
-                if (MODE != kSc2Features && c > 0) {   // the weight histogram counts nonzero weights
-                    if (c <= kHistLdsBins) lds_add(hist, c - 1);
-                    else atomicAdd(&gh[c], 1);
-                }
-            }
-        }
-        wmax = half_max(wmax);
-        if ((lane & 31) == 31) atomicMax(&tmax[par], wmax);
-        __syncthreads();
-        // thread t: column chunk cc = t % 32 (8 columns) of rows lr = 8k + t / 32, k = 0..31, in four
-        // batches of eight rows; lanes 0-31 of a wave hold one row, lanes 32-63 the next
-        int32_t *rowmax = w.rowmax + (int64_t)b * w.max_n;
-        int32_t *rstat = w.rowstat + (int64_t)b * w.max_n * 20;
-        uint16_t *Gb = w.G + d.g_off;
-        const int cc = tid & 31, j0 = bj * kSc2Tile + cc * 8;
+        for (int base = 0; base < all; base += kSpCap) {
+            const int np = min(kSpCap, all - base);   // runs of this pass
+            {
+                int pos = 4 * (first - base);
+                const int end = pos + 4 * runs;
+                if (pos < 4 * np && end > 0) {
+                    uint32_t e = 0;   // 16 row << 16 | 16 column, bit 31: an edge, not the filling of a run
+                    v4u next = row_bits(0);
 #pragma unroll 1
-        for (int kb = 0; kb < 4; ++kb) {
-            int rmax[8], rsum[8];
+                    for (int kb = 0; kb < S / 128; ++kb) {
+                        const v4u v = next;
+                        next = row_bits(kb + 1);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int lr = (kb * 8 + u) * 8 + (tid >> 5), i = bi * kSc2Tile + lr;
-                const uint4 tv = *reinterpret_cast<const uint4 *>(&T[lr * kSc2Tile + cc * 8]);
-                const uint32_t tw[4] = {tv.x, tv.y, tv.z, tv.w};
-                u16x2 m2 = {0, 0};
-                rsum[u] = 0;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(u16x2, tw[k]));
-                    rsum[u] += (int)((tw[k] & 0xFFFFu) + (tw[k] >> 16));
+                        for (int c = 0; c < 4; ++c) {
+                            uint32_t x = v[c];
+                            while (x) {
+                                e = (uint32_t)row << 20 | (uint32_t)(128 * kb + 32 * c + __builtin_ctz(x)) << 4 | 0x80000000u;
+                                x &= x - 1;
+                                if (pos >= 0 && pos < 4 * np) list[pos] = e;
+                                ++pos;
+                            }
+                        }
+                    }
+                    for (; pos < end; ++pos)
+                        if (pos >= 0 && pos < 4 * np) list[pos] = e & 0x7FFFFFFFu;
                 }
-                rmax[u] = max((int)m2.x, (int)m2.y);
-                *reinterpret_cast<uint4 *>(Gb + (int64_t)i * d.npad + j0) = tv;
             }
+            __syncthreads();
+            // counting thread t holds runs t q .. t q + q - 1 of the pass
+            const int q = (np + kSpCount - 1) / kSpCount, r0 = min(np, tid * q), nr = tid < kSpCount ? min(q, np - r0) : 0;
+            uint32_t ed[4 * kRuns], cnt[4 * kRuns];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                rmax[u] = half_max(rmax[u]);
-                if (MODE != kSc2Plain) rsum[u] = half_sum(rsum[u]);
+            for (int k = 0; k < kRuns; ++k) {
+                const v4u v = k < nr ? *reinterpret_cast<const v4u *>(list + 4 * (r0 + k)) : v4u{0, 0, 0, 0};
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    ed[4 * k + u] = v[u];
+                    cnt[4 * k + u] = 0;
+                }
             }
-            if ((lane & 31) == 31) {
+            __syncthreads();   // the list's room is the buffers'
+            // at block kb's barrier the block has landed (wave 14 waited) and the reads of block kb - 1 are done
+            if (wv == kSpWaves - 2) {
+                // 64-row pieces of I and of J below npad (a multiple of 256), 1 KiB a load
+                const int ends[2] = {min(S, npad - i0) * 16, min(S, npad - j0) * 16}, loads = (ends[0] + ends[1]) / 1024;
+                auto feed = [&](int kb) {
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int i = bi * kSc2Tile + (kb * 8 + u) * 8 + (tid >> 5);
-                    if (rmax[u] > 0) {
-                        if (MODE != kSc2Features) atomicMax(&rowmax[i], rmax[u]);
-                        if (MODE != kSc2Plain) {
-                            atomicAdd(&rstat[i * 20 + 1], rsum[u]);
-                            atomicMax(&rstat[i * 20 + 2], rmax[u]);
+                    for (int h = 0; h < 2; ++h) {
+                        const uint8_t *p = Cb + (uint32_t)kb * kbs + (uint32_t)(h ? j0 : i0) * 16;
+                        uint8_t *buf = smem + (kb % kSpBufs) * (2 * kSpSide) + h * kSpSide;
+#pragma unroll 4
+                        for (int v = 0; v < ends[h]; v += 1024)
+                            __builtin_amdgcn_global_load_lds((gvoid *)(p + v + (uint32_t)lane * 16), (lvoid *)(buf + v), 16, 0, 0);
+                    }
+                };
+                feed(0);
+                feed(1);   // npad is a multiple of 256: at least two blocks
+                if (nkb > 2) feed(2);
+                for (int kb = 0; kb < nkb; ++kb) {
+                    wait_vm(min(2, nkb - 1 - kb) * loads);
+                    asm volatile("s_barrier" ::: "memory");
+                    if (kb + 3 < nkb) feed(kb + 3);
+                }
+            } else if (wv == kSpWaves - 1) {
+                const int zstep = (zrows + nkb - 1) / nkb;
+                for (int kb = 0; kb < nkb; ++kb) {
+                    asm volatile("s_barrier" ::: "memory");
+                    if (base == 0) zeros(kb * zstep, min(zrows, (kb + 1) * zstep), 1);
+                }
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // in L2 before any weight is stored over them
+            } else {
+                for (int kb = 0; kb < nkb; ++kb) {
+                    lds8 *buf = (lds8 *)smem + (kb % kSpBufs) * (2 * kSpSide);
+                    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+                    for (int k = 0; k < kRuns; ++k) {
+                        if (k < q) {   // uniform
+                            const v4u ri = *(ldsv *)(buf + ((ed[4 * k] >> 16) & 0x7FFFu));
+                            v4u rj[4];
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) rj[u] = *(ldsv *)(buf + (ed[4 * k + u] & 0xFFFFu) + kSpSide);
+#pragma unroll
+                            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                                for (int e = 0; e < 4; ++e)
+                                    asm("v_bcnt_u32_b32 %0, %1, %0" : "+v"(cnt[4 * k + u]) : "v"(ri[e] & rj[u][e]));
                         }
                     }
                 }
             }
-        }
-        if (MODE != kSc2Features) hist_flush(hist, gh, min(tmax[par], kHistLdsBins));
-        if (MODE != kSc2Plain) {
             __syncthreads();
-            column_stats<kSc2Tile, kSc2Tile>(T, kSc2Tile, reinterpret_cast<int32_t *>(smem), rstat, bj * kSc2Tile);
+            for (int k = tid; k < kSpZero / 4; k += kSpThreads) reinterpret_cast<int4 *>(smem)[k] = make_int4(0, 0, 0, 0);
+            __syncthreads();
+            int32_t *low = reinterpret_cast<int32_t *>(smem + kSpLowAt);
+            const uint32_t copy = (uint32_t)(lane & (kSpCopies - 1)) * kSpPitch;
+#pragma unroll
+            for (int k = 0; k < kRuns; ++k) {
+                const int i = (int)(ed[4 * k] >> 20) & (kSpMax - 1);
+                int rm = 0, rs = 0;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const uint32_t c = (int32_t)ed[4 * k + u] < 0 ? cnt[4 * k + u] : 0u;
+                    const int j = (int)(ed[4 * k + u] >> 4) & (kSpMax - 1);
+                    if (c > 0) {
+                        Gb[(int64_t)(i0 + i) * npad + j0 + j] = (uint16_t)c;
+                        if (MODE != kSc2Features) {   // the weight histogram counts nonzero weights
+                            if (c <= (uint32_t)kSpLow) lds_add(low, copy + c);
+                            else if (c <= (uint32_t)kHistLdsBins) lds_add(hist, c - 1);
+                            else atomicAdd(&gh[c], 1);
+                        }
+                        if (MODE != kSc2Plain) {
+                            atomicAdd(&csum[j], (int)c);
+                            atomicMax(&cmax[j], (int)c);
+                        }
+                    }
+                    rm = max(rm, (int)c);
+                    rs += (int)c;
+                }
+                if (rm > 0) {
+                    atomicMax(&rmax[i], rm);
+                    if (MODE != kSc2Plain) atomicAdd(&rsum[i], rs);
+                }
+            }
+            __syncthreads();
+            // ---- the pass's row statistics and histogram
+            if (MODE != kSc2Features && tid > 0 && tid <= kSpLow) {
+                int c = 0;
+#pragma unroll
+                for (int v = 0; v < kSpCopies; ++v) c += low[v * kSpPitch + tid];
+                hist[tid - 1] = c;   // no other add reached these bins
+            }
+            if (tid < S) {
+                const int m = rmax[tid];
+                if (m > 0) {
+                    if (MODE != kSc2Features) {
+                        atomicMax(&w.rowmax[(int64_t)b * w.max_n + i0 + tid], m);
+                        atomicMax(tmax, m);
+                    }
+                    if (MODE != kSc2Plain) {
+                        int32_t *rs = w.rowstat + ((int64_t)b * w.max_n + i0 + tid) * 20;
+                        atomicAdd(&rs[1], rsum[tid]);
+                        atomicMax(&rs[2], m);
+                    }
+                }
+                if (MODE != kSc2Plain && cmax[tid] > 0) {
+                    int32_t *rs = w.rowstat + ((int64_t)b * w.max_n + j0 + tid) * 20;
+                    atomicAdd(&rs[1], csum[tid]);
+                    atomicMax(&rs[2], cmax[tid]);
+                }
+            }
+            __syncthreads();
+            if (MODE != kSc2Features) hist_flush(hist, gh, min(*tmax, kHistLdsBins));
+            __syncthreads();   // the LDS is the next pass's
         }
-        if (tid == 0) tmax[par ^ 1] = 0;
-        par ^= 1;
-        __syncthreads();   // T is the next item's chunk buffers
+        if (all == 0) {
+            zeros(wv, zrows, kSpWaves);
+            __syncthreads();   // scan is the next tile's
+        }
     }
 }
 
@@ -1221,7 +1262,7 @@ __global__ void __launch_bounds__(256, 1) k_sc2_sparse(Work w)
 hipError_t launch_plan(const Work &w, const int32_t *offsets, int32_t n_single, int32_t B, int32_t max_n,
                        PairDesc *pairs, PairState *state, Plan *plan, int32_t *pre, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_plan, dim3(1), dim3(1024), 0, s, offsets, n_single, B, max_n, w.pool, w.H, pairs,
+    hipLaunchKernelGGL(k_plan, dim3(1), dim3(1024), 0, s, offsets, n_single, B, max_n, w.pool, w.H, w.sp_tile, pairs,
                        state, plan, pre, w.pre_stride);
     return hipGetLastError();
 }
@@ -1260,19 +1301,40 @@ constexpr int sc2_lds(int mode)
 }
 }  // namespace
 
+// Tile edge of the bit-count kernel for B pairs of up to n matches: larger tiles read each row's bits fewer
+// times, smaller ones spread a short list over the CUs (one workgroup each). The cost of a round of tiles is
+// its edges, plus what a tile costs besides (as much as 2^17 entries).
+int sparse_tile(int64_t B, int32_t n, int num_cus)
+{
+    int best = kSpMax;
+    int64_t cost = INT64_MAX;
+    for (int S = kSpMax; S >= 256; S -= 256) {
+        const int64_t nb = (n + S - 1) / S, rounds = (B * nb * (nb + 1) / 2 + num_cus - 1) / num_cus;
+        const int64_t c = rounds * ((int64_t)S * S + (1 << 17));
+        if (c < cost) {
+            cost = c;
+            best = S;
+        }
+    }
+    return best;
+}
+
+// Tiles of the bit-count kernel, before launch_sc2 takes those it left. tiles: of its list, at most.
+hipError_t launch_sc2_sparse(const Work &w, int64_t tiles, int num_cus, hipStream_t s)
+{
+    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(tiles, num_cus));
+    if (!w.learned) hipLaunchKernelGGL(k_sc2_sparse<kSc2Plain>, dim3(grid), dim3(kSpThreads), kSpLds, s, w);
+    else if (!w.feat_all) hipLaunchKernelGGL(k_sc2_sparse<kSc2Learned>, dim3(grid), dim3(kSpThreads), kSpLds, s, w);
+    else hipLaunchKernelGGL(k_sc2_sparse<kSc2Features>, dim3(grid), dim3(kSpThreads), kSpLds, s, w);
+    return hipGetLastError();
+}
+
 // items: 256 x 256 tiles of the list. The grid is a multiple of 8 with as many workgroups per XCD as
 // an even range would hold work items, up to what its CUs hold.
 hipError_t launch_sc2(const Work &w, int64_t items, int num_cus, hipStream_t s)
 {
     const int mode = !w.learned ? kSc2Plain : w.feat_all ? kSc2Features : kSc2Learned;
     const int cus = std::max(1, num_cus / 8);
-    if (w.sc2_sparse_cap > 0) {
-        const int grid = (int)(8 * std::min<int64_t>((items + 7) / 8, cus));
-        if (mode == kSc2Plain) hipLaunchKernelGGL(k_sc2_sparse<kSc2Plain>, dim3(grid), dim3(256), kSparseLds, s, w);
-        else if (mode == kSc2Learned) hipLaunchKernelGGL(k_sc2_sparse<kSc2Learned>, dim3(grid), dim3(256), kSparseLds, s, w);
-        else hipLaunchKernelGGL(k_sc2_sparse<kSc2Features>, dim3(grid), dim3(256), kSparseLds, s, w);
-        return hipGetLastError();
-    }
     const int grid = (int)(8 * std::min<int64_t>(4 * ((items + 7) / 8), cus * (mode == kSc2Plain ? kSc2PerCu : 2)));
     if (mode == kSc2Plain) hipLaunchKernelGGL(k_sc2<kSc2Plain>, dim3(grid), dim3(256), sc2_lds(kSc2Plain), s, w);
     else if (mode == kSc2Learned) hipLaunchKernelGGL(k_sc2<kSc2Learned>, dim3(grid), dim3(256), sc2_lds(kSc2Learned), s, w);
@@ -1286,7 +1348,7 @@ hipError_t setup_graph_kernels()
                           reinterpret_cast<const void *>(k_sc2_sparse<kSc2Learned>),
                           reinterpret_cast<const void *>(k_sc2_sparse<kSc2Features>),
                           reinterpret_cast<const void *>(k_sc2<kSc2Learned>)};
-    const int lds[4] = {kSparseLds, kSparseLds, kSparseLds, sc2_lds(kSc2Learned)};
+    const int lds[4] = {kSpLds, kSpLds, kSpLds, sc2_lds(kSc2Learned)};
     hipError_t e = hipSuccess;
     for (int k = 0; k < 4 && e == hipSuccess; ++k)
         e = hipFuncSetAttribute(fns[k], hipFuncAttributeMaxDynamicSharedMemorySize, lds[k]);
