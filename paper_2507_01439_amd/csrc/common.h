@@ -341,7 +341,7 @@ hipError_t launch_hyp(const Work &w, int B, int ppw, int grid, int num_cus, hipS
 hipError_t launch_fit_triplets(const float *src, const float *dst, int n, const int32_t *tri, int T, float *poses,
                                int32_t *ok, int grid, hipStream_t s);
 hipError_t launch_score_poses(const float *src, const float *dst, int n, const float *poses, int P, float theta,
-                              int metric, int32_t *in_out, float *score_out, int grid, hipStream_t s);
+                              int metric, int32_t *in_out, float *score_out, int num_cus, hipStream_t s);
 hipError_t setup_hyp_kernels();
 
 // Once per process and device, before any launch (and so outside stream capture):

@@ -818,29 +818,34 @@ __global__ void __launch_bounds__(64 * NW) k_hyp(Work w, int B, int ppw)
 }
 
 // Inlier numbers (Eq. 9) and, for metric 1 / 2, the error-based scores of
-// caller-given poses against one pair's matches: eight poses per workgroup,
+// caller-given poses against one pair's matches: U poses per workgroup,
 // the matches strided over the 256 threads and every sum formed in the same
 // order as in k_hyp, so a pose scores the same bits here as there.
+// Bound by the latency of the matches' loads and by the exact root and quotient of the scores: the next group's
+// loads are in flight meanwhile, and a wave without an inlier skips them. 2000 poses on 5000 matches with scores
+// 24.8 -> 16.9 us, 2500 on 20000 114 -> 62, counts only 52.8 -> 30.5 (from eight poses a workgroup and neither).
+template <int U, bool SCORE>
 __global__ void __launch_bounds__(256) k_score_poses(const float *src, const float *dst, int n, const float *poses,
                                                      int P, float theta, int metric, int32_t *in_out,
                                                      float *score_out)
 {
-    __shared__ int32_t cnt_l[4][8];
-    __shared__ float sum_l[4][8];
+    constexpr int M = 4;   // matches of a thread in flight
+    __shared__ int32_t cnt_l[4][U];
+    __shared__ float sum_l[4][U];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const float th2 = theta * theta;
-    for (int p0 = blockIdx.x * 8; p0 < P; p0 += gridDim.x * 8) {
-        float ps[8][12];
+    for (int p0 = blockIdx.x * U; p0 < P; p0 += gridDim.x * U) {
+        float ps[U][12];
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
+        for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int k = 0; k < 12; ++k) ps[u][k] = poses[(int64_t)min(p0 + u, P - 1) * 12 + k];
-        int cu[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        float su[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        for (int k0 = tid; k0 < n; k0 += 1024) {
-            float x[4][3], y[4][3];
+        int cu[U] = {};
+        float su[U] = {};
+        float x[M][3], y[M][3];
+        auto fetch = [&](int k0) {
 #pragma unroll
-            for (int m = 0; m < 4; ++m) {
+            for (int m = 0; m < M; ++m) {
                 const int64_t gi = min(k0 + 256 * m, n - 1);
 #pragma unroll
                 for (int f = 0; f < 3; ++f) {
@@ -848,15 +853,27 @@ __global__ void __launch_bounds__(256) k_score_poses(const float *src, const flo
                     y[m][f] = dst[3 * gi + f];
                 }
             }
+        };
+        fetch(tid);
+        for (int k0 = tid; k0 - tid < n; k0 += 256 * M) {
+            float cx[M][3], cy[M][3];
 #pragma unroll
-            for (int m = 0; m < 4; ++m) {
+            for (int m = 0; m < M; ++m)
+#pragma unroll
+                for (int f = 0; f < 3; ++f) {
+                    cx[m][f] = x[m][f];
+                    cy[m][f] = y[m][f];
+                }
+            fetch(k0 + 256 * M);   // the next matches' loads pass this group's arithmetic
+#pragma unroll
+            for (int m = 0; m < M; ++m) {
                 const bool in = k0 + 256 * m < n;
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const float r2 = residual2(ps[u], x[m][0], x[m][1], x[m][2], y[m][0], y[m][1], y[m][2]);
+                for (int u = 0; u < U; ++u) {
+                    const float r2 = residual2(ps[u], cx[m][0], cx[m][1], cx[m][2], cy[m][0], cy[m][1], cy[m][2]);
                     const bool hit = in && r2 <= th2;
                     cu[u] += hit;
-                    if (metric) {
+                    if (SCORE && __any(hit)) {   // the root and the quotient cost more than the residual
                         const float c = fmaxf((theta - __builtin_sqrtf(r2)) / theta, 0.0f);
                         su[u] += hit ? (metric == 1 ? c : c * c) : 0.0f;
                     }
@@ -864,7 +881,7 @@ __global__ void __launch_bounds__(256) k_score_poses(const float *src, const flo
             }
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < U; ++u) {
             const int t = wave_total(cu[u]);
             const float f = wave_total_f(su[u]);
             if (lane == 0) {
@@ -873,7 +890,7 @@ __global__ void __launch_bounds__(256) k_score_poses(const float *src, const flo
             }
         }
         __syncthreads();
-        if (tid < 8 && p0 + tid < P) {
+        if (tid < U && p0 + tid < P) {
             in_out[p0 + tid] = cnt_l[0][tid] + cnt_l[1][tid] + cnt_l[2][tid] + cnt_l[3][tid];
             if (metric && score_out)
                 score_out[p0 + tid] = ((sum_l[0][tid] + sum_l[1][tid]) + sum_l[2][tid]) + sum_l[3][tid];
@@ -915,12 +932,21 @@ hipError_t launch_fit_triplets(const float *src, const float *dst, int n, const 
     return hipGetLastError();
 }
 
+// Poses per workgroup: one while the poses are few, so that they spread over the CUs, otherwise as many as share
+// each match's loads with profit: scores are bound by the root and the quotient, counts by the loads. Measured at
+// 1 / 2 / 4 / 8 (us): scores of 50 poses on 20000 matches 13.8 / 25.5 / 41.5 / 70.4, 2000 on 5000 20.0 / 16.9 /
+// 18.5 / 24.2, 2500 on 20000 81 / 62 / 72 / 103; counts of 2500 on 20000 49 / 37 / 30 / 33.
 hipError_t launch_score_poses(const float *src, const float *dst, int n, const float *poses, int P, float theta,
-                              int metric, int32_t *in_out, float *score_out, int grid, hipStream_t s)
+                              int metric, int32_t *in_out, float *score_out, int num_cus, hipStream_t s)
 {
-    grid = max(1, min(grid, (P + 7) / 8));
-    hipLaunchKernelGGL(k_score_poses, dim3(grid), dim3(256), 0, s, src, dst, n, poses, P, theta, metric, in_out,
-                       score_out);
+    auto go = [&](auto kernel, int per) {
+        const int grid = min((P + per - 1) / per, 4 * num_cus);
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, s, src, dst, n, poses, P, theta, metric, in_out, score_out);
+    };
+    if (metric && P <= 2 * num_cus) go(k_score_poses<1, true>, 1);
+    else if (metric) go(k_score_poses<2, true>, 2);
+    else if (P <= 4 * num_cus) go(k_score_poses<1, false>, 1);
+    else go(k_score_poses<4, false>, 4);
     return hipGetLastError();
 }
 

@@ -692,7 +692,7 @@ tr_status tr_score_poses(tr_handle *h, const float *src, const float *dst, int32
     if (P == 0) return TR_OK;
     if (hipSetDevice(h->device) != hipSuccess) return TR_ERR_HIP;
     const hipError_t e = launch_score_poses(src, dst, n, poses_dev, P, theta, metric, in_dev, score_dev,
-                                            h->num_cus * 4, static_cast<hipStream_t>(stream));
+                                            h->num_cus, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? TR_OK : TR_ERR_HIP;
 }
 
