@@ -26,7 +26,7 @@ constexpr int kFusedPool = 512;   // learned pools up to this size are reordered
 
 // Work-list stages whose per-pair item counts depend on N_b; each has a
 // prefix array of B+1 entries in Work::pre, over the pairs in cost order.
-enum Stage { kPrep = 0, kCompat, kSc2, kSp, kRowBlk, kScore, kNumPrefix };
+enum Stage { kPrep = 0, kCompat, kSc2, kSp, kCollect, kRowBlk, kScore, kNumPrefix };
 // Rows of Work::pre after the stage prefixes: the cost order (slot -> pair), its inverse.
 constexpr int kOrderRow = kNumPrefix, kSlotRow = kNumPrefix + 1, kPreRows = kNumPrefix + 2;
 
@@ -86,7 +86,8 @@ struct Work {
     uint16_t *G;              // G arena
     int32_t *ghist;           // max_batch x kHistGroups x hist_stride weight histograms (filled by the SC2 epilogue)
     int32_t hist_stride;      // max_n rounded up to 8 (16-byte aligned copies)
-    int32_t *rowmax;          // max_batch x max_n: max_{j>i} G_ij (filled by the SC2 epilogue)
+    uint16_t *segmax;         // per pair npad / 64 x npad from g_off / 64: the maximum of G over the pairs i < j of
+                              // row i in each 64-column segment (segment-major, written by the SC2 kernels)
     int32_t compat_rows;      // rows of a compatibility tile per work item: 8, 16, 32, 64 or 128
     uint32_t *cnt_part;       // per compatibility work item: edges (15 bits), boundary pairs << 15, non-finite
                               // input << 30
@@ -202,6 +203,20 @@ __host__ __device__ inline PairDesc pair_desc_of(int32_t n, int32_t pt_off, int6
     return d;
 }
 
+// Segments (64 columns) of 64 rows that a wave of the row scan takes: sixteen, whose maxima it reads at once; one
+// in small pairs, which would fill few waves. Up to 512 matches the four waves of a workgroup share one segment by
+// rows (n = 300: 5.9 us, 6.2 apart); beyond, the workgroups' atomics cost more than that saves (n = 1000: 8.4 us,
+// 5.9 apart).
+__host__ __device__ inline int32_t collect_segs(int32_t n)
+{
+    return n <= 1024 ? 1 : 16;
+}
+
+__host__ __device__ inline bool collect_shared(int32_t n)
+{
+    return n <= 512;
+}
+
 __host__ __device__ inline int64_t stage_items(int stage, int32_t n, int32_t H, int32_t sp)
 {
     const int64_t npad = (n + kSc2Tile - 1) / kSc2Tile * kSc2Tile;
@@ -211,6 +226,10 @@ __host__ __device__ inline int64_t stage_items(int stage, int32_t n, int32_t H, 
     case kCompat: return nbc * (nbc + 1) / 2;
     case kSc2: return nbs * (nbs + 1) / 2;
     case kSp: { const int64_t nb = (n + sp - 1) / sp; return nb * (nb + 1) / 2; }   // bit-count tiles of edge sp
+    case kCollect: {
+        const int64_t nb = (n + 63) / 64, sg = collect_segs(n), units = nb * ((nb + sg - 1) / sg);
+        return collect_shared(n) ? units : (units + 3) / 4;
+    }
     case kRowBlk: return (n + kRowsPerItem - 1) / kRowsPerItem;
     default: return (int64_t)((H + kScoreHyp - 1) / kScoreHyp) * ((n + kScorePts - 1) / kScorePts);
     }

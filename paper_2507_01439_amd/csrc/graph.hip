@@ -343,7 +343,7 @@ __device__ __forceinline__ uint32_t transpose32(uint32_t x, int lane)
 // huge point (beyond 1e8), and thresholds outside [1e-9, 1e8], are evaluated exactly throughout.
 //
 // Counts (edges, boundary pairs, non-finite input; the last by diagonal items) go to the item's slot. The
-// diagonal items clear the pair's weight histograms and row maxima for their rows, and with learned pivots
+// diagonal items clear the pair's weight histograms for their rows, and with learned pivots
 // the SC2 row statistics and row marks.
 __global__ void __launch_bounds__(256) k_compat(Work w)
 {
@@ -485,7 +485,6 @@ __global__ void __launch_bounds__(256) k_compat(Work w)
                 for (int g = 0; g < kHistGroups; g += 2)
                     w.ghist[((int64_t)b * kHistGroups + g + (lane >> 5)) * w.hist_stride + ri] = 0;
                 const int64_t rw = (int64_t)b * w.max_n + ri;
-                if (lane < 32) w.rowmax[rw] = 0;
                 if (w.learned && lane < 32) {   // the SC2 row statistics and the row marks
                     w.rowstat[rw * 20 + 1] = 0;
                     w.rowstat[rw * 20 + 2] = 0;
@@ -628,7 +627,7 @@ constexpr int kHistBytes = kHistWords * 4;
 constexpr int kOutPitch = kOut + 8;            // uint16 per LDS row of a tile staged for the column statistics
 constexpr int kOutBytes = kOut * kOutPitch * 2;
 constexpr float kAccBias = 8388608.0f;         // 2^23: a count v < 2^16 is then the low 16 bits of 2^23 + v
-// What the epilogue leaves besides the weights: the histogram and row maxima the pivots need, the
+// What the epilogue leaves besides the weights: the histogram and segment maxima the pivots need, the
 // row sums and maxima the learned features need, or both (a learned registration).
 enum Sc2Mode { kSc2Plain = 0, kSc2Learned = 1, kSc2Features = 2 };
 constexpr int kSc2PerCu = 3;                   // workgroups resident per CU (registers: 168 per lane)
@@ -812,9 +811,8 @@ __device__ __forceinline__ void sc2_dense_tile(const Work &w, const PairDesc &d,
     // ---- epilogue: lane (l31, lh) of block (x, y) holds row i0 + 32x + l31 and, after the swaps, columns
     // j0 + 32y + 16q + 8 lh .. + 7 for q = 0, 1
     int32_t *gh = w.ghist + ((int64_t)b * kHistGroups + copy) * w.hist_stride;
-    int32_t *rowmax = w.rowmax + (int64_t)b * w.max_n;
     int32_t *rstat = w.rowstat + (int64_t)b * w.max_n * 20;
-    uint16_t *Gb = w.G + d.g_off;
+    uint16_t *Gb = w.G + d.g_off, *smax = w.segmax + d.g_off / 64 + (int64_t)(j0 / 64) * d.npad;
     const bool small_n = d.n <= kHistLdsBins + 1;
     const uint32_t spare = kHistLdsBins + lane;
     int wmax = 0;
@@ -880,12 +878,10 @@ __device__ __forceinline__ void sc2_dense_tile(const Work &w, const PairDesc &d,
             swap_halves(r0, r1);
             rs = (int)(r0 + r1);
         }
-        if (lh == 0 && m > 0) {   // m > 0 only in rows below n
-            if (MODE != kSc2Features) atomicMax(&rowmax[i], m);
-            if (MODE != kSc2Plain) {
-                atomicAdd(&rstat[i * 20 + 1], rs);
-                atomicMax(&rstat[i * 20 + 2], m);
-            }
+        if (MODE != kSc2Features && lh == 0) smax[i] = (uint16_t)m;
+        if (MODE != kSc2Plain && lh == 0 && m > 0) {   // m > 0 only in rows below n
+            atomicAdd(&rstat[i * 20 + 1], rs);
+            atomicMax(&rstat[i * 20 + 2], m);
         }
     }
     if (MODE != kSc2Features) {
@@ -985,11 +981,12 @@ constexpr int kSpMax = 1024;                       // largest tile edge
 constexpr int kSpSide = kSpMax * 16;               // one block's rows of I or J
 constexpr int kSpBufs = 4;                         // blocks in LDS: one counted, three in flight
 constexpr int kSpRing = kSpBufs * 2 * kSpSide;     // before and after the counting other data
-constexpr int kSpStat = kHistBytes;                // row maxima; with learned statistics also column maxima, sums
+constexpr int kSpStat = kHistBytes;                // learned statistics: column maxima, row and column sums
 // Weights up to kSpLow (most, where a tile has few edges) count in copies by lane: on few bins 64 lanes' adds queue.
 constexpr int kSpLow = 255, kSpCopies = 16, kSpPitch = kSpLow + 2;
-constexpr int kSpLowAt = kSpStat + 4 * kSpMax * 4;
-constexpr int kSpZero = kSpLowAt / 4 + kSpCopies * kSpPitch;   // words cleared before the weights are collected
+constexpr int kSpLowAt = kSpStat + 3 * kSpMax * 4;
+constexpr int kSpSegAt = kSpLowAt + kSpCopies * kSpPitch * 4;    // maxima by 64-column segment and row
+constexpr int kSpZero = kSpSegAt / 4 + kSpMax / 64 * kSpMax;     // words cleared before the weights are collected
 constexpr int kSpLds = kSpRing + 8 * kSpWaves + 16;
 static_assert(kSpCap * 16 <= kSpRing && 4 * kSpZero <= kSpRing && kSpZero % 4 == 0, "LDS layout of the bit-count kernel");
 
@@ -1011,8 +1008,8 @@ __global__ void __launch_bounds__(kSpThreads) k_sc2_sparse(Work w)
     typedef __attribute__((address_space(3))) const uint8_t lds8;
     typedef __attribute__((address_space(3))) const v4u ldsv;
     int32_t *hist = reinterpret_cast<int32_t *>(smem), *tmax = hist + kHistWords - 2;
-    int32_t *rmax = reinterpret_cast<int32_t *>(smem + kSpStat), *cmax = rmax + kSpMax, *rsum = cmax + kSpMax,
-            *csum = rsum + kSpMax;
+    int32_t *cmax = reinterpret_cast<int32_t *>(smem + kSpStat), *rsum = cmax + kSpMax, *csum = rsum + kSpMax;
+    int32_t *seg = reinterpret_cast<int32_t *>(smem + kSpSegAt);
     int32_t *scan = reinterpret_cast<int32_t *>(smem + kSpRing);
     uint32_t *list = reinterpret_cast<uint32_t *>(smem);
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1086,7 +1083,7 @@ __global__ void __launch_bounds__(kSpThreads) k_sc2_sparse(Work w)
             __syncthreads();
             continue;
         }
-        uint16_t *Gb = w.G + d.g_off;
+        uint16_t *Gb = w.G + d.g_off, *smax = w.segmax + d.g_off / 64 + (int64_t)(j0 / 64) * npad + i0;
         int32_t *gh = w.ghist + ((int64_t)b * kHistGroups + local % kHistGroups) * w.hist_stride;
         // zeros of the tile: rows from, from + step, .. below to (a wave), up to column npad
         const int zrows = min(S, n - i0), zcols = min(S, npad - j0);
@@ -1194,13 +1191,14 @@ __global__ void __launch_bounds__(kSpThreads) k_sc2_sparse(Work w)
 #pragma unroll
             for (int k = 0; k < kRuns; ++k) {
                 const int i = (int)(ed[4 * k] >> 20) & (kSpMax - 1);
-                int rm = 0, rs = 0;
+                int rs = 0;
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const uint32_t c = (int32_t)ed[4 * k + u] < 0 ? cnt[4 * k + u] : 0u;
                     const int j = (int)(ed[4 * k + u] >> 4) & (kSpMax - 1);
                     if (c > 0) {
                         Gb[(int64_t)(i0 + i) * npad + j0 + j] = (uint16_t)c;
+                        atomicMax(&seg[(j >> 6) * kSpMax + i], (int)c);
                         if (MODE != kSc2Features) {   // the weight histogram counts nonzero weights
                             if (c <= (uint32_t)kSpLow) lds_add(low, copy + c);
                             else if (c <= (uint32_t)kHistLdsBins) lds_add(hist, c - 1);
@@ -1211,13 +1209,9 @@ __global__ void __launch_bounds__(kSpThreads) k_sc2_sparse(Work w)
                             atomicMax(&cmax[j], (int)c);
                         }
                     }
-                    rm = max(rm, (int)c);
                     rs += (int)c;
                 }
-                if (rm > 0) {
-                    atomicMax(&rmax[i], rm);
-                    if (MODE != kSc2Plain) atomicAdd(&rsum[i], rs);
-                }
+                if (MODE != kSc2Plain && rs > 0) atomicAdd(&rsum[i], rs);
             }
             __syncthreads();
             // ---- the pass's row statistics and histogram
@@ -1228,12 +1222,17 @@ __global__ void __launch_bounds__(kSpThreads) k_sc2_sparse(Work w)
                 hist[tid - 1] = c;   // no other add reached these bins
             }
             if (tid < S) {
-                const int m = rmax[tid];
-                if (m > 0) {
-                    if (MODE != kSc2Features) {
-                        atomicMax(&w.rowmax[(int64_t)b * w.max_n + i0 + tid], m);
-                        atomicMax(tmax, m);
+                int m = 0;
+                for (int v = 0; v < S / 64; ++v) {
+                    const int x = seg[v * kSpMax + tid];
+                    m = max(m, x);
+                    if (MODE != kSc2Features && i0 + tid < npad && j0 + 64 * v < npad) {
+                        uint16_t *sm = smax + (int64_t)v * npad + tid;
+                        *sm = (uint16_t)(base == 0 ? x : max(x, (int)*sm));
                     }
+                }
+                if (m > 0) {
+                    if (MODE != kSc2Features) atomicMax(tmax, m);
                     if (MODE != kSc2Plain) {
                         int32_t *rs = w.rowstat + ((int64_t)b * w.max_n + i0 + tid) * 20;
                         atomicAdd(&rs[1], rsum[tid]);
@@ -1252,6 +1251,8 @@ __global__ void __launch_bounds__(kSpThreads) k_sc2_sparse(Work w)
         }
         if (all == 0) {
             zeros(wv, zrows, kSpWaves);
+            for (int v = 0; v < S / 64; ++v)
+                if (MODE != kSc2Features && tid < S && i0 + tid < npad && j0 + 64 * v < npad) smax[(int64_t)v * npad + tid] = 0;
             __syncthreads();   // scan is the next tile's
         }
     }

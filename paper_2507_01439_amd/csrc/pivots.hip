@@ -6,8 +6,8 @@
 // Every pair heavier than alpha is a pivot, and the first m pairs of weight
 // alpha in row-major order fill the remaining slots.
 //
-//   (the SC2 epilogue leaves kHistGroups weight histograms per pair and the
-//   per-row maximum of the upper triangle)
+//   (the SC2 kernels leave kHistGroups weight histograms per pair and the
+//   maximum of each row's 64-column segments of the upper triangle)
 //   k_thresh   sums the histograms; finds alpha, the pairs heavier than it
 //              (c_gt) and the ties to take (m); sums the compatibility
 //              kernel's per-tile counts (boundary pairs, edges, non-finite)
@@ -21,6 +21,8 @@
 // or a row-major tie index, so the pivot list does not depend on the order
 // atomics were served in.
 #include "common.h"
+
+#include <type_traits>
 
 namespace tr {
 namespace {
@@ -230,30 +232,31 @@ __global__ void __launch_bounds__(1024) k_thresh(Work w)
 
 // ---------------------------------------------------------------- row scan
 
-constexpr int kCollectCap = 2048;   // keys a workgroup stages in LDS before its one global reservation
+constexpr int kCollectCap = 1024;   // keys a workgroup stages in LDS before its one global reservation
 
-// One row (i, j > i) of the O2Graph per wave, all of its 16-byte chunks of
-// weights loaded before any is used (the pass is latency-bound); rows whose
-// maximum is below alpha are not read. Each chunk gives two 8-bit masks: the
-// pairs (inside i < j < n) heavier than alpha and those equal to it.
+// The pairs that can be pivots, appended to the workgroup's XCD region of the pool in no particular order (the
+// rank sort fixes it). A workgroup stages its keys in LDS, reserves its range with one atomic and copies them
+// out; if an item holds more than kCollectCap keys it reserves the count first and writes straight to the pool
+// on a second read.
 //
-// Collected keys: on the fast path (every pair of weight >= alpha fits the
-// pool) the pairs of weight >= alpha, on the ordered path the pairs heavier
-// than alpha (there are c_gt < K of them); either way they are appended to the
-// workgroup's XCD region of the pool in no particular order and the rank sort
-// fixes the order. A workgroup stages its keys in LDS, reserves its range with
-// one atomic and copies them out; if its rows hold more than kCollectCap keys
-// it reserves the count first and writes straight to the pool on a second
-// read of those rows.
+// Fast path (every pair of weight >= alpha fits the pool): a wave takes 64 rows by 16 segments of 64 columns,
+// reads the segments' maxima (a row per lane) and then only the segments that reach alpha, eight lanes each.
+// There are at most as many as collected keys, so the pass costs its round trips: of the weights, which a
+// whole-row scan mostly read (rows nearly all hold some pivot), a few per cent are touched.
+// 256 pairs of 800 to 5000 matches 440 -> 72 us, N = 20000 29 -> 10.3, N = 5000 8.9 -> 6.5; N = 300 5.4 -> 5.9 (from
+// one row per wave, read whole where its maximum reaches alpha).
 //
-// Ordered path, besides: per row, the pairs of weight alpha and a mask of the
-// 512-column segments holding any; per row block, their sum. The sort kernel
+// Ordered path: the pairs heavier than alpha (there are c_gt < K of them), one row per wave, all of its 16-byte
+// chunks loaded before any is used; rows whose maximum is below alpha are not read. Each chunk gives two 8-bit
+// masks: the pairs (inside i < j < n) heavier than alpha and those equal to it. Besides: per row, the pairs of
+// weight alpha and a mask of the 512-column segments holding any; per row block, their sum. The sort kernel
 // locates the first m ties in row-major order from these.
 __global__ void __launch_bounds__(256) k_rowscan(Work w)
 {
     __shared__ uint64_t buf[kCollectCap];
     __shared__ int32_t nbuf, base;
     __shared__ int32_t part[4];
+    __shared__ uint16_t list[4][64 * 16];
     __shared__ SlotCache slots;
     // batches of up to kInfoMax pairs: each slot's threshold, path and sizes in LDS as well, so an
     // item (four rows) starts with no device-memory round trip but its rows' maxima
@@ -263,22 +266,26 @@ __global__ void __launch_bounds__(256) k_rowscan(Work w)
         int64_t g_off;
     };
     __shared__ SlotInfo info[kInfoMax];
-    const bool cached = slot_cache_fill(w, kRowBlk, slots);
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    // the pool region and counter of this workgroup's XCD (workgroup g runs on XCD g mod 8)
+    const int rgn = blockIdx.x & (kCollectRegions - 1);
+    const bool cached = slot_cache_fill(w, kCollect, slots);
     const bool with_info = cached && w.plan->B <= kInfoMax;
     __syncthreads();
+    // some pair takes the ordered path (may, where the pairs are not all known here)
+    bool slow = !with_info;
     if (with_info)
-        for (int k = threadIdx.x; k < w.plan->B; k += blockDim.x) {
+        for (int k = tid; k < w.plan->B; k += blockDim.x) {
             const int b = slots.order[k];
             const PairState st = w.state[b];
             const PairDesc d = w.pairs[b];
             info[k] = SlotInfo{st.alpha, st.fast, d.kpiv, d.n, d.npad, 0, d.g_off};
+            slow |= d.kpiv > 0 && !st.fast;
         }
-    __syncthreads();
-    const int total = stage_total(w, kRowBlk);
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    for (int item = blockIdx.x; item < total; item += gridDim.x) {
-        int blk, b, alpha, fast;
-        PairDesc d;
+    if (with_info) slow = __syncthreads_or(slow);
+    // an item's pair, path and place in the pair; false: nothing to do (the same for the whole workgroup)
+    auto open_item = [&](Stage stage, int item, bool ordered, int &blk, int &b, int &alpha, PairDesc &d) {
+        int fast;
         if (with_info) {
             const int k = find_pair(slots.pre, w.plan->B, item);
             blk = item - slots.pre[k];
@@ -291,28 +298,153 @@ __global__ void __launch_bounds__(256) k_rowscan(Work w)
             d.npad = f.npad;
             d.g_off = f.g_off;
         } else {
-            b = stage_pair_cached(w, kRowBlk, slots, cached, item, blk);
+            b = stage_pair_cached(w, stage, slots, cached, item, blk);
             const PairState st = w.state[b];
             d = pair_desc(w, b);
             alpha = st.alpha;
             fast = st.fast;
         }
-        if (d.kpiv <= 0) continue;   // same for the whole workgroup
-        const bool ordered = !fast;
+        return d.kpiv > 0 && ordered == !fast;
+    };
+    // stage (direct = false) or write (direct = true, at base + ...) the keys of the set bits of hits[v]: pairs
+    // (i[v], 8 c[v] + e) with the weights q[v]
+    auto append = [&](auto n_c, const uint32_t *hits, const int *i, const int *c, const uint4 *q, bool direct, uint64_t *cand) {
+        constexpr int N = decltype(n_c)::value;
+        int m = 0;
+#pragma unroll
+        for (int v = 0; v < N; ++v) m += __builtin_popcount(hits[v]);
+        const int incl = wave_incl_scan(m);
+        const int tot = __builtin_amdgcn_readlane(incl, 63);
+        int off = 0;
+        if (lane == 63) off = atomicAdd(&nbuf, tot);
+        off = __builtin_amdgcn_readlane(off, 63) + incl - m;
+#pragma unroll
+        for (int v = 0; v < N; ++v) {
+            const uint32_t uw[4] = {q[v].x, q[v].y, q[v].z, q[v].w};
+            for (uint32_t h = hits[v]; h; h &= h - 1) {
+                const int e = __builtin_ctz(h);
+                const uint32_t lo = e & 2 ? uw[1] : uw[0], hi = e & 2 ? uw[3] : uw[2], x = e & 4 ? hi : lo;
+                const uint64_t key = pivot_key(e & 1 ? x >> 16 : x & 0xFFFFu, i[v], 8 * c[v] + e);
+                if (direct) {
+                    if (base + off < w.pool_cap) cand[base + off] = key;
+                } else if (off < kCollectCap) {
+                    buf[off] = key;
+                }
+                ++off;
+            }
+        }
+    };
+    // the item's keys into the pool: `scan` stages them, or writes them if the stage is too small
+    auto collect = [&](int b, uint64_t *cand, auto &&scan) {
+        if (tid == 0) nbuf = 0;
+        __syncthreads();
+        scan(false);
+        __syncthreads();
+        const int n_wg = nbuf;
+        __syncthreads();   // every thread has read nbuf before it is reset
+        if (n_wg > 0) {
+            if (tid == 0) base = atomicAdd(&w.tick[(int64_t)b * w.tick_stride + rgn * kTickLine], n_wg);
+            __syncthreads();
+            if (n_wg <= kCollectCap) {
+                for (int k = tid; k < n_wg; k += 256)
+                    if (base + k < w.pool_cap) cand[base + k] = buf[k];
+            } else {
+                if (tid == 0) nbuf = 0;
+                __syncthreads();
+                scan(true);
+            }
+        }
+    };
+    // ---- fast path
+    const int units = stage_total(w, kCollect);
+    for (int item = blockIdx.x; item < units; item += gridDim.x) {
+        int blk, b, alpha;
+        PairDesc d;
+        if (!open_item(kCollect, item, false, blk, b, alpha, d)) continue;
+        const int nseg = (d.n + 63) / 64, segs = collect_segs(d.n), u = collect_shared(d.n) ? blk : 4 * blk + wv, rb = u % nseg, s0 = u / nseg * segs;
+        uint64_t *cand = w.cand + ((int64_t)b * kCollectRegions + rgn) * w.pool_cap;
+        const uint16_t *G = w.G + d.g_off + (int64_t)(64 * rb) * d.npad;
+        int nh = 0;   // the wave's segments that reach alpha: row | segment << 6 in `list`
+        if (s0 < nseg && s0 + segs > rb) {   // segments left of the rows' own hold no pair
+            const int i = !collect_shared(d.n) || lane >> 4 == wv ? 64 * rb + lane : d.n;   // n: not this wave's row
+            const uint16_t *sm = w.segmax + d.g_off / 64 + i;
+            int m[16];
+#pragma unroll
+            for (int t = 0; t < 16; ++t) {
+                const int s = s0 + t;
+                m[t] = t < segs && s >= rb && s < nseg && i < d.n ? (int)sm[(int64_t)s * d.npad] : -1;
+            }
+#pragma unroll
+            for (int t = 0; t < 16; ++t) {
+                const bool hit = m[t] >= alpha;
+                const uint64_t mask = __ballot(hit);
+                if (hit)
+                    list[wv][nh + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0))] =
+                        (uint16_t)(lane | t << 6);
+                nh += __builtin_popcountll(mask);
+            }
+        }
+        collect(b, cand, [&](bool direct) {
+            for (int h0 = 0; h0 < nh; h0 += 64) {
+                uint4 q[8];
+                int row[8], c[8];
+#pragma unroll
+                for (int v = 0; v < 8; ++v) {
+                    const int h = h0 + 8 * v + (lane >> 3), x = list[wv][min(h, nh - 1)];
+                    row[v] = h < nh ? x & 63 : -1;
+                    c[v] = 8 * (s0 + (x >> 6)) + (lane & 7);
+                    q[v] = *reinterpret_cast<const uint4 *>(G + (int64_t)(x & 63) * d.npad + 8 * c[v]);
+                }
+                uint32_t hits[8];
+                bool any = false;
+#pragma unroll
+                for (int v = 0; v < 8; ++v) {
+                    // bit e: pair (i, 8c + e) lies in i < j < n and weighs at least alpha
+                    const int i = 64 * rb + row[v];
+                    const int lo = min(max(i + 1 - 8 * c[v], 0), 8), hi = min(max(d.n - 8 * c[v], 0), 8);
+                    const uint32_t range = row[v] < 0 ? 0u : ((1u << hi) - 1u) & ~((1u << lo) - 1u);
+                    const uint32_t uw[4] = {q[v].x, q[v].y, q[v].z, q[v].w};
+                    hits[v] = 0;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        hits[v] |= ((uint32_t)((int)(uw[k] & 0xFFFFu) >= alpha) << (2 * k)) |
+                                   ((uint32_t)((int)(uw[k] >> 16) >= alpha) << (2 * k + 1));
+                    hits[v] &= range;
+                    any |= hits[v] != 0;
+                    row[v] = i;
+                }
+                if (__any(any)) append(std::integral_constant<int, 8>(), hits, row, c, q, direct, cand);
+            }
+        });
+        __syncthreads();   // buf, nbuf, base and list are the next item's
+    }
+    if (w.n1 ? w.state[0].fast != 0 : !slow) return;
+    // ---- ordered path
+    __syncthreads();
+    slot_cache_fill(w, kRowBlk, slots);
+    __syncthreads();
+    const int total = stage_total(w, kRowBlk);
+    for (int item = blockIdx.x; item < total; item += gridDim.x) {
+        int blk, b, alpha;
+        PairDesc d;
+        if (!open_item(kRowBlk, item, true, blk, b, alpha, d)) continue;
         const int c1 = (d.n + 7) >> 3;
         const int i = blk * kRowsPerItem + wv;
-        const int rm = i < d.n ? w.rowmax[(int64_t)b * w.max_n + i] : 0;
-        const bool live = i < d.n && !(alpha > 0 && rm < alpha);
+        bool live = i < d.n && alpha <= 0;
+        if (i < d.n && alpha > 0) {   // some segment reaches alpha
+            const uint16_t *sm = w.segmax + d.g_off / 64 + i;
+            for (int s = (i >> 6) + lane; s < (d.n + 63) / 64; s += 64) live |= (int)sm[(int64_t)s * d.npad] >= alpha;
+            live = __any(live);
+        }
         const uint16_t *row = w.G + d.g_off + (int64_t)i * d.npad;
         const int c_lo = (i + 1) >> 3;
-        // the pool region and counter of this workgroup's XCD (workgroup g runs on XCD g mod 8)
-        const int rgn = blockIdx.x & (kCollectRegions - 1);
         uint64_t *cand = w.cand + ((int64_t)b * kCollectRegions + rgn) * w.pool_cap;
-        // direct = false: stage the keys into buf; true: write cand[base + ...]. ties / segs: the
-        // lane's pairs of weight alpha and the segments holding any (ordered path)
-        auto scan = [&](bool direct, int &ties, uint64_t &segs) {
-            ties = 0;
-            segs = 0;
+        // ties / segs: the lane's pairs of weight alpha and the segments holding any
+        int ties = 0;
+        uint64_t segs = 0;
+        collect(b, cand, [&](bool direct) {
+            if (!live) return;
             for (int c0 = c_lo; c0 < c1; c0 += 1024) {
                 uint4 q[16];
 #pragma unroll
@@ -331,79 +463,33 @@ __global__ void __launch_bounds__(256) k_rowscan(Work w)
                     const uint32_t uw[4] = {q[u].x, q[u].y, q[u].z, q[u].w};
                     uint32_t hge = 0, heq = 0;
 #pragma unroll
-                    for (int k = 0; k < 4; ++k)
+                    for (int k = 0; k < 4; ++k) {
                         hge |= ((uint32_t)((int)(uw[k] & 0xFFFFu) >= alpha) << (2 * k)) |
                                ((uint32_t)((int)(uw[k] >> 16) >= alpha) << (2 * k + 1));
-                    hge &= range;
-                    if (ordered) {   // the same on the whole workgroup
-#pragma unroll
-                        for (int k = 0; k < 4; ++k)
-                            heq |= ((uint32_t)((int)(uw[k] & 0xFFFFu) == alpha) << (2 * k)) |
-                                   ((uint32_t)((int)(uw[k] >> 16) == alpha) << (2 * k + 1));
-                        heq &= range;
-                        if (!direct) {
-                            ties += __builtin_popcount(heq);
-                            if (__any(heq != 0)) segs |= 1ull << ((c0 - c_lo) / 64 + u);   // at most 64 segments (N < 32768)
-                        }
+                        heq |= ((uint32_t)((int)(uw[k] & 0xFFFFu) == alpha) << (2 * k)) |
+                               ((uint32_t)((int)(uw[k] >> 16) == alpha) << (2 * k + 1));
                     }
-                    const uint32_t hits = hge & ~heq;   // fast path: heq is 0
-                    if (!__any(hits != 0)) continue;   // most chunks hold no key
-                    const int m = __builtin_popcount(hits);
-                    const int incl = wave_incl_scan(m);
-                    const int tot = __builtin_amdgcn_readlane(incl, 63);
-                    int off = 0;
-                    if (lane == 63) off = atomicAdd(&nbuf, tot);
-                    off = __builtin_amdgcn_readlane(off, 63) + incl - m;
-                    if (hits) {
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            if ((hits >> e) & 1u) {
-                                const uint32_t v = (uw[e >> 1] >> (16 * (e & 1))) & 0xFFFFu;
-                                const uint64_t key = pivot_key(v, i, 8 * c + e);
-                                if (direct) {
-                                    if (base + off < w.pool_cap) cand[base + off] = key;
-                                } else if (off < kCollectCap) {
-                                    buf[off] = key;
-                                }
-                                ++off;
-                            }
-                        }
+                    heq &= range;
+                    if (!direct) {
+                        ties += __builtin_popcount(heq);
+                        if (__any(heq != 0)) segs |= 1ull << ((c0 - c_lo) / 64 + u);   // at most 64 segments (N < 32768)
                     }
+                    const uint32_t hits = hge & range & ~heq;
+                    if (__any(hits != 0))   // most chunks hold no key
+                        append(std::integral_constant<int, 1>(), &hits, &i, &c, &q[u], direct, cand);
                 }
             }
-        };
-        int ties = 0, unused = 0;
-        uint64_t segs = 0, unused_segs = 0;
-        if (tid == 0) nbuf = 0;
-        __syncthreads();
-        if (live) scan(false, ties, segs);
-        __syncthreads();
-        const int n_wg = nbuf;
-        __syncthreads();   // every thread has read nbuf before it is reset
-        if (n_wg > 0) {
-            if (tid == 0) base = atomicAdd(&w.tick[(int64_t)b * w.tick_stride + rgn * kTickLine], n_wg);
-            __syncthreads();
-            if (n_wg <= kCollectCap) {
-                for (int k = tid; k < n_wg; k += 256)
-                    if (base + k < w.pool_cap) cand[base + k] = buf[k];
-            } else {
-                if (tid == 0) nbuf = 0;
-                __syncthreads();
-                if (live) scan(true, unused, unused_segs);
+        });
+        ties = __builtin_amdgcn_readlane(wave_incl_scan(ties), 63);
+        if (lane == 0) {
+            if (i < d.n) {
+                w.rowcnt[(int64_t)b * w.max_n + i] = ties;
+                w.rowseg[(int64_t)b * w.max_n + i] = segs;
             }
+            part[wv] = ties;
         }
-        if (ordered) {
-            ties = __builtin_amdgcn_readlane(wave_incl_scan(ties), 63);
-            if (lane == 0) {
-                if (i < d.n) {
-                    w.rowcnt[(int64_t)b * w.max_n + i] = ties;
-                    w.rowseg[(int64_t)b * w.max_n + i] = segs;
-                }
-                part[wv] = ties;
-            }
-            __syncthreads();
-            if (tid == 0) w.blkcnt[(int64_t)b * w.nblk_stride + blk] = part[0] + part[1] + part[2] + part[3];
-        }
+        __syncthreads();
+        if (tid == 0) w.blkcnt[(int64_t)b * w.nblk_stride + blk] = part[0] + part[1] + part[2] + part[3];
         __syncthreads();   // buf, nbuf, base and part are the next item's
     }
 }

@@ -47,9 +47,10 @@ struct tr_handle {
     Plan *plan = nullptr;
     int32_t *pre = nullptr;
     uint8_t *C = nullptr;
+    uint16_t *segmax = nullptr;
     uint16_t *G = nullptr;
     uint32_t *cnt_part = nullptr;
-    int32_t *ghist = nullptr, *rowmax = nullptr, *rowcnt = nullptr, *blkcnt = nullptr;
+    int32_t *ghist = nullptr, *rowcnt = nullptr, *blkcnt = nullptr;
     uint64_t *cand = nullptr, *rowseg = nullptr, *hyp_rec = nullptr;
     int32_t *tick = nullptr;
     int32_t *sp_list = nullptr;
@@ -155,7 +156,7 @@ void workspace_layout(tr_handle *h, Get &&get)
     get(h->G, B * nn);
     get(h->sp_list, 2 + B * stage_items(kSp, h->max_n, 0, 256));   // 256: its smallest tile
     get(h->ghist, B * kHistGroups * (size_t)((max_n + 7) & ~(size_t)7));
-    get(h->rowmax, B * max_n);
+    get(h->segmax, B * nn / 64);
     get(h->cnt_part, B * (size_t)stage_items(kCompat, h->npad_max, 0, 256) * (kCompatTile / kCompatMinRows));
     get(h->rowcnt, B * max_n);
     get(h->blkcnt, B * h->nblk_stride);
@@ -236,7 +237,7 @@ Work make_work(tr_handle *h, const float *src, const float *dst, const tr_params
     w.G = h->G;
     w.ghist = h->ghist;
     w.hist_stride = (h->max_n + 7) & ~7;
-    w.rowmax = h->rowmax;
+    w.segmax = h->segmax;
     w.cnt_part = h->cnt_part;
     w.rowcnt = h->rowcnt;
     w.blkcnt = h->blkcnt;
