@@ -355,7 +355,7 @@ hipError_t launch_compat_features(const Work &w, int64_t items, int cap, hipStre
 int sparse_tile(int64_t B, int32_t n, int num_cus);
 hipError_t launch_sc2_sparse(const Work &w, int64_t tiles, int num_cus, hipStream_t s);
 hipError_t launch_sc2(const Work &w, int64_t items, int num_cus, hipStream_t s);
-hipError_t launch_pivots(const Work &w, int B, int grid_rows, hipStream_t s);
+hipError_t launch_pivots(const Work &w, int B, int grid_rows, int num_cus, hipStream_t s);
 hipError_t launch_hyp(const Work &w, int B, int ppw, int grid, int num_cus, hipStream_t s);
 hipError_t launch_fit_triplets(const float *src, const float *dst, int n, const int32_t *tri, int T, float *poses,
                                int32_t *ok, int grid, hipStream_t s);

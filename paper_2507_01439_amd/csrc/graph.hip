@@ -356,6 +356,8 @@ __global__ void __launch_bounds__(256) k_compat(Work w)
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const float tau = w.tau, t2 = 2.0f * tau * tau, t4 = (tau * tau) * (tau * tau);
     const bool odd_tau = !(tau >= 1e-9f && tau <= 1e8f);
+    if (w.n1 && blockIdx.x == 0)   // its counters (collection regions, clique-search tickets)
+        for (int k = tid; k < w.tick_stride / kTickLine; k += 256) w.tick[k * kTickLine] = 0;
     if (w.n1 && blockIdx.x == 0 && tid == 0) {   // a single-pair call has no planner: reset its state here
         PairState st = {};
         st.status = TR_OK;

@@ -10,7 +10,8 @@
 //   maximum of each row's 64-column segments of the upper triangle)
 //   k_thresh   sums the histograms; finds alpha, the pairs heavier than it
 //              (c_gt) and the ties to take (m); sums the compatibility
-//              kernel's per-tile counts (boundary pairs, edges, non-finite)
+//              kernel's per-tile counts (boundary pairs, edges, non-finite);
+//              small single pairs do this at the start of k_rowscan
 //   k_rowscan  collects every pair of weight >= alpha when they fit the pool
 //              (fast path), else the pairs heavier than alpha and, per row and
 //              per row block, the count of pairs of weight alpha (ordered path)
@@ -22,6 +23,7 @@
 // atomics were served in.
 #include "common.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace tr {
@@ -101,39 +103,24 @@ __device__ __forceinline__ void load8(const uint16_t *row, int c, int (&v)[8])
     }
 }
 
-// alpha = the K-th largest weight over all N(N-1)/2 pairs (zeros included).
-__global__ void __launch_bounds__(1024) k_thresh(Work w)
+struct Threshold {
+    int32_t alpha, c_gt, m_eq, fast, ncand;   // as in PairState
+};
+
+// alpha = the K-th largest weight over all N(N-1)/2 pairs (zeros included), by a workgroup of NT threads.
+// hs: n ints of LDS.
+template <int NT>
+__device__ Threshold pair_threshold(const Work &w, const PairDesc &d, int b, int32_t *hs)
 {
-    extern __shared__ int32_t hs[];
-    __shared__ int32_t res[3], wtot[16];
-    __shared__ int32_t tally[16][3];
-    const int b = batch_pair(w, blockIdx.x);
-    const PairDesc d = pair_desc(w, b);
+    __shared__ int32_t wtot[NT / 64];
+    __shared__ Threshold res;
     const int64_t K = d.kpiv;
-    // this call's counters of the pair (collection regions, clique-search tickets) start at zero;
-    // the later kernels of the call update them
-    for (int k = threadIdx.x; k < w.tick_stride / kTickLine; k += 1024) w.tick[(int64_t)b * w.tick_stride + k * kTickLine] = 0;
-    if (K <= 0) return;
-    // boundary pairs, edges and non-finite input of the pair, summed over its compatibility items;
-    // the first eight items per thread are loaded together with the histogram
-    constexpr int kTiles = 8;
-    const int per = kCompatTile / w.compat_rows;   // work items per list tile
-    const int t0 = per * stage_first(w, kCompat, b), t1 = t0 + per * stage_count(w, kCompat, b);
-    int cc[3] = {0, 0, 0};
-    uint32_t tv[kTiles];
-    auto load_tiles = [&](int tb) {
-#pragma unroll
-        for (int u = 0; u < kTiles; ++u) {
-            const int t = tb + 1024 * u;
-            tv[u] = t < t1 ? w.cnt_part[t] : 0;
-        }
-    };
-    load_tiles(t0 + (int)threadIdx.x);
+    const int tid = threadIdx.x;
     const int32_t *gh = w.ghist + (int64_t)b * kHistGroups * w.hist_stride;
     // eight consecutive bins per thread: two 16-byte loads from each copy, all issued before any is
-    // summed (the pass is latency-bound: one round up to N = 8192); bins at or past n are never
-    // written and are not summed (the copies are padded to a multiple of 8)
-    for (int v0 = 8 * threadIdx.x; v0 < d.n; v0 += 8 * 1024) {
+    // summed (the pass is latency-bound: 1024 threads take one round up to N = 8192); bins at or past n are
+    // never written and are not summed (the copies are padded to a multiple of 8)
+    for (int v0 = 8 * tid; v0 < d.n; v0 += 8 * NT) {
         int4 c[kHistGroups][2];
 #pragma unroll
         for (int g = 0; g < kHistGroups; ++g) {
@@ -155,83 +142,141 @@ __global__ void __launch_bounds__(1024) k_thresh(Work w)
         for (int u = 0; u < 8; ++u)
             if (v0 + u < d.n) hs[v0 + u] = sum[u];
     }
-    for (int tb = t0 + (int)threadIdx.x;;) {
-#pragma unroll
-        for (int u = 0; u < kTiles; ++u) {
-            cc[0] += (tv[u] >> 15) & 0x7FFFu;
-            cc[1] += tv[u] & 0x7FFFu;
-            cc[2] |= tv[u] >> 30;
-        }
-        tb += 1024 * kTiles;
-        if (tb >= t1) break;
-        load_tiles(tb);
-    }
-#pragma unroll
-    for (int f = 0; f < 3; ++f) {
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) cc[f] += __shfl_xor(cc[f], o, 64);
-    }
-    if ((threadIdx.x & 63) == 0) {
-        tally[threadIdx.x >> 6][0] = cc[0];
-        tally[threadIdx.x >> 6][1] = cc[1];
-        tally[threadIdx.x >> 6][2] = cc[2];
-    }
     __syncthreads();
     // bins w = 1 .. n-1 walked from the top: thread t sums the contiguous positions u0 .. u1-1
-    // (u = n-1-w); an in-wave scan and the sixteen wave totals give each thread the count above
+    // (u = n-1-w); an in-wave scan and the wave totals give each thread the count above
     // its range, and the thread whose range holds the K-th largest weight walks it (counts stay
     // below n(n-1)/2 < 2^31)
     const int nb = d.n - 1;
-    const int cs = (nb + 1023) / 1024;
-    const int u0 = min(nb, (int)threadIdx.x * cs), u1 = min(nb, u0 + cs);
+    const int cs = (nb + NT - 1) / NT;
+    const int u0 = min(nb, tid * cs), u1 = min(nb, u0 + cs);
     int local = 0;
     for (int u = u0; u < u1; ++u) local += hs[d.n - 1 - u];
     const int incl = wave_incl_scan(local);
-    if ((threadIdx.x & 63) == 63) wtot[threadIdx.x >> 6] = incl;
+    if ((tid & 63) == 63) wtot[tid >> 6] = incl;
     __syncthreads();
     int64_t tot = 0, before = 0;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
+    for (int v = 0; v < NT / 64; ++v) {
         const int t = wtot[v];
-        before += v < (int)(threadIdx.x >> 6) ? t : 0;
+        before += v < (tid >> 6) ? t : 0;
         tot += t;
     }
     const int64_t excl = before + incl - local;
-    if (threadIdx.x == 0 && K > tot) { res[0] = 0; res[1] = (int32_t)tot; res[2] = (int32_t)(K - tot); }
+    // pairs of weight alpha: the histogram bin, or every pair of weight 0
+    auto found = [&](int alpha, int64_t above, int64_t ties) {
+        const bool fast = above + ties <= w.pool_cap;
+        res = Threshold{alpha, (int32_t)above, (int32_t)(K - above), fast, fast ? (int32_t)(above + ties) : (int32_t)K};
+    };
+    if (tid == 0 && K > tot) found(0, tot, (int64_t)d.n * (d.n - 1) / 2 - tot);
     if (K <= tot && excl < K && K <= excl + local) {
         int64_t cum = excl;
         for (int u = u0; u < u1; ++u) {
             const int wt = d.n - 1 - u;
             const int64_t c = hs[wt];
-            if (cum + c >= K) { res[0] = wt; res[1] = (int32_t)cum; res[2] = (int32_t)(K - cum); break; }
+            if (cum + c >= K) {
+                found(wt, cum, c);
+                break;
+            }
             cum += c;
         }
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const int alpha = res[0], c_gt = res[1];
-        // pairs of weight alpha: the histogram bin, or every pair of weight 0
-        const int64_t ties = alpha > 0 ? hs[alpha] : (int64_t)d.n * (d.n - 1) / 2 - tot;
-        const bool fast = c_gt + ties <= w.pool_cap;
-        w.state[b].alpha = alpha;
-        w.state[b].c_gt = c_gt;
-        w.state[b].m_eq = res[2];
-        w.state[b].fast = fast ? 1 : 0;
-        w.state[b].ncand = fast ? (int32_t)(c_gt + ties) : (int32_t)K;
-        int tb = 0, te = 0, tn = 0;
-        for (int v = 0; v < 16; ++v) {
-            tb += tally[v][0];
-            te += tally[v][1];
-            tn |= tally[v][2];
+    return res;
+}
+
+__device__ __forceinline__ void store_threshold(PairState &st, const Threshold &t)
+{
+    st.alpha = t.alpha;
+    st.c_gt = t.c_gt;
+    st.m_eq = t.m_eq;
+    st.fast = t.fast;
+    st.ncand = t.ncand;
+}
+
+// Boundary pairs, edges and non-finite input of the pair, summed over its compatibility items by NT threads; the
+// first eight items per thread are loaded at construction.
+template <int NT>
+struct Tally {
+    static constexpr int kItems = 8;
+    int t0, t1;
+    uint32_t tv[kItems];
+
+    __device__ __forceinline__ void load(const Work &w, int tb)
+    {
+#pragma unroll
+        for (int u = 0; u < kItems; ++u) {
+            const int t = tb + NT * u;
+            tv[u] = t < t1 ? w.cnt_part[t] : 0;
         }
-        w.state[b].n_boundary = tb;
-        w.state[b].n_edges = te;
-        w.state[b].nonfinite = tn != 0;
     }
+
+    __device__ __forceinline__ Tally(const Work &w, int b)
+    {
+        const int per = kCompatTile / w.compat_rows;   // work items per list tile
+        t0 = per * stage_first(w, kCompat, b);
+        t1 = t0 + per * stage_count(w, kCompat, b);
+        load(w, t0 + (int)threadIdx.x);
+    }
+
+    __device__ void store(const Work &w, int b)
+    {
+        __shared__ int32_t tally[NT / 64][3];
+        int cc[3] = {0, 0, 0};
+        for (int tb = t0 + (int)threadIdx.x;;) {
+#pragma unroll
+            for (int u = 0; u < kItems; ++u) {
+                cc[0] += (tv[u] >> 15) & 0x7FFFu;
+                cc[1] += tv[u] & 0x7FFFu;
+                cc[2] |= tv[u] >> 30;
+            }
+            tb += NT * kItems;
+            if (tb >= t1) break;
+            load(w, tb);
+        }
+#pragma unroll
+        for (int f = 0; f < 3; ++f) {
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) cc[f] += __shfl_xor(cc[f], o, 64);
+        }
+        if ((threadIdx.x & 63) == 0) {
+            tally[threadIdx.x >> 6][0] = cc[0];
+            tally[threadIdx.x >> 6][1] = cc[1];
+            tally[threadIdx.x >> 6][2] = cc[2];
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            int tb = 0, te = 0, tn = 0;
+            for (int v = 0; v < NT / 64; ++v) {
+                tb += tally[v][0];
+                te += tally[v][1];
+                tn |= tally[v][2];
+            }
+            w.state[b].n_boundary = tb;
+            w.state[b].n_edges = te;
+            w.state[b].nonfinite = tn != 0;
+        }
+    }
+};
+
+__global__ void __launch_bounds__(1024) k_thresh(Work w)
+{
+    extern __shared__ int32_t hs[];
+    const int b = batch_pair(w, blockIdx.x);
+    const PairDesc d = pair_desc(w, b);
+    // this call's counters of the pair (collection regions, clique-search tickets) start at zero;
+    // the later kernels of the call update them
+    for (int k = threadIdx.x; k < w.tick_stride / kTickLine; k += 1024) w.tick[(int64_t)b * w.tick_stride + k * kTickLine] = 0;
+    if (d.kpiv <= 0) return;
+    Tally<1024> tally(w, b);
+    const Threshold t = pair_threshold<1024>(w, d, b, hs);
+    if (threadIdx.x == 0) store_threshold(w.state[b], t);
+    tally.store(w, b);
 }
 
 // ---------------------------------------------------------------- row scan
 
+constexpr int kFuseThreshMax = 8192;   // matches of a single pair up to which the row scan finds the threshold itself
 constexpr int kCollectCap = 1024;   // keys a workgroup stages in LDS before its one global reservation
 
 // The pairs that can be pivots, appended to the workgroup's XCD region of the pool in no particular order (the
@@ -251,8 +296,16 @@ constexpr int kCollectCap = 1024;   // keys a workgroup stages in LDS before its
 // masks: the pairs (inside i < j < n) heavier than alpha and those equal to it. Besides: per row, the pairs of
 // weight alpha and a mask of the 512-column segments holding any; per row block, their sum. The sort kernel
 // locates the first m ties in row-major order from these.
+//
+// FUSED (a single pair of few matches): every workgroup finds the threshold itself, from the same histograms, in
+// place of a kernel before this one; the first stores it, the last sums the pair's counts. No more workgroups than
+// CUs, as each reads all copies of the histogram. Both kernels / this one alone (us, without the gap between them):
+// N = 300 11.3 / 7.4, N = 1000 11.3 / 7.6, N = 2749 12.1 / 9.4, N = 5000 13.9 / 10.6; a call of 6500 matches
+// 125.4 / 122.3, of 8000 170.9 / 170.9.
+template <bool FUSED>
 __global__ void __launch_bounds__(256) k_rowscan(Work w)
 {
+    extern __shared__ int32_t hs[];   // FUSED
     __shared__ uint64_t buf[kCollectCap];
     __shared__ int32_t nbuf, base;
     __shared__ int32_t part[4];
@@ -269,7 +322,15 @@ __global__ void __launch_bounds__(256) k_rowscan(Work w)
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     // the pool region and counter of this workgroup's XCD (workgroup g runs on XCD g mod 8)
     const int rgn = blockIdx.x & (kCollectRegions - 1);
-    const bool cached = slot_cache_fill(w, kCollect, slots);
+    Threshold own{};
+    if (FUSED) {
+        const PairDesc d = pair_desc(w, 0);
+        if (d.kpiv <= 0) return;
+        if (blockIdx.x == gridDim.x - 1) Tally<256>(w, 0).store(w, 0);
+        own = pair_threshold<256>(w, d, 0, hs);
+        if (blockIdx.x == 0 && tid == 0) store_threshold(w.state[0], own);
+    }
+    const bool cached = !FUSED && slot_cache_fill(w, kCollect, slots);
     const bool with_info = cached && w.plan->B <= kInfoMax;
     __syncthreads();
     // some pair takes the ordered path (may, where the pairs are not all known here)
@@ -299,10 +360,9 @@ __global__ void __launch_bounds__(256) k_rowscan(Work w)
             d.g_off = f.g_off;
         } else {
             b = stage_pair_cached(w, stage, slots, cached, item, blk);
-            const PairState st = w.state[b];
             d = pair_desc(w, b);
-            alpha = st.alpha;
-            fast = st.fast;
+            alpha = FUSED ? own.alpha : w.state[b].alpha;
+            fast = FUSED ? own.fast : w.state[b].fast;
         }
         return d.kpiv > 0 && ordered == !fast;
     };
@@ -419,10 +479,10 @@ __global__ void __launch_bounds__(256) k_rowscan(Work w)
         });
         __syncthreads();   // buf, nbuf, base and list are the next item's
     }
-    if (w.n1 ? w.state[0].fast != 0 : !slow) return;
+    if (FUSED ? own.fast != 0 : w.n1 ? w.state[0].fast != 0 : !slow) return;
     // ---- ordered path
     __syncthreads();
-    slot_cache_fill(w, kRowBlk, slots);
+    if (!FUSED) slot_cache_fill(w, kRowBlk, slots);
     __syncthreads();
     const int total = stage_total(w, kRowBlk);
     for (int item = blockIdx.x; item < total; item += gridDim.x) {
@@ -687,10 +747,14 @@ __global__ void __launch_bounds__(kSortThreads) k_sort(Work w, int blocks_per_pa
 }  // namespace
 
 // grid_rows: workgroups of the row scan
-hipError_t launch_pivots(const Work &w, int B, int grid_rows, hipStream_t s)
+hipError_t launch_pivots(const Work &w, int B, int grid_rows, int num_cus, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_thresh, dim3(B), dim3(1024), (size_t)w.max_n * sizeof(int32_t), s, w);
-    hipLaunchKernelGGL(k_rowscan, dim3(grid_rows), dim3(256), 0, s, w);
+    if (w.n1 && w.n1 <= kFuseThreshMax) {
+        hipLaunchKernelGGL(k_rowscan<true>, dim3(std::min(grid_rows, num_cus)), dim3(256), (size_t)w.n1 * sizeof(int32_t), s, w);
+    } else {
+        hipLaunchKernelGGL(k_thresh, dim3(B), dim3(1024), (size_t)w.max_n * sizeof(int32_t), s, w);
+        hipLaunchKernelGGL(k_rowscan<false>, dim3(grid_rows), dim3(256), 0, s, w);
+    }
     const int bpp = (w.pool_cap + 63) / 64;   // the fast path may rank up to pool_cap keys
     hipLaunchKernelGGL(k_sort, dim3(B * bpp), dim3(kSortThreads), (size_t)((w.pool_cap + 15) & ~15) * sizeof(uint64_t),
                        s, w, bpp);

@@ -44,3 +44,24 @@ def test_a_cluster_of_pivots_and_pool_overflow(n):
             check_taps(reg, X, Y, prm, r, mask, label=f"cluster n={n} k1={k1}")
         finally:
             reg.close()
+
+
+@pytest.mark.parametrize("ratio", [0.0, 0.3])
+@pytest.mark.parametrize("n", [3, 257, 2049, 4100, 8192, 8193])
+def test_single_pair_finds_the_batch_threshold(n, ratio):
+    # a single pair's row scan finds the threshold itself up to 8192 matches, a batch's and a larger one's are given it
+    say(f"threshold n={n} ratio={ratio}")
+    p = synth.make_pair(synth.CONFIGS["indoor_n1000"].replace(n=n, inlier_ratio=ratio), 90 + n)
+    prm = T.make_params(0.1, 0.1, k1=300, k2=2)
+    reg = T.Registrar(max_n=n, max_batch=1, max_k1=300, max_k2=2)
+    try:
+        src, dst = torch.from_numpy(p.src).cuda(), torch.from_numpy(p.dst).cuda()
+        offs = torch.tensor([0, n], dtype=torch.int32, device="cuda")
+        got = []
+        for batch in (False, True):
+            out, mask = reg.register_batch(src, dst, offs, prm, max_n=n) if batch else reg.register(src, dst, prm)
+            torch.cuda.synchronize()
+            got.append((out.cpu().numpy().tobytes(), mask.cpu().numpy()[:n].tobytes(), reg.debug(T.TR_TAP_PIVOTS, 0).tobytes()))
+        assert got[0] == got[1]
+    finally:
+        reg.close()
