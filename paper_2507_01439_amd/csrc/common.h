@@ -86,8 +86,8 @@ struct Work {
     uint16_t *G;              // G arena
     int32_t *ghist;           // max_batch x kHistGroups x hist_stride weight histograms (filled by the SC2 epilogue)
     int32_t hist_stride;      // max_n rounded up to 8 (16-byte aligned copies)
-    uint16_t *segmax;         // per pair npad / 64 x npad from g_off / 64: the maximum of G over the pairs i < j of
-                              // row i in each 64-column segment (segment-major, written by the SC2 kernels)
+    uint16_t *segmax;         // per pair npad x npad / 64 from g_off / 64: the maximum of G over the pairs i < j of row
+                              // i in each 64-column segment (order: part_at; written by the SC2 kernels)
     int32_t compat_rows;      // rows of a compatibility tile per work item: 8, 16, 32, 64 or 128
     uint32_t *cnt_part;       // per compatibility work item: edges (15 bits), boundary pairs << 15, non-finite
                               // input << 30
@@ -113,7 +113,12 @@ struct Work {
     float *gscore;            // max_batch x h_cap error-based scores (metric != 0)
     int32_t metric;           // hypothesis ranking: 0 inlier number, 1 MAE form, 2 MSE form
     int32_t h_cap;
-    int32_t *rowstat;         // max_batch x max_n x 20 feature accumulators (learned mode)
+    int32_t *rowstat;         // max_batch x max_n x 20 feature accumulators (learned mode): degree, two unused, 16 bins
+    // row sums and maxima of the SC2 matrix in parts that the SC2 kernels store (learned mode), with segmax: row i's
+    // sum over the pairs i < j of each 64-column segment (as segmax), and per 128-row block and column the sum and
+    // maximum over the pairs i < j of the block (npad x npad / 128 from g_off / 128)
+    int32_t *rowsum, *colsum;
+    uint16_t *colmax;
     int32_t *mark;            // max_batch x max_n: row claimed by a candidate-feature workgroup
     int32_t feat_all;         // learned features for every match (training) instead of the pool's
     uint16_t *feat;           // max_batch x max_n x 19 bfloat16 features
@@ -201,6 +206,13 @@ __host__ __device__ inline PairDesc pair_desc_of(int32_t n, int32_t pt_off, int6
     d.c_off = arena_off;
     d.g_off = arena_off;
     return d;
+}
+
+// Place of row (column) x's k-th of `parts` partial values: 32 rows together, so that a kernel stores whole lines and
+// one that sums a row's parts stays within few pages.
+__host__ __device__ inline int32_t part_at(int32_t x, int32_t k, int32_t parts)
+{
+    return ((x >> 5) * parts + k) * 32 + (x & 31);
 }
 
 // Segments (64 columns) of 64 rows that a wave of the row scan takes: sixteen, whose maxima it reads at once; one

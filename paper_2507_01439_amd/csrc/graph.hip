@@ -344,7 +344,7 @@ __device__ __forceinline__ uint32_t transpose32(uint32_t x, int lane)
 //
 // Counts (edges, boundary pairs, non-finite input; the last by diagonal items) go to the item's slot. The
 // diagonal items clear the pair's weight histograms for their rows, and with learned pivots
-// the SC2 row statistics and row marks.
+// the row marks.
 __global__ void __launch_bounds__(256) k_compat(Work w)
 {
     __shared__ float4 rows[4][32][2];
@@ -487,11 +487,7 @@ __global__ void __launch_bounds__(256) k_compat(Work w)
                 for (int g = 0; g < kHistGroups; g += 2)
                     w.ghist[((int64_t)b * kHistGroups + g + (lane >> 5)) * w.hist_stride + ri] = 0;
                 const int64_t rw = (int64_t)b * w.max_n + ri;
-                if (w.learned && lane < 32) {   // the SC2 row statistics and the row marks
-                    w.rowstat[rw * 20 + 1] = 0;
-                    w.rowstat[rw * 20 + 2] = 0;
-                    w.mark[rw] = 0;
-                }
+                if (w.learned && lane < 32) w.mark[rw] = 0;   // the row marks
             }
         }
         const int sums = wave_sum((nbnd << 15) | nedge);   // at most 16384 pairs each
@@ -670,9 +666,11 @@ __device__ __forceinline__ void lds_add(int32_t *hist, uint32_t k)
 // Sums and maxima of the tile's columns (column j of the upper tile is row j of the lower one, the
 // SC2 matrix being symmetric), from the masked tile T[ROWS][pitch] in LDS: thread t takes columns 2c,
 // 2c+1 (c = t mod COLS/2) over rows of one residue class, sixteen 4-byte reads in flight; the classes
-// meet in xl (3 ints per column pair and class). j_base: the tile's first column.
+// meet in xl (3 ints per column pair and class). csum, cmax: the tile's first column there, its groups
+// of 32 columns `stride` apart.
 template <int ROWS, int COLS>
-__device__ __forceinline__ void column_stats(const uint16_t *T, int pitch, int32_t *xl, int32_t *rstat, int j_base)
+__device__ __forceinline__ void column_stats(const uint16_t *T, int pitch, int32_t *xl, int32_t *csum, uint16_t *cmax,
+                                             int stride)
 {
     constexpr int kPairs = COLS / 2, kCls = 256 / kPairs;   // column pairs; row classes
     const int cp = threadIdx.x % kPairs, cls = threadIdx.x / kPairs;
@@ -706,15 +704,9 @@ __device__ __forceinline__ void column_stats(const uint16_t *T, int pitch, int32
             s1 += x[1];
             mx = __builtin_elementwise_max(mx, __builtin_bit_cast(u16x2, (uint32_t)x[2]));
         }
-        const int cs[2] = {s0, s1}, cm[2] = {(int)mx.x, (int)mx.y};
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            const int j = j_base + 2 * cp + e;
-            if (cm[e] > 0) {
-                atomicAdd(&rstat[j * 20 + 1], cs[e]);
-                atomicMax(&rstat[j * 20 + 2], cm[e]);
-            }
-        }
+        const int at = cp / 16 * stride + 2 * cp % 32;
+        *reinterpret_cast<int2 *>(csum + at) = make_int2(s0, s1);
+        *reinterpret_cast<uint32_t *>(cmax + at) = __builtin_bit_cast(uint32_t, mx);
     }
 }
 
@@ -813,8 +805,7 @@ __device__ __forceinline__ void sc2_dense_tile(const Work &w, const PairDesc &d,
     // ---- epilogue: lane (l31, lh) of block (x, y) holds row i0 + 32x + l31 and, after the swaps, columns
     // j0 + 32y + 16q + 8 lh .. + 7 for q = 0, 1
     int32_t *gh = w.ghist + ((int64_t)b * kHistGroups + copy) * w.hist_stride;
-    int32_t *rstat = w.rowstat + (int64_t)b * w.max_n * 20;
-    uint16_t *Gb = w.G + d.g_off, *smax = w.segmax + d.g_off / 64 + (int64_t)(j0 / 64) * d.npad;
+    uint16_t *Gb = w.G + d.g_off;
     const bool small_n = d.n <= kHistLdsBins + 1;
     const uint32_t spare = kHistLdsBins + lane;
     int wmax = 0;
@@ -880,10 +871,12 @@ __device__ __forceinline__ void sc2_dense_tile(const Work &w, const PairDesc &d,
             swap_halves(r0, r1);
             rs = (int)(r0 + r1);
         }
-        if (MODE != kSc2Features && lh == 0) smax[i] = (uint16_t)m;
-        if (MODE != kSc2Plain && lh == 0 && m > 0) {   // m > 0 only in rows below n
-            atomicAdd(&rstat[i * 20 + 1], rs);
-            atomicMax(&rstat[i * 20 + 2], m);
+        if (lh == 0) {
+            // parts that the readers add up: atomics on the rows' totals (and the columns' below) took 16 of 53 us at
+            // N = 5000 and 150 of 800 us for 64 feature pairs
+            const int64_t at = d.g_off / 64 + part_at(i, j0 / 64, d.npad / 64);
+            w.segmax[at] = (uint16_t)m;
+            if (MODE != kSc2Plain) w.rowsum[at] = rs;
         }
     }
     if (MODE != kSc2Features) {
@@ -892,7 +885,10 @@ __device__ __forceinline__ void sc2_dense_tile(const Work &w, const PairDesc &d,
     }
     __syncthreads();   // T, the histogram and the tile's maximum are complete
     if (MODE != kSc2Features) hist_flush(hist, gh, min(*tmax, kHistLdsBins));
-    if (MODE != kSc2Plain) column_stats<kOut, kOut>(T, kOutPitch, reinterpret_cast<int32_t *>(T), rstat, bj * kOut);
+    if (MODE != kSc2Plain) {
+        const int64_t at = d.g_off / 128 + part_at(bj * kOut, bi, d.npad / kOut);
+        column_stats<kOut, kOut>(T, kOutPitch, reinterpret_cast<int32_t *>(T), w.colsum + at, w.colmax + at, d.npad / kOut * 32);
+    }
 }
 
 // This workgroup's share of the SC2 list in 256 x 256 tiles: XCD x takes a contiguous range of the
@@ -1085,7 +1081,7 @@ __global__ void __launch_bounds__(kSpThreads) k_sc2_sparse(Work w)
             __syncthreads();
             continue;
         }
-        uint16_t *Gb = w.G + d.g_off, *smax = w.segmax + d.g_off / 64 + (int64_t)(j0 / 64) * npad + i0;
+        uint16_t *Gb = w.G + d.g_off;
         int32_t *gh = w.ghist + ((int64_t)b * kHistGroups + local % kHistGroups) * w.hist_stride;
         // zeros of the tile: rows from, from + step, .. below to (a wave), up to column npad
         const int zrows = min(S, n - i0), zcols = min(S, npad - j0);
@@ -1094,6 +1090,28 @@ __global__ void __launch_bounds__(kSpThreads) k_sc2_sparse(Work w)
                 uint16_t *p = Gb + (int64_t)(i0 + r) * npad + j0;
                 for (int c = 8 * lane; c < zcols; c += 512) *reinterpret_cast<uint4 *>(p + c) = make_uint4(0, 0, 0, 0);
             }
+        };
+        // learned statistics of row i0 + t and column j0 + t (rs, cs: sums, cm: maximum; `more`: beyond those stored
+        // already): the tile's sums stand in one of its segments that the row has, zeros in the others
+        auto tile_stats = [&](int rs, int cs, int cm, bool more) {
+            const int own = diag ? tid / 64 : 0;
+            for (int v = 0; v < S / 64; ++v)
+                if (i0 + tid < npad && j0 + 64 * v < npad) {
+                    int32_t *p = w.rowsum + d.g_off / 64 + part_at(i0 + tid, j0 / 64 + v, npad / 64);
+                    if (v == own) *p = more ? *p + rs : rs;
+                    else if (!more) *p = 0;
+                }
+            for (int v = 0; v < S / 128; ++v)
+                if (j0 + tid < npad && i0 + 128 * v < npad) {
+                    const int64_t at = d.g_off / 128 + part_at(j0 + tid, i0 / 128 + v, npad / 128);
+                    if (v == 0) {
+                        w.colsum[at] = more ? w.colsum[at] + cs : cs;
+                        w.colmax[at] = (uint16_t)(more ? max(cm, (int)w.colmax[at]) : cm);
+                    } else if (!more) {
+                        w.colsum[at] = 0;
+                        w.colmax[at] = 0;
+                    }
+                }
         };
         for (int base = 0; base < all; base += kSpCap) {
             const int np = min(kSpCap, all - base);   // runs of this pass
@@ -1228,24 +1246,13 @@ __global__ void __launch_bounds__(kSpThreads) k_sc2_sparse(Work w)
                 for (int v = 0; v < S / 64; ++v) {
                     const int x = seg[v * kSpMax + tid];
                     m = max(m, x);
-                    if (MODE != kSc2Features && i0 + tid < npad && j0 + 64 * v < npad) {
-                        uint16_t *sm = smax + (int64_t)v * npad + tid;
+                    if (i0 + tid < npad && j0 + 64 * v < npad) {
+                        uint16_t *sm = w.segmax + d.g_off / 64 + part_at(i0 + tid, j0 / 64 + v, npad / 64);
                         *sm = (uint16_t)(base == 0 ? x : max(x, (int)*sm));
                     }
                 }
-                if (m > 0) {
-                    if (MODE != kSc2Features) atomicMax(tmax, m);
-                    if (MODE != kSc2Plain) {
-                        int32_t *rs = w.rowstat + ((int64_t)b * w.max_n + i0 + tid) * 20;
-                        atomicAdd(&rs[1], rsum[tid]);
-                        atomicMax(&rs[2], m);
-                    }
-                }
-                if (MODE != kSc2Plain && cmax[tid] > 0) {
-                    int32_t *rs = w.rowstat + ((int64_t)b * w.max_n + j0 + tid) * 20;
-                    atomicAdd(&rs[1], csum[tid]);
-                    atomicMax(&rs[2], cmax[tid]);
-                }
+                if (MODE != kSc2Features && m > 0) atomicMax(tmax, m);
+                if (MODE != kSc2Plain) tile_stats(rsum[tid], csum[tid], cmax[tid], base > 0);
             }
             __syncthreads();
             if (MODE != kSc2Features) hist_flush(hist, gh, min(*tmax, kHistLdsBins));
@@ -1254,7 +1261,9 @@ __global__ void __launch_bounds__(kSpThreads) k_sc2_sparse(Work w)
         if (all == 0) {
             zeros(wv, zrows, kSpWaves);
             for (int v = 0; v < S / 64; ++v)
-                if (MODE != kSc2Features && tid < S && i0 + tid < npad && j0 + 64 * v < npad) smax[(int64_t)v * npad + tid] = 0;
+                if (tid < S && i0 + tid < npad && j0 + 64 * v < npad)
+                    w.segmax[d.g_off / 64 + part_at(i0 + tid, j0 / 64 + v, npad / 64)] = 0;
+            if (MODE != kSc2Plain && tid < S) tile_stats(0, 0, 0, false);
             __syncthreads();   // scan is the next tile's
         }
     }

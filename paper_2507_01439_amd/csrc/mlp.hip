@@ -68,6 +68,24 @@ __device__ float forward(const MlpLds &L, const float (&x)[19])
 
 // ---------------------------------------------------------------- features
 
+// Sum and maximum of row i of the SC2 matrix from the parts k, k + step, .. that the SC2 kernels left: the row's own
+// segments and, the matrix being symmetric, its column's blocks above.
+__device__ __forceinline__ void sc2_row_parts(const Work &w, const PairDesc &d, int i, int k, int step, int &sum, int &mx)
+{
+    const int64_t at = d.g_off / 64 + part_at(i, 0, d.npad / 64), ct = d.g_off / 128 + part_at(i, 0, d.npad / 128);
+    sum = mx = 0;
+#pragma unroll 4
+    for (int s = i / 64 + k; s < (d.n + 63) / 64; s += step) {
+        sum += w.rowsum[at + 32 * s];
+        mx = max(mx, (int)w.segmax[at + 32 * s]);
+    }
+#pragma unroll 4
+    for (int s = k; s <= i / 128; s += step) {
+        sum += w.colsum[ct + 32 * s];
+        mx = max(mx, (int)w.colmax[ct + 32 * s]);
+    }
+}
+
 // 19 values per match from the integer accumulators (degree, SC2 row sum and
 // max, 16-bin delta histogram): ratios formed in float64, rounded to float32,
 // then to bfloat16.
@@ -81,11 +99,13 @@ __global__ void __launch_bounds__(256) k_features(Work w, uint16_t *packed)
         const int i = local * kPrepRows + threadIdx.x;
         if (i >= d.n) continue;
         const int32_t *rs = w.rowstat + ((int64_t)b * w.max_n + i) * 20;
+        int sum, mx;
+        sc2_row_parts(w, d, i, 0, 1, sum, mx);
         const double n1 = (double)(d.n - 1), n = (double)d.n;
         uint16_t *f = packed ? packed + (int64_t)(d.pt_off + i) * 19 : w.feat + ((int64_t)b * w.max_n + i) * 19;
         f[0] = f2bf((float)((double)rs[0] / n1));
-        f[1] = f2bf((float)((double)rs[1] / (n1 * n)));
-        f[2] = f2bf((float)((double)rs[2] / n));
+        f[1] = f2bf((float)((double)sum / (n1 * n)));
+        f[2] = f2bf((float)((double)mx / n));
 #pragma unroll
         for (int k = 0; k < 16; ++k) f[3 + k] = f2bf((float)((double)rs[3 + k] / n1));
     }
@@ -224,11 +244,11 @@ __device__ __forceinline__ void place_pivot(const Work &w, int b, int K, int p, 
 // each of the pair's points once and evaluates delta_ij against all claimed
 // rows, exactly as the compatibility kernel does (same operation order,
 // correctly rounded square roots), counting the degree and the 16-bin delta
-// histogram; the SC2 row sum and maximum come from the SC2 epilogue (loaded at
-// the claim, in flight during the point loop). Each wave then scores the rows
+// histogram; the SC2 row sum and maximum are added up from the SC2 kernels'
+// parts, a row per wave. Each wave then scores the rows
 // of its slot. Matches outside the pool get no features and no score.
 //
-__global__ void __launch_bounds__(256) k_cand_rows(Work w, int B, int R, const uint16_t *wbf16, const float *w32)
+__global__ void __launch_bounds__(256, 2) k_cand_rows(Work w, int B, int R, const uint16_t *wbf16, const float *w32)
 {
     __shared__ float crd[kCandRows][6];
     __shared__ int32_t row_l[kCandRows], rsv_l[kCandRows][2];
@@ -271,7 +291,7 @@ __global__ void __launch_bounds__(256) k_cand_rows(Work w, int B, int R, const u
             };
             fetch_points(pa, tid);
             if (256 * kU < d.n) fetch_points(pb, tid + 256 * kU);
-            int rsum = 0, rmax = 0, pos = -1;   // wave 0: the SC2 row statistics of its claimed row
+            int pos = -1;   // wave 0: the lane's place among the claimed rows
             if (wv == 0) {
                 const int e = e0 + lane;
                 int i = -1;
@@ -283,9 +303,6 @@ __global__ void __launch_bounds__(256) k_cand_rows(Work w, int B, int R, const u
                 if (i >= 0) {
                     pos = __popcll(m & ((1ull << lane) - 1ull));
                     const int64_t gi = d.pt_off + i;
-                    const int32_t *rs = w.rowstat + ((int64_t)b * w.max_n + i) * 20;
-                    rsum = rs[1];
-                    rmax = rs[2];
                     row_l[pos] = i;
                     crd[pos][0] = w.src[3 * gi]; crd[pos][1] = w.src[3 * gi + 1]; crd[pos][2] = w.src[3 * gi + 2];
                     crd[pos][3] = w.dst[3 * gi]; crd[pos][4] = w.dst[3 * gi + 1]; crd[pos][5] = w.dst[3 * gi + 2];
@@ -295,6 +312,8 @@ __global__ void __launch_bounds__(256) k_cand_rows(Work w, int B, int R, const u
             __syncthreads();
             const int cnt = cnt_l;
             if (cnt > 0) {   // the same for the whole workgroup
+                int rsum = 0, rmax = 0;   // wave r: the lane's parts of claimed row r's SC2 statistics
+                if (wv < cnt) sc2_row_parts(w, d, __builtin_amdgcn_readfirstlane(row_l[wv]), lane, 64, rsum, rmax);
                 uint32_t cw[kCandRows][4];   // 16 bins, 8 bits each (at most ceil(32767/256) per thread)
                 int deg[kCandRows];
 #pragma unroll
@@ -367,9 +386,14 @@ __global__ void __launch_bounds__(256) k_cand_rows(Work w, int B, int R, const u
                     const int td = wave_total(deg[r]);
                     if (lane == 0) red[wv][r][8] = td;
                 }
-                if (pos >= 0) {
-                    rsv_l[pos][0] = rsum;
-                    rsv_l[pos][1] = rmax;
+                if (wv < cnt) {
+                    rsum = wave_total(rsum);
+#pragma unroll
+                    for (int o = 32; o > 0; o >>= 1) rmax = max(rmax, __shfl_xor(rmax, o, 64));
+                    if (lane == 0) {
+                        rsv_l[wv][0] = rsum;
+                        rsv_l[wv][1] = rmax;
+                    }
                 }
                 __syncthreads();
 #pragma unroll 1

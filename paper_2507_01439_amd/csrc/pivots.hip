@@ -427,12 +427,12 @@ __global__ void __launch_bounds__(256) k_rowscan(Work w)
         int nh = 0;   // the wave's segments that reach alpha: row | segment << 6 in `list`
         if (s0 < nseg && s0 + segs > rb) {   // segments left of the rows' own hold no pair
             const int i = !collect_shared(d.n) || lane >> 4 == wv ? 64 * rb + lane : d.n;   // n: not this wave's row
-            const uint16_t *sm = w.segmax + d.g_off / 64 + i;
+            const uint16_t *sm = w.segmax + d.g_off / 64 + part_at(64 * rb + lane, 0, d.npad / 64);
             int m[16];
 #pragma unroll
             for (int t = 0; t < 16; ++t) {
                 const int s = s0 + t;
-                m[t] = t < segs && s >= rb && s < nseg && i < d.n ? (int)sm[(int64_t)s * d.npad] : -1;
+                m[t] = t < segs && s >= rb && s < nseg && i < d.n ? (int)sm[32 * s] : -1;
             }
 #pragma unroll
             for (int t = 0; t < 16; ++t) {
@@ -493,8 +493,8 @@ __global__ void __launch_bounds__(256) k_rowscan(Work w)
         const int i = blk * kRowsPerItem + wv;
         bool live = i < d.n && alpha <= 0;
         if (i < d.n && alpha > 0) {   // some segment reaches alpha
-            const uint16_t *sm = w.segmax + d.g_off / 64 + i;
-            for (int s = (i >> 6) + lane; s < (d.n + 63) / 64; s += 64) live |= (int)sm[(int64_t)s * d.npad] >= alpha;
+            const uint16_t *sm = w.segmax + d.g_off / 64 + part_at(i, 0, d.npad / 64);
+            for (int s = (i >> 6) + lane; s < (d.n + 63) / 64; s += 64) live |= (int)sm[32 * s] >= alpha;
             live = __any(live);
         }
         const uint16_t *row = w.G + d.g_off + (int64_t)i * d.npad;

@@ -57,7 +57,8 @@ struct tr_handle {
     int32_t tick_stride = 0, rec_stride = 0;
     int32_t *pivots_plain = nullptr, *pivots = nullptr, *cliques = nullptr, *inl = nullptr;
     float *poses = nullptr, *gscore = nullptr;
-    int32_t *rowstat = nullptr, *mark = nullptr;
+    int32_t *rowstat = nullptr, *rowsum = nullptr, *colsum = nullptr, *mark = nullptr;
+    uint16_t *colmax = nullptr;
     uint16_t *feat = nullptr;
     float *scores = nullptr;
     tr_result *scratch_out = nullptr;   // results of feature-only passes
@@ -171,6 +172,9 @@ void workspace_layout(tr_handle *h, Get &&get)
     get(h->inl, B * h->h_cap);
     get(h->gscore, B * h->h_cap);
     get(h->rowstat, B * max_n * 20);
+    get(h->rowsum, B * nn / 64);
+    get(h->colsum, B * nn / 128);
+    get(h->colmax, B * nn / 128);
     get(h->mark, B * max_n);
     get(h->feat, B * max_n * 19);
     get(h->scores, B * max_n);
@@ -259,6 +263,9 @@ Work make_work(tr_handle *h, const float *src, const float *dst, const tr_params
     w.metric = (p.flags & TR_FLAG_RANK_MAE) ? 1 : (p.flags & TR_FLAG_RANK_MSE) ? 2 : 0;
     w.h_cap = h->h_cap;
     w.rowstat = h->rowstat;
+    w.rowsum = h->rowsum;
+    w.colsum = h->colsum;
+    w.colmax = h->colmax;
     w.mark = h->mark;
     w.feat_all = 0;
     w.feat = h->feat;
