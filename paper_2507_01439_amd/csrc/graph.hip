@@ -628,7 +628,8 @@ constexpr float kAccBias = 8388608.0f;         // 2^23: a count v < 2^16 is then
 // What the epilogue leaves besides the weights: the histogram and segment maxima the pivots need, the
 // row sums and maxima the learned features need, or both (a learned registration).
 enum Sc2Mode { kSc2Plain = 0, kSc2Learned = 1, kSc2Features = 2 };
-constexpr int kSc2PerCu = 3;                   // workgroups resident per CU (registers: 168 per lane)
+constexpr int kSc2PerCu = 3;                   // workgroups resident per CU (registers: 168 per lane; a learned tile's
+                                               // LDS allows two; 64 feature pairs take 615 us, 650 at two)
 
 // Maximum over each half of the wave (lanes 0-31, 32-63), left in lanes 31 and 63: prefix
 // steps inside each 16-lane DPP row, then the last lane of rows 0 and 2 joins rows 1 and 3.
@@ -910,7 +911,7 @@ __device__ __forceinline__ void sc2_range(const Work &w, int &start, int &end)
 // Dense product of every tile: a work item is one 128 x 128 quadrant of a list tile (quadrants below
 // the diagonal or past n are skipped).
 template <int MODE>
-__global__ void __launch_bounds__(256, MODE == kSc2Plain ? kSc2PerCu : 2) k_sc2(Work w)
+__global__ void __launch_bounds__(256, MODE == kSc2Learned ? 2 : kSc2PerCu) k_sc2(Work w)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     int32_t *hist = reinterpret_cast<int32_t *>(smem), *tmax = hist + kHistWords - 2;   // zero outside the epilogue
@@ -1347,7 +1348,7 @@ hipError_t launch_sc2(const Work &w, int64_t items, int num_cus, hipStream_t s)
 {
     const int mode = !w.learned ? kSc2Plain : w.feat_all ? kSc2Features : kSc2Learned;
     const int cus = std::max(1, num_cus / 8);
-    const int grid = (int)(8 * std::min<int64_t>(4 * ((items + 7) / 8), cus * (mode == kSc2Plain ? kSc2PerCu : 2)));
+    const int grid = (int)(8 * std::min<int64_t>(4 * ((items + 7) / 8), cus * (mode == kSc2Learned ? 2 : kSc2PerCu)));
     if (mode == kSc2Plain) hipLaunchKernelGGL(k_sc2<kSc2Plain>, dim3(grid), dim3(256), sc2_lds(kSc2Plain), s, w);
     else if (mode == kSc2Learned) hipLaunchKernelGGL(k_sc2<kSc2Learned>, dim3(grid), dim3(256), sc2_lds(kSc2Learned), s, w);
     else hipLaunchKernelGGL(k_sc2<kSc2Features>, dim3(grid), dim3(256), sc2_lds(kSc2Features), s, w);
