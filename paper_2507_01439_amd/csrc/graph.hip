@@ -885,7 +885,11 @@ __device__ __forceinline__ void sc2_dense_tile(const Work &w, const PairDesc &d,
         if (lane == 31) atomicMax(tmax, wmax);
     }
     __syncthreads();   // T, the histogram and the tile's maximum are complete
-    if (MODE != kSc2Features) hist_flush(hist, gh, min(*tmax, kHistLdsBins));
+    if (MODE != kSc2Features) {
+        const int top = *tmax;   // the pair's largest weight stands in bin 0 of the copies
+        if (threadIdx.x == 0 && top > 0) atomicMax(&gh[0], top);
+        hist_flush(hist, gh, min(top, kHistLdsBins));
+    }
     if (MODE != kSc2Plain) {
         const int64_t at = d.g_off / 128 + part_at(bj * kOut, bi, d.npad / kOut);
         column_stats<kOut, kOut>(T, kOutPitch, reinterpret_cast<int32_t *>(T), w.colsum + at, w.colmax + at, d.npad / kOut * 32);
@@ -1256,7 +1260,11 @@ __global__ void __launch_bounds__(kSpThreads) k_sc2_sparse(Work w)
                 if (MODE != kSc2Plain) tile_stats(rsum[tid], csum[tid], cmax[tid], base > 0);
             }
             __syncthreads();
-            if (MODE != kSc2Features) hist_flush(hist, gh, min(*tmax, kHistLdsBins));
+            if (MODE != kSc2Features) {
+                const int top = *tmax;
+                if (tid == 0 && top > 0) atomicMax(&gh[0], top);
+                hist_flush(hist, gh, min(top, kHistLdsBins));
+            }
             __syncthreads();   // the LDS is the next pass's
         }
         if (all == 0) {

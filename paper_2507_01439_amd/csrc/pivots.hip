@@ -103,6 +103,8 @@ __device__ __forceinline__ void load8(const uint16_t *row, int c, int (&v)[8])
     }
 }
 
+constexpr int kMaxFirst = 2048;
+
 struct Threshold {
     int32_t alpha, c_gt, m_eq, fast, ncand;   // as in PairState
 };
@@ -117,10 +119,20 @@ __device__ Threshold pair_threshold(const Work &w, const PairDesc &d, int b, int
     const int64_t K = d.kpiv;
     const int tid = threadIdx.x;
     const int32_t *gh = w.ghist + (int64_t)b * kHistGroups * w.hist_stride;
+    // bin 0 of each copy holds the largest weight it saw: bins past that are empty. Worth its round trip where the
+    // copies take long to read (us:
+    // k_thresh at N = 20000 24.3 -> 7.5, the fused scan at N = 5000 11.2 -> 8.5, at 2749 9.5 -> 8.1; at 1000 7.6 -> 8.0)
+    int n = d.n;
+    if (n > kMaxFirst) {
+        int top = 0;
+#pragma unroll
+        for (int g = 0; g < kHistGroups; ++g) top = max(top, gh[(int64_t)g * w.hist_stride]);
+        n = min(n, top + 1);
+    }
     // eight consecutive bins per thread: two 16-byte loads from each copy, all issued before any is
-    // summed (the pass is latency-bound: 1024 threads take one round up to N = 8192); bins at or past n are
-    // never written and are not summed (the copies are padded to a multiple of 8)
-    for (int v0 = 8 * tid; v0 < d.n; v0 += 8 * NT) {
+    // summed (the pass is latency-bound: 1024 threads take one round up to 8192 bins); bins at or past n are
+    // empty or never written and are not summed (the copies are padded to a multiple of 8)
+    for (int v0 = 8 * tid; v0 < n; v0 += 8 * NT) {
         int4 c[kHistGroups][2];
 #pragma unroll
         for (int g = 0; g < kHistGroups; ++g) {
@@ -140,18 +152,18 @@ __device__ Threshold pair_threshold(const Work &w, const PairDesc &d, int b, int
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-            if (v0 + u < d.n) hs[v0 + u] = sum[u];
+            if (v0 + u < n) hs[v0 + u] = sum[u];
     }
     __syncthreads();
     // bins w = 1 .. n-1 walked from the top: thread t sums the contiguous positions u0 .. u1-1
     // (u = n-1-w); an in-wave scan and the wave totals give each thread the count above
     // its range, and the thread whose range holds the K-th largest weight walks it (counts stay
     // below n(n-1)/2 < 2^31)
-    const int nb = d.n - 1;
+    const int nb = max(n - 1, 0);
     const int cs = (nb + NT - 1) / NT;
     const int u0 = min(nb, tid * cs), u1 = min(nb, u0 + cs);
     int local = 0;
-    for (int u = u0; u < u1; ++u) local += hs[d.n - 1 - u];
+    for (int u = u0; u < u1; ++u) local += hs[n - 1 - u];
     const int incl = wave_incl_scan(local);
     if ((tid & 63) == 63) wtot[tid >> 6] = incl;
     __syncthreads();
@@ -172,7 +184,7 @@ __device__ Threshold pair_threshold(const Work &w, const PairDesc &d, int b, int
     if (K <= tot && excl < K && K <= excl + local) {
         int64_t cum = excl;
         for (int u = u0; u < u1; ++u) {
-            const int wt = d.n - 1 - u;
+            const int wt = n - 1 - u;
             const int64_t c = hs[wt];
             if (cum + c >= K) {
                 found(wt, cum, c);
@@ -300,8 +312,8 @@ constexpr int kCollectCap = 1024;   // keys a workgroup stages in LDS before its
 // FUSED (a single pair of few matches): every workgroup finds the threshold itself, from the same histograms, in
 // place of a kernel before this one; the first stores it, the last sums the pair's counts. No more workgroups than
 // CUs, as each reads all copies of the histogram. Both kernels / this one alone (us, without the gap between them):
-// N = 300 11.3 / 7.4, N = 1000 11.3 / 7.6, N = 2749 12.1 / 9.4, N = 5000 13.9 / 10.6; a call of 6500 matches
-// 125.4 / 122.3, of 8000 170.9 / 170.9.
+// N = 300 11.3 / 7.4, N = 1000 11.3 / 7.6, N = 2749 12.1 / 8.1, N = 5000 13.9 / 8.5; a call of 6500 matches
+// 125.4 / 122.3, of 8000 170.9 / 170.9 (both before the largest weight bounded the bins read).
 template <bool FUSED>
 __global__ void __launch_bounds__(256) k_rowscan(Work w)
 {
