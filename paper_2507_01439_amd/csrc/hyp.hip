@@ -614,7 +614,7 @@ __device__ __forceinline__ void store_agent(float *p, float v)
 // finishes a pair's last item (two levels of atomic tickets, no waiting)
 // selects the result.
 template <int KMAX, int METRIC, int NW>
-__global__ void __launch_bounds__(64 * NW) k_hyp(Work w, int B, int ppw)
+__global__ void __launch_bounds__(64 * NW, 2) k_hyp(Work w, int B, int ppw)
 {
     constexpr int NT = 64 * NW;
     static_assert(METRIC == 0 || NW == 4, "error-score sums keep the four-wave order of k_score_poses");
@@ -965,14 +965,20 @@ hipError_t launch_hyp(const Work &w, int B, int ppw, int grid, int num_cus, hipS
     const int total = B * ((w.k1 + ppw - 1) / ppw);
     grid = max(1, min(total, grid));
     const bool small = w.k2 <= 2;
-    // inlier-number ranking: eight waves per workgroup (two per SIMD) share the scoring; the
-    // error-based rankings keep four, the summation order tr_score_poses reproduces
+    // inlier-number ranking: eight waves per workgroup (two per SIMD) share the scoring of a short list's items; in
+    // a long one two workgroups of four per CU overlap one's search and fits with the other's scoring. Eight /
+    // four (us): N = 5000 (250 items) 25.1 / 27.8, N = 20000 (625) 113 / 116, 256 pairs 1267 / 1080, sixteen of
+    // N = 20000 1084 / 1015. The error-based rankings keep four, the summation order tr_score_poses reproduces
+    const bool many = total >= 4 * num_cus;
     if (w.metric == 1) {
         if (small) hipLaunchKernelGGL((k_hyp<2, 1, 4>), dim3(grid), dim3(256), 0, s, w, B, ppw);
         else hipLaunchKernelGGL((k_hyp<TR_MAX_K2, 1, 4>), dim3(grid), dim3(256), 0, s, w, B, ppw);
     } else if (w.metric == 2) {
         if (small) hipLaunchKernelGGL((k_hyp<2, 2, 4>), dim3(grid), dim3(256), 0, s, w, B, ppw);
         else hipLaunchKernelGGL((k_hyp<TR_MAX_K2, 2, 4>), dim3(grid), dim3(256), 0, s, w, B, ppw);
+    } else if (many) {
+        if (small) hipLaunchKernelGGL((k_hyp<2, 0, 4>), dim3(grid), dim3(256), 0, s, w, B, ppw);
+        else hipLaunchKernelGGL((k_hyp<TR_MAX_K2, 0, 4>), dim3(grid), dim3(256), 0, s, w, B, ppw);
     } else {
         if (small) hipLaunchKernelGGL((k_hyp<2, 0, 8>), dim3(grid), dim3(512), 0, s, w, B, ppw);
         else hipLaunchKernelGGL((k_hyp<TR_MAX_K2, 0, 8>), dim3(grid), dim3(512), 0, s, w, B, ppw);
