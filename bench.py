@@ -28,7 +28,7 @@ sys.path.insert(0, ROOT)
 METRIC = "registrations/s @N=5k; learned vs plain pivots at equal success rate"
 PEAK_FP4_TFLOPS = 10100.0   # MI355X dense FP4 MFMA, TFLOP/s (the SC2 product runs on FP4 operands)
 PEAK_VALU_TOPS = 256 * 64 * 2.4e9 / 1e12   # unpacked float32 vector issue, lane slots / s
-COMPAT_SLOTS_PER_PAIR = 22.0   # minimum vector issue slots of one compatibility evaluation
+COMPAT_SLOTS_PER_PAIR = 18.0   # minimum vector issue slots of one compatibility evaluation
 PEAK_HBM_GBS = 8000.0       # MI355X HBM3E, GB/s
 WEIGHTS = os.path.join(ROOT, "paper_2507_01439_amd", "weights", "scorer_indoor.bin")
 PEAK_FP32_TFLOPS = 157.3    # MI355X float32 rate, vector and MFMA alike (the scorer's training kernels use both)
@@ -322,10 +322,10 @@ def main():
             "mfma_busy_fraction": load_counters(f"k_sc2_{args.workload}_traffic.txt")[1],
             "avg_launch_us": sc2_ms * 1000.0, "algorithmic_ops_per_launch": sc2_ops}
     roof["frac"] = roof["achieved"] / roof["peak"]
-    # k_compat is bound by vector ALU issue: per pair evaluation at least two square roots
-    # (quarter rate, 4 issue slots each), six coordinate differences, two squared norms
-    # (multiply + two fused multiply-adds each), the length difference and the comparison:
-    # 22 lane slots. Peak: 256 CUs x 64 lanes x 2.4 GHz unpacked float32 issue.
+    # k_compat is bound by vector ALU issue: per pair evaluation six coordinate differences, two
+    # squared norms (multiply + two fused multiply-adds each), their sum and difference, two fused
+    # multiply-adds, the guard's comparison and the decision's bit: 18 lane slots. Peak: 256 CUs x
+    # 64 lanes x 2.4 GHz unpacked float32 issue.
     compat_pairs = float(sum(n * (n - 1) / 2.0 for n in ns_all))
     compat_tops = compat_pairs * COMPAT_SLOTS_PER_PAIR / (stages["compat"] * 1e-3) / 1e12
     line = {
