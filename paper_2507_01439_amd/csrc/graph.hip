@@ -974,8 +974,8 @@ __global__ void __launch_bounds__(256, MODE == kSc2Learned ? 2 : kSc2PerCu) k_sc
 // them). Measured at 1.3 % edges: N = 20000 375 us where k_sc2 takes 1230, sixteen such pairs 4.6 ms (18.7 ms with
 // 256 x 256 tiles, edges in 64-byte pieces and a tile staged in LDS for the store). Software-pipelined reads with
 // a barrier per two blocks: 395; all sixteen waves feeding, zeroing and counting: 392; a read of row i per edge
-// where it changes instead of runs: 618 (16 edges a thread); one lane order by bank class: three to ten
-// percent fewer conflicts for as much work before.
+// where it changes instead of runs: 618 (16 edges a thread). Ordering a row's edges by bank class would meet 3 to
+// 10 % fewer conflicts, an order that knows the other lanes' 24 %, for about the time it saves.
 constexpr int kSpThreads = 1024, kSpWaves = kSpThreads / 64;
 constexpr int kSpCount = 14 * 64;                  // threads of the counting waves
 constexpr int kRuns = 5;                           // runs per counting thread: four edges of one row each
@@ -1080,7 +1080,10 @@ __global__ void __launch_bounds__(kSpThreads) k_sc2_sparse(Work w)
         next = __builtin_amdgcn_readfirstlane(scan[2 * kSpWaves]);
         all = __builtin_amdgcn_readfirstlane(all);
         edges = __builtin_amdgcn_readfirstlane(edges);
-        const bool take = edges <= w.sp_limit;
+        // (counted against the whole square, the half tiles on the diagonal and the narrow last ones of pairs too dense
+        // for this kernel came here, up to two passes of 20 CUs alone: 1738 us a call at N = 20000, 5.3 %; 1389 now)
+        const int entries = min(S, n - i0) * min(S, n - j0) / (diag ? 2 : 1);   // the last tiles are narrower
+        const bool take = edges <= (w.sp_limit > 0 ? w.sp_limit : entries / kSparseDensity);
         if (!take) {   // the same for the whole workgroup: the dense kernel's
             if (tid == 0) w.sp_list[2 + atomicAdd(&w.sp_list[0], 1)] = item;
             __syncthreads();

@@ -781,6 +781,9 @@ hipError_t setup_pivot_kernels()
     if (e == hipSuccess)
         e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_thresh), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 32768 * (int)sizeof(int32_t));
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_rowscan<true>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kFuseThreshMax * (int)sizeof(int32_t));
     return e;
 }
 

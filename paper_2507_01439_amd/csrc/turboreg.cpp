@@ -302,7 +302,7 @@ tr_status check_params(tr_handle *h, const tr_params *p)
 // tile on the matrix cores (us): N = 5000 116 / 103 at 0.7 to 2.7 % edges; N = 8192 160 / 188 at 0.7 %,
 // 186 / 187 at 2.7 %, 205 / 186 at 3.8 %; N = 12000 245 / 418, 324 / 403 and 411 / 405; N = 20000 464 / 1385,
 // 862 / 1398 and 1069 / 1402, 1370 / 1404 at 5.3 %.
-constexpr int32_t kSparseMinN = 8192, kSparseDensity = 32;
+constexpr int32_t kSparseMinN = 8192;
 
 // The launch sequence for B pairs (offsets on the device) or one pair (n_single).
 // features_only stops after the learned features.
@@ -321,7 +321,7 @@ tr_status enqueue(tr_handle *h, const Work &w_in, const int32_t *offsets, int32_
     if (sparse) {
         const int64_t area = (int64_t)w.sp_tile * w.sp_tile;
         w.sp_list = h->sp_list;
-        w.sp_limit = (int32_t)(cfg.sc2_sparse_cap > 0 ? cfg.sc2_sparse_cap * area / (256 * 256) : area / kSparseDensity);
+        w.sp_limit = (int32_t)(cfg.sc2_sparse_cap * area / (256 * 256));
     }
     const bool profile = ev != nullptr;
     const int64_t npad = (max_n + kSc2Tile - 1) / kSc2Tile * kSc2Tile;
