@@ -623,13 +623,13 @@ constexpr int kHistLdsBins = 8126;
 constexpr int kHistWords = kHistLdsBins + 64 + 2;
 constexpr int kHistBytes = kHistWords * 4;
 constexpr int kOutPitch = kOut + 8;            // uint16 per LDS row of a tile staged for the column statistics
-constexpr int kOutBytes = kOut * kOutPitch * 2;
+constexpr int kOutBytes = kOut / 2 * kOutPitch * 2;   // half of its rows at a time
 constexpr float kAccBias = 8388608.0f;         // 2^23: a count v < 2^16 is then the low 16 bits of 2^23 + v
 // What the epilogue leaves besides the weights: the histogram and segment maxima the pivots need, the
 // row sums and maxima the learned features need, or both (a learned registration).
 enum Sc2Mode { kSc2Plain = 0, kSc2Learned = 1, kSc2Features = 2 };
-constexpr int kSc2PerCu = 3;                   // workgroups resident per CU (registers: 168 per lane; a learned tile's
-                                               // LDS allows two; 64 feature pairs take 615 us, 650 at two)
+constexpr int kSc2PerCu = 3;                   // workgroups resident per CU (registers: 168 per lane; two took 64 feature
+                                               // pairs from 615 to 650 us, learned N = 5000 from 34.9 to 38.5)
 
 // Maximum over each half of the wave (lanes 0-31, 32-63), left in lanes 31 and 63: prefix
 // steps inside each 16-lane DPP row, then the last lane of rows 0 and 2 joins rows 1 and 3.
@@ -665,23 +665,19 @@ __device__ __forceinline__ void lds_add(int32_t *hist, uint32_t k)
 }
 
 // Sums and maxima of the tile's columns (column j of the upper tile is row j of the lower one, the
-// SC2 matrix being symmetric), from the masked tile T[ROWS][pitch] in LDS: thread t takes columns 2c,
-// 2c+1 (c = t mod COLS/2) over rows of one residue class, sixteen 4-byte reads in flight; the classes
-// meet in xl (3 ints per column pair and class). csum, cmax: the tile's first column there, its groups
-// of 32 columns `stride` apart.
-template <int ROWS, int COLS>
-__device__ __forceinline__ void column_stats(const uint16_t *T, int pitch, int32_t *xl, int32_t *csum, uint16_t *cmax,
-                                             int stride)
-{
-    constexpr int kPairs = COLS / 2, kCls = 256 / kPairs;   // column pairs; row classes
-    const int cp = threadIdx.x % kPairs, cls = threadIdx.x / kPairs;
-    const uint32_t *Tw = reinterpret_cast<const uint32_t *>(T);
+// SC2 matrix being symmetric), from half of the masked tile's rows at a time in LDS: thread t takes columns 2c,
+// 2c+1 (c = t mod 64) over rows of one residue class (its wave), sixteen 4-byte reads in flight; the classes
+// meet in xl (3 ints per column pair and class), which may overlie the rows.
+struct ColumnStats {
     int s0 = 0, s1 = 0;
     u16x2 mx = {0, 0};
-    for (int m0 = 0; m0 < ROWS / kCls; m0 += 16) {
+
+    __device__ __forceinline__ void add(const uint16_t *T)   // after a barrier
+    {
+        const uint32_t *Tw = reinterpret_cast<const uint32_t *>(T) + (threadIdx.x >> 6) * (kOutPitch / 2) + (threadIdx.x & 63);
         uint32_t v[16];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) v[u] = Tw[(kCls * (m0 + u) + cls) * (pitch / 2) + cp];
+        for (int u = 0; u < 16; ++u) v[u] = Tw[4 * u * (kOutPitch / 2)];
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
             s0 += (int)(v[u] & 0xFFFFu);
@@ -689,27 +685,32 @@ __device__ __forceinline__ void column_stats(const uint16_t *T, int pitch, int32
             mx = __builtin_elementwise_max(mx, __builtin_bit_cast(u16x2, v[u]));
         }
     }
-    __syncthreads();   // the tile is read (xl may overlie it)
-    if (cls) {
-        int32_t *x = xl + 3 * ((cls - 1) * kPairs + cp);
-        x[0] = s0;
-        x[1] = s1;
-        x[2] = (int32_t)__builtin_bit_cast(uint32_t, mx);
-    }
-    __syncthreads();
-    if (!cls) {
-#pragma unroll
-        for (int c = 1; c < kCls; ++c) {
-            const int32_t *x = xl + 3 * ((c - 1) * kPairs + cp);
-            s0 += x[0];
-            s1 += x[1];
-            mx = __builtin_elementwise_max(mx, __builtin_bit_cast(u16x2, (uint32_t)x[2]));
+
+    // csum, cmax: the tile's first column there, its groups of 32 columns `stride` apart
+    __device__ __forceinline__ void store(int32_t *xl, int32_t *csum, uint16_t *cmax, int stride)   // after a barrier
+    {
+        const int cp = threadIdx.x & 63, cls = threadIdx.x >> 6;
+        if (cls) {
+            int32_t *x = xl + 3 * ((cls - 1) * 64 + cp);
+            x[0] = s0;
+            x[1] = s1;
+            x[2] = (int32_t)__builtin_bit_cast(uint32_t, mx);
         }
-        const int at = cp / 16 * stride + 2 * cp % 32;
-        *reinterpret_cast<int2 *>(csum + at) = make_int2(s0, s1);
-        *reinterpret_cast<uint32_t *>(cmax + at) = __builtin_bit_cast(uint32_t, mx);
+        __syncthreads();
+        if (!cls) {
+#pragma unroll
+            for (int c = 1; c < 4; ++c) {
+                const int32_t *x = xl + 3 * ((c - 1) * 64 + cp);
+                s0 += x[0];
+                s1 += x[1];
+                mx = __builtin_elementwise_max(mx, __builtin_bit_cast(u16x2, (uint32_t)x[2]));
+            }
+            const int at = cp / 16 * stride + 2 * cp % 32;
+            *reinterpret_cast<int2 *>(csum + at) = make_int2(s0, s1);
+            *reinterpret_cast<uint32_t *>(cmax + at) = __builtin_bit_cast(uint32_t, mx);
+        }
     }
-}
+};
 
 // One 128 x 128 output tile (bi <= bj in units of 128) of G[i][j] = C_ij sum_k C_ik C_jk, i < j < n,
 // by a workgroup of four waves in a 2 x 2 layout, each a 64 x 64 sub-tile of 2 x 2 blocks of
@@ -810,6 +811,7 @@ __device__ __forceinline__ void sc2_dense_tile(const Work &w, const PairDesc &d,
     const bool small_n = d.n <= kHistLdsBins + 1;
     const uint32_t spare = kHistLdsBins + lane;
     int wmax = 0;
+    ColumnStats cols;
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
         const int i = i0 + 32 * x + l31;
@@ -843,7 +845,7 @@ __device__ __forceinline__ void sc2_dense_tile(const Work &w, const PairDesc &d,
                 const int jc = j0 + 32 * y + 16 * q + 8 * lh;
                 *reinterpret_cast<uint4 *>(Gb + (int64_t)i * d.npad + jc) = make_uint4(o[0], o[1], o[2], o[3]);
                 if (MODE != kSc2Plain)
-                    *reinterpret_cast<uint4 *>(&T[(wm * 64 + 32 * x + l31) * kOutPitch + jc - bj * kOut]) =
+                    *reinterpret_cast<uint4 *>(&T[(32 * wm + l31) * kOutPitch + jc - bj * kOut]) =
                         make_uint4(o[0], o[1], o[2], o[3]);
                 if (MODE != kSc2Features) {
                     // no branch: a zero entry (v - 1 wraps) and one past the LDS bins count in the lane's
@@ -879,6 +881,11 @@ __device__ __forceinline__ void sc2_dense_tile(const Work &w, const PairDesc &d,
             w.segmax[at] = (uint16_t)m;
             if (MODE != kSc2Plain) w.rowsum[at] = rs;
         }
+        if (MODE != kSc2Plain) {
+            __syncthreads();   // this half of the rows is in T
+            cols.add(T);
+            __syncthreads();   // T is the other half's, or the classes'
+        }
     }
     if (MODE != kSc2Features) {
         wmax = half_max(wmax);   // both halves of the wave hold the same rows
@@ -892,7 +899,7 @@ __device__ __forceinline__ void sc2_dense_tile(const Work &w, const PairDesc &d,
     }
     if (MODE != kSc2Plain) {
         const int64_t at = d.g_off / 128 + part_at(bj * kOut, bi, d.npad / kOut);
-        column_stats<kOut, kOut>(T, kOutPitch, reinterpret_cast<int32_t *>(T), w.colsum + at, w.colmax + at, d.npad / kOut * 32);
+        cols.store(reinterpret_cast<int32_t *>(T), w.colsum + at, w.colmax + at, d.npad / kOut * 32);
     }
 }
 
@@ -915,7 +922,7 @@ __device__ __forceinline__ void sc2_range(const Work &w, int &start, int &end)
 // Dense product of every tile: a work item is one 128 x 128 quadrant of a list tile (quadrants below
 // the diagonal or past n are skipped).
 template <int MODE>
-__global__ void __launch_bounds__(256, MODE == kSc2Learned ? 2 : kSc2PerCu) k_sc2(Work w)
+__global__ void __launch_bounds__(256, kSc2PerCu) k_sc2(Work w)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     int32_t *hist = reinterpret_cast<int32_t *>(smem), *tmax = hist + kHistWords - 2;   // zero outside the epilogue
@@ -1359,7 +1366,7 @@ hipError_t launch_sc2(const Work &w, int64_t items, int num_cus, hipStream_t s)
 {
     const int mode = !w.learned ? kSc2Plain : w.feat_all ? kSc2Features : kSc2Learned;
     const int cus = std::max(1, num_cus / 8);
-    const int grid = (int)(8 * std::min<int64_t>(4 * ((items + 7) / 8), cus * (mode == kSc2Learned ? 2 : kSc2PerCu)));
+    const int grid = (int)(8 * std::min<int64_t>(4 * ((items + 7) / 8), cus * kSc2PerCu));
     if (mode == kSc2Plain) hipLaunchKernelGGL(k_sc2<kSc2Plain>, dim3(grid), dim3(256), sc2_lds(kSc2Plain), s, w);
     else if (mode == kSc2Learned) hipLaunchKernelGGL(k_sc2<kSc2Learned>, dim3(grid), dim3(256), sc2_lds(kSc2Learned), s, w);
     else hipLaunchKernelGGL(k_sc2<kSc2Features>, dim3(grid), dim3(256), sc2_lds(kSc2Features), s, w);
