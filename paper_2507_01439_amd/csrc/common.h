@@ -216,6 +216,14 @@ __host__ __device__ inline int32_t part_at(int32_t x, int32_t k, int32_t parts)
     return ((x >> 5) * parts + k) * 32 + (x & 31);
 }
 
+// Byte offset, from a lane's piece of the first two 128-column blocks of C, of step s of the dense SC2 product
+// (two blocks, 2 x kbs bytes, a step; ns steps). The loop asks for up to two steps past the last: these read the
+// last one's blocks again (unused), so that no load leaves the pair's bits.
+__host__ __device__ inline int32_t sc2_step_offset(int32_t s, int32_t ns, uint32_t kbs)
+{
+    return (s < ns ? s : ns - 1) * (int32_t)(2 * kbs);
+}
+
 // Segments (64 columns) of 64 rows that a wave of the row scan takes: sixteen, whose maxima it reads at once; one
 // in small pairs, which would fill few waves. Up to 512 matches the four waves of a workgroup share one segment by
 // rows (n = 300: 5.9 us, 6.2 apart); beyond, the workgroups' atomics cost more than that saves (n = 1000: 8.4 us,

@@ -761,9 +761,9 @@ __device__ __forceinline__ void sc2_dense_tile(const Work &w, const PairDesc &d,
         for (int y = 0; y < 2; ++y)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[x][y][r] = kAccBias;
-    // (buffer loads: the step is a scalar offset, and steps past the last read zeros)
+    // (buffer loads: the step is a scalar offset)
     auto load = [&](int s, v4u (&fj)[2], v4u (&fi)[2]) {
-        const int so = s * (int)(2 * kbs);
+        const int so = sc2_step_offset(s, ns, kbs);
 #pragma unroll
         for (int y = 0; y < 2; ++y) {
             fj[y] = __builtin_amdgcn_raw_buffer_load_b128(rows, oj + y * 512, so, 0);
