@@ -335,12 +335,14 @@ __device__ __forceinline__ uint32_t transpose32(uint32_t x, int lane)
 // |sqrt a - sqrt b| <= tau is for s >= tau^2 the sign of E = d^2 - 2 tau^2 s + tau^4 =
 // (delta^2 - tau^2)(L^2 - tau^2): no square root, and the sign bit shifts straight into the lane's word
 // (20 issue slots a pair; 26 with two hardware square roots). A guard makes every decision the exact one
-// (length32, correctly rounded roots). a and b carry 5 x 2^-24 relative, so E near delta = tau is off by
-// at most 12 x 2^-24 tau L s; the exact evaluation's own rounding moves delta by 3 x 2^-24 L, as much again
-// in E; the boundary report counts |delta - tau| < 1e-6, 4.4e-6 tau s in E. A row holding a pair with
-// |E| <= tau s (2^-18 L + 5e-6) + 2.1 tau^4 (L <= s / L0 + L0 / 2 for any L0; the last term covers the pairs
-// with s near or below tau^2, where E's sign says nothing) is evaluated exactly. Items with a non-finite or
-// huge point (beyond 1e8), and thresholds outside [1e-9, 1e8], are evaluated exactly throughout.
+// (length32, correctly rounded roots). Both sides take the same float a and b; the exact evaluation's roots and
+// difference move delta by at most e = 2^-23 L, so E at its decision is at most e (2 tau + e)(L^2 - tau^2) off zero:
+// 2^-21 tau L s, and 2^-44 s^2 where rounding alone exceeds tau (scenes 10^8 times larger and more). E's own
+// rounding is 2^-22 of these terms and of tau^2 s; the boundary report counts |delta - tau| < 1e-6, 4e-6 tau s in E.
+// A row holding a pair with |E| <= tau s (2^-18 L + 5e-6) + 2^-42 s^2 + 2.1 tau^4 is evaluated exactly (L^2 <= 2 s,
+// L <= s / L0 + L0 / 2 for any L0; the last term covers the pairs with s near or below tau^2, where E's sign says
+// nothing). Items with a non-finite or huge point (beyond 1e8), and thresholds outside [1e-9, 1e8], are evaluated
+// exactly throughout.
 //
 // Counts (edges, boundary pairs, non-finite input; the last by diagonal items) go to the item's slot. The
 // diagonal items clear the pair's weight histograms for their rows, and with learned pivots
@@ -415,7 +417,7 @@ __global__ void __launch_bounds__(256) k_compat(Work w)
             // L0: the largest |x_i - x_j| of one row, so that L0 is near the L of most pairs
             const float lx = a1.x - x[0].x, ly = a1.y - x[0].y, lz = a1.z - x[0].z;
             const float L0 = fmaxf(2.0f * __builtin_amdgcn_sqrtf(wave_fmax(wild ? 0.0f : lx * lx + ly * ly + lz * lz)), 16.0f * tau);
-            const float g1 = tau * 0x1p-18f / L0, g0 = tau * __builtin_fmaf(L0, 0x1p-19f, 5e-6f);
+            const float g1 = __builtin_fmaf(tau, 0x1p-18f / L0, 0x1p-42f), g0 = tau * __builtin_fmaf(L0, 0x1p-19f, 5e-6f);
             uint64_t self[2] = {0, 0};   // diagonal tile: the lane holding row 0's own match
             if (diag) self[rof >> 6] = 1ull << (rof & 63);
             uint32_t col[2] = {0, 0};    // bit r: pair (i0 + r, j)
