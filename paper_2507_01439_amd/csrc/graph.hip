@@ -338,11 +338,12 @@ __device__ __forceinline__ uint32_t transpose32(uint32_t x, int lane)
 // (length32, correctly rounded roots). Both sides take the same float a and b; the exact evaluation's roots and
 // difference move delta by at most e = 2^-23 L, so E at its decision is at most e (2 tau + e)(L^2 - tau^2) off zero:
 // 2^-21 tau L s, and 2^-44 s^2 where rounding alone exceeds tau (scenes 10^8 times larger and more). E's own
-// rounding is 2^-22 of these terms and of tau^2 s; the boundary report counts |delta - tau| < 1e-6, 4e-6 tau s in E.
-// A row holding a pair with |E| <= tau s (2^-18 L + 5e-6) + 2^-42 s^2 + 2.1 tau^4 is evaluated exactly (L^2 <= 2 s,
-// L <= s / L0 + L0 / 2 for any L0; the last term covers the pairs with s near or below tau^2, where E's sign says
-// nothing). Items with a non-finite or huge point (beyond 1e8), and thresholds outside [1e-9, 1e8], are evaluated
-// exactly throughout.
+// rounding is 2^-22 of these terms and of tau^2 s. The boundary report counts |delta - tau| < 1e-6: with e + 1e-6
+// for e, 4e-6 tau s and 4e-12 s more in E (the second where tau is below 1e-6 or so).
+// A row holding a pair with |E| <= tau s (2^-18 L + 5e-6) + 5e-12 s + 2^-42 s^2 + 2.1 tau^4 is evaluated exactly
+// (L^2 <= 2 s, L <= s / L0 + L0 / 2 for any L0; the last term covers the pairs with s near or below tau^2, where E's
+// sign says nothing). Items with a non-finite or huge point (beyond 1e8), and thresholds outside [1e-9, 1e8], are
+// evaluated exactly throughout.
 //
 // Counts (edges, boundary pairs, non-finite input; the last by diagonal items) go to the item's slot. The
 // diagonal items clear the pair's weight histograms for their rows, and with learned pivots
@@ -417,7 +418,8 @@ __global__ void __launch_bounds__(256) k_compat(Work w)
             // L0: the largest |x_i - x_j| of one row, so that L0 is near the L of most pairs
             const float lx = a1.x - x[0].x, ly = a1.y - x[0].y, lz = a1.z - x[0].z;
             const float L0 = fmaxf(2.0f * __builtin_amdgcn_sqrtf(wave_fmax(wild ? 0.0f : lx * lx + ly * ly + lz * lz)), 16.0f * tau);
-            const float g1 = __builtin_fmaf(tau, 0x1p-18f / L0, 0x1p-42f), g0 = tau * __builtin_fmaf(L0, 0x1p-19f, 5e-6f);
+            const float g1 = __builtin_fmaf(tau, 0x1p-18f / L0, 0x1p-42f);
+            const float g0 = __builtin_fmaf(tau, __builtin_fmaf(L0, 0x1p-19f, 5e-6f), 5e-12f);
             uint64_t self[2] = {0, 0};   // diagonal tile: the lane holding row 0's own match
             if (diag) self[rof >> 6] = 1ull << (rof & 63);
             uint32_t col[2] = {0, 0};    // bit r: pair (i0 + r, j)
