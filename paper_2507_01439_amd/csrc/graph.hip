@@ -599,13 +599,16 @@ __global__ void __launch_bounds__(64 * kFeatWaves) k_compat_features(Work w)
             *reinterpret_cast<uint2 *>(Cb + (uint32_t)(blk >> 1) * kbs + 8 * (blk & 1)) = make_uint2(word[0], word[1]);
         }
         atomicAdd(&deg[lane], degree);
+        // the match itself was counted as any other: out of its bin again (delta 0: the last where the bins have no width;
+        // the first also if it is not finite)
+        const float self = (x.x - x.x) + (x.y - x.y) + (x.z - x.z) + (y.x - y.x) + (y.y - y.y) + (y.z - y.z);   // 0 or NaN
+        if (wv == 0) atomicAdd(&hist[self >= q ? 15 : 0][lane], -1);
         __syncthreads();
-        // slots: 0 degree, 1 and 2 the SC2 sum and maximum (added by the next kernel), 3 .. 18 the histogram (bin 0
-        // without the match itself)
+        // slots: 0 degree, 1 and 2 the SC2 sum and maximum (added by the next kernel), 3 .. 18 the histogram
         int32_t *rs = w.rowstat + ((int64_t)b * w.max_n + i0) * 20;
         for (int k = tid; k < 64 * 20 && i0 + k / 20 < n; k += 64 * kFeatWaves) {
             const int r = k / 20, f = k % 20;
-            rs[k] = f == 0 ? deg[r] : f < 3 || f == 19 ? 0 : hist[f - 3][r] - (f == 3);
+            rs[k] = f == 0 ? deg[r] : f < 3 || f == 19 ? 0 : hist[f - 3][r];
         }
         __syncthreads();   // hist and deg are the next item's
     }
