@@ -487,13 +487,15 @@ typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 
 // GELU and its derivative with one exponential and one reciprocal: with u = c (x + 0.044715 x^3),
 // (1 + tanh u) / 2 = sigma(2u) = s, so gelu = x s and gelu' = s + x s (1 - s) 2 u'. No cancellation for
-// negative x (1 + tanh u loses its digits there); the tanh form's call is some forty instructions.
+// negative x (1 + tanh u loses its digits there); the tanh form's call is some forty instructions. Far to the left
+// 1 + exp(-2u) is infinite and s is 0 whatever the size of x (the Newton step alone works on a bounded one).
 __device__ __forceinline__ void gelu_both(float x, float &a, float &g)
 {
     constexpr float kL = -2.0f * kGeluC * 1.4426950408889634f;   // exp(-2u) = 2^(kL (x + 0.044715 x^3))
     const float x2 = x * x;
-    const float p = 1.0f + __builtin_amdgcn_exp2f(fminf(x * __builtin_fmaf(0.044715f * kL, x2, kL), 126.0f));
-    const float s0 = __builtin_amdgcn_rcpf(p), s = __builtin_fmaf(__builtin_fmaf(-p, s0, 1.0f), s0, s0);   // one Newton step
+    const float p = 1.0f + __builtin_amdgcn_exp2f(x * __builtin_fmaf(0.044715f * kL, x2, kL));
+    const float s0 = __builtin_amdgcn_rcpf(p);
+    const float s = __builtin_fmaf(__builtin_fmaf(-fminf(p, 0x1p126f), s0, 1.0f), s0, s0);   // one Newton step
     a = x * s;
     g = __builtin_fmaf(__builtin_fmaf(-a, s, a), __builtin_fmaf(6.0f * 0.044715f * kGeluC, x2, 2.0f * kGeluC), s);
 }
