@@ -163,9 +163,10 @@ tr_status tr_score_poses(tr_handle *h, const float *src, const float *dst, int32
  * Calls are grouped by shape: the number of 256-row tiles of their largest
  * pair, round_up(max_n, 256) / 256, and the batch size B (1 for tr_register).
  * Each group has a launch configuration; a group never tuned or set uses the
- * defaults (5, 8, 4 for one pair or 16 for a batch, 4, 0). No configuration
- * changes any result: C, weights, pivots, cliques, poses, inlier numbers and
- * the selection are the same under every valid configuration. */
+ * defaults (5, 8, 4 for one pair or 16 for a batch, 4, and 0 up to 8192
+ * matches or 2048 beyond). No configuration changes any result: C, weights,
+ * pivots, cliques, poses, inlier numbers and the selection are the same under
+ * every valid configuration. */
 typedef struct {
     int32_t sc2_super;      /* SC2 tile walk: side of the super-tiles (in 256 x 256
                                output tiles) whose tiles run close together, 1..16  */
@@ -175,9 +176,8 @@ typedef struct {
     int32_t hyp_per_cu;     /* hypothesis workgroups launched per CU, 1..16        */
     int32_t sc2_sparse_cap; /* SC2 output tiles with at most this many edges per
                                256 x 256 entries count common neighbours per edge
-                               from bit rows instead of the dense product; 0 = the
-                               library's rule (tiles of few edges, in calls of pairs
-                               beyond 8192 matches). 0..TR_SC2_SPARSE_CAP_MAX    */
+                               from bit rows instead of the dense product; 0 = every
+                               tile takes the product. 0..TR_SC2_SPARSE_CAP_MAX  */
 } tr_tuning;
 
 /* Configuration of the group of (max_n, B). TR_ERR_INVALID_ARG for max_n < 3, B < 1. */

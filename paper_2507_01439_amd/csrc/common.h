@@ -11,7 +11,6 @@ constexpr int kSc2Tile = 256;     // SC2 work-list tile edge (four 128 x 128 out
 constexpr int kHistGroups = 8;    // SC2 tiles add their weight histograms into this many copies per pair
 constexpr int kCompatTile = 128;  // tile edge of the compatibility list
 constexpr int kCompatMinRows = 8; // fewest rows of a tile one work item takes (Work::compat_rows)
-constexpr int kSparseDensity = 32;   // the bit-count kernel takes tiles of at most one edge in so many entries
 constexpr int kRowsPerItem = 4;   // rows per work item of the pivot scans (one per wave)
 constexpr int kPrepRows = 256;    // rows per work item of the prep / feature kernels
 constexpr int kRankSortMax = 4096; // candidate lists up to this size are ordered by a rank sort
@@ -78,7 +77,7 @@ struct Work {
     int32_t graph;
     int32_t sc2_super;        // SC2 tile walk: super-tile side in output tiles (launch configuration)
     int32_t sp_tile;          // tile edge of the SC2 bit-count kernel
-    int32_t sp_limit;         // most edges of a tile it takes; 0: 1 / kSparseDensity of its entries
+    int32_t sp_cap;           // it takes tiles of at most so many edges per 256 x 256 entries (launch configuration)
     int32_t *sp_list;         // the tiles it left to the dense kernel: their number, its next tile, its list
                               // items; null where it is not launched
     float tau, theta;

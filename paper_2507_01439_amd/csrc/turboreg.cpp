@@ -188,6 +188,12 @@ std::pair<int32_t, int32_t> tuning_key(int32_t max_n, int32_t B)
     return {(max_n + kSc2Tile - 1) / kSc2Tile, B};
 }
 
+// Bit counts by default: in groups of pairs beyond kSparseMinN matches, for tiles whose edges are at most one in 32
+// entries. Whole calls with every tile counted / every tile on the matrix cores (us): N = 5000 116 / 103 at 0.7 to
+// 2.7 % edges; N = 8192 160 / 188 at 0.7 %, 186 / 187 at 2.7 %, 205 / 186 at 3.8 %; N = 12000 245 / 418, 324 / 403
+// and 411 / 405; N = 20000 464 / 1385, 862 / 1398 and 1069 / 1402, 1370 / 1404 at 5.3 %.
+constexpr int32_t kSparseMinN = 8192, kSparseCap = 256 * 256 / 32;
+
 tr_tuning tuning_for(const tr_handle *h, int32_t max_n, int32_t B)
 {
     auto it = h->tuning.find(tuning_key(max_n, B));
@@ -197,7 +203,7 @@ tr_tuning tuning_for(const tr_handle *h, int32_t max_n, int32_t B)
     t.compat_per_cu = 8;   // twice the workgroups a CU holds: late ones fill the slots that free first
     t.hyp_ppw = B == 1 ? 4 : 16;   // batches: more pivots per workgroup, fewer passes over each pair's matches
     t.hyp_per_cu = 4;
-    t.sc2_sparse_cap = 0;
+    t.sc2_sparse_cap = max_n > kSparseMinN ? kSparseCap : 0;
     return t;
 }
 
@@ -297,13 +303,6 @@ tr_status check_params(tr_handle *h, const tr_params *p)
     return TR_OK;
 }
 
-// Without a requested threshold (sc2_sparse_cap = 0) calls of pairs beyond kSparseMinN matches count bits in
-// tiles whose edges are at most 1 / kSparseDensity of their entries. Whole calls with every tile counted / every
-// tile on the matrix cores (us): N = 5000 116 / 103 at 0.7 to 2.7 % edges; N = 8192 160 / 188 at 0.7 %,
-// 186 / 187 at 2.7 %, 205 / 186 at 3.8 %; N = 12000 245 / 418, 324 / 403 and 411 / 405; N = 20000 464 / 1385,
-// 862 / 1398 and 1069 / 1402, 1370 / 1404 at 5.3 %.
-constexpr int32_t kSparseMinN = 8192;
-
 // The launch sequence for B pairs (offsets on the device) or one pair (n_single).
 // features_only stops after the learned features.
 tr_status enqueue(tr_handle *h, const Work &w_in, const int32_t *offsets, int32_t n_single, int32_t B,
@@ -314,14 +313,11 @@ tr_status enqueue(tr_handle *h, const Work &w_in, const int32_t *offsets, int32_
     if (!ev_mask) ev_mask = &ev_mask_unused;
     Work w = w_in;
     w.sc2_super = cfg.sc2_super;
-    // the bit-count kernel: on request, and for pairs large enough that its tiles fill the CUs (a tile it does
-    // not take costs it a count of its edges)
-    const bool sparse = cfg.sc2_sparse_cap > 0 || max_n > kSparseMinN;
+    const bool sparse = cfg.sc2_sparse_cap > 0;   // (a tile that the bit-count kernel does not take costs it a count)
     w.sp_tile = sparse ? sparse_tile(B, max_n, h->num_cus) : 256;
     if (sparse) {
-        const int64_t area = (int64_t)w.sp_tile * w.sp_tile;
         w.sp_list = h->sp_list;
-        w.sp_limit = (int32_t)(cfg.sc2_sparse_cap * area / (256 * 256));
+        w.sp_cap = cfg.sc2_sparse_cap;
     }
     const bool profile = ev != nullptr;
     const int64_t npad = (max_n + kSc2Tile - 1) / kSc2Tile * kSc2Tile;
