@@ -176,7 +176,8 @@ typedef struct {
     int32_t hyp_per_cu;     /* hypothesis workgroups launched per CU, 1..16        */
     int32_t sc2_sparse_cap; /* SC2 output tiles with at most this many edges per
                                256 x 256 entries count common neighbours per edge
-                               from bit rows instead of the dense product; 0 = every
+                               from bit rows instead of the dense product (not in
+                               calls of no more such tiles than CUs); 0 = every
                                tile takes the product. 0..TR_SC2_SPARSE_CAP_MAX  */
 } tr_tuning;
 

@@ -57,6 +57,7 @@ struct PairState {
 struct Plan {
     int32_t B;
     int32_t total[kNumPrefix];
+    int32_t sp_tile;        // tile edge of the SC2 bit-count kernel, 0: every tile takes the product
     int32_t sc2_split[9];   // SC2 items [sc2_split[x], sc2_split[x+1]) go to XCD x: equal modelled cost
 };
 
@@ -76,7 +77,7 @@ struct Work {
     int32_t H;                // k1 * k2 hypotheses per pair
     int32_t graph;
     int32_t sc2_super;        // SC2 tile walk: super-tile side in output tiles (launch configuration)
-    int32_t sp_tile;          // tile edge of the SC2 bit-count kernel
+    int32_t sp_tile;          // the same for a single-pair call (sc2_sparse_edge)
     int32_t sp_cap;           // it takes tiles of at most so many edges per 256 x 256 entries (launch configuration)
     int32_t *sp_list;         // the tiles it left to the dense kernel: their number, its next tile, its list
                               // items; null where it is not launched
@@ -245,7 +246,7 @@ __host__ __device__ inline int64_t stage_items(int stage, int32_t n, int32_t H, 
     case kPrep: return (n + kPrepRows - 1) / kPrepRows;
     case kCompat: return nbc * (nbc + 1) / 2;
     case kSc2: return nbs * (nbs + 1) / 2;
-    case kSp: { const int64_t nb = (n + sp - 1) / sp; return nb * (nb + 1) / 2; }   // bit-count tiles of edge sp
+    case kSp: { const int64_t nb = sp > 0 ? (n + sp - 1) / sp : 0; return nb * (nb + 1) / 2; }   // bit-count tiles of edge sp
     case kCollect: {
         const int64_t nb = (n + 63) / 64, sg = collect_segs(n), units = nb * ((nb + sg - 1) / sg);
         return collect_shared(n) ? units : (units + 3) / 4;
@@ -253,6 +254,28 @@ __host__ __device__ inline int64_t stage_items(int stage, int32_t n, int32_t H, 
     case kRowBlk: return (n + kRowsPerItem - 1) / kRowsPerItem;
     default: return (int64_t)((H + kScoreHyp - 1) / kScoreHyp) * ((n + kScorePts - 1) / kScorePts);
     }
+}
+
+// Tile edge of the SC2 bit-count kernel, by the number of tiles of each edge 256, 512, 768 and 1024 over all pairs:
+// larger tiles read each row's bits fewer times, smaller ones spread a short list over the CUs (one workgroup each).
+// The cost of a round of tiles is its edges, plus what a tile costs besides (as much as 2^17 entries). 0: no tiles, a
+// list that one round of 256-tiles holds takes the product, whatever limit is asked for. Bit counts / product there
+// (us a call, 1.5 % edges): one pair of 1000 106 / 74, of 3000 113 / 86, of 5000 130 / 111, sixteen of 1000 183 / 147;
+// beyond it one of 8000 176 / 190, sixteen of 3000 309 / 285, of 5000 568 / 629.
+constexpr int kSpEdges = 4;
+__host__ __device__ inline int32_t sparse_tile(const int32_t *tiles, int32_t num_cus)
+{
+    if (tiles[0] <= num_cus) return 0;
+    int32_t best = 0;
+    int64_t cost = INT64_MAX;
+    for (int k = kSpEdges; k >= 1; --k) {
+        const int64_t rounds = (tiles[k - 1] + num_cus - 1) / num_cus, c = rounds * (65536 * k * k + (1 << 17));
+        if (c < cost) {
+            cost = c;
+            best = 256 * k;
+        }
+    }
+    return best;
 }
 
 // Work lists: all items of a stage, pair after pair, in the plan's slot order: for batches of
@@ -263,6 +286,11 @@ __host__ __device__ inline int64_t stage_items(int stage, int32_t n, int32_t H, 
 __device__ __forceinline__ int stage_total(const Work &w, int stage)
 {
     return w.n1 ? (int)stage_items(stage, w.n1, w.H, w.sp_tile) : w.plan->total[stage];
+}
+
+__device__ __forceinline__ int sc2_sparse_edge(const Work &w)
+{
+    return w.n1 ? w.sp_tile : w.plan->sp_tile;
 }
 
 // The pair in slot k of the cost order (kernels with one workgroup, or a fixed number, per
@@ -367,12 +395,11 @@ __device__ inline void bitonic_sort_lds(uint64_t *keys, int P)
 
 // ---- launchers (one per kernel family); each returns the launch's hipError_t ----
 hipError_t launch_plan(const Work &w, const int32_t *offsets, int32_t n_single, int32_t B,
-                       int32_t max_n, PairDesc *pairs, PairState *state, Plan *plan, int32_t *pre,
+                       int32_t max_n, int num_cus, PairDesc *pairs, PairState *state, Plan *plan, int32_t *pre,
                        hipStream_t s);
 int compat_rows(int64_t tiles, int num_cus);
 hipError_t launch_compat(const Work &w, int64_t tiles, int cap, hipStream_t s);
 hipError_t launch_compat_features(const Work &w, int64_t items, int cap, hipStream_t s);
-int sparse_tile(int64_t B, int32_t n, int num_cus);
 hipError_t launch_sc2_sparse(const Work &w, int64_t tiles, int num_cus, hipStream_t s);
 hipError_t launch_sc2(const Work &w, int64_t items, int num_cus, hipStream_t s);
 hipError_t launch_pivots(const Work &w, int B, int grid_rows, int num_cus, hipStream_t s);

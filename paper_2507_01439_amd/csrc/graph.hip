@@ -117,9 +117,9 @@ __device__ __forceinline__ int snake_slot(int p, int B)
 // order of the pairs (from 16 pairs on: by decreasing npad, pairs of one size in index order,
 // dealt to the XCDs; else index order);
 // the work-item counts of every stage and their prefix sums over that order; the XCD ranges of
-// the SC2 list, equal in modelled cost.
+// the SC2 list, equal in modelled cost; with sp_cus > 0 (bit counts on so many CUs) their tile edge.
 __global__ void __launch_bounds__(1024) k_plan(const int32_t *offsets, int32_t n_single, int32_t B,
-                                               int32_t max_n, int32_t pool, int32_t H, int32_t sp,
+                                               int32_t max_n, int32_t pool, int32_t H, int32_t sp_cus,
                                                PairDesc *pairs, PairState *state, Plan *plan,
                                                int32_t *pre, int32_t pre_stride)
 {
@@ -129,6 +129,7 @@ __global__ void __launch_bounds__(1024) k_plan(const int32_t *offsets, int32_t n
     __shared__ int32_t kfirst[kCostKeys];        // pairs per size key, then the key's next free position
     __shared__ int32_t wfirst[16][kCostKeys];    // per wave of a chunk: pairs per key, then first position
     __shared__ int32_t nl[1024], ol[1024];       // B <= 1024: n of each valid pair (0 if invalid); the order
+    __shared__ int32_t sp_tiles[kSpEdges];       // bit-count tiles of each edge over all pairs (sparse_tile)
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, nw = blockDim.x >> 6;
     int32_t *order = pre + kOrderRow * pre_stride, *slot_of = pre + kSlotRow * pre_stride;
     auto size_of = [&](int b, int32_t &n, int32_t &pt) {   // n and first match of pair b; valid?
@@ -149,6 +150,7 @@ __global__ void __launch_bounds__(1024) k_plan(const int32_t *offsets, int32_t n
     // epilogue (scan, histogram, stores), which takes about as long as 2048 columns
     auto sc2_unit = [](int32_t npad) { return (int64_t)npad + 2048; };
     for (int k = tid; k < kCostKeys; k += blockDim.x) kfirst[k] = 0;
+    if (tid < kSpEdges) sp_tiles[tid] = 0;
     __syncthreads();
     // pass 1, pair order: descriptors, state, arena offsets, size-key counts, total SC2 cost
     int64_t acarry = 0, sc2_cost = 0;
@@ -157,7 +159,7 @@ __global__ void __launch_bounds__(1024) k_plan(const int32_t *offsets, int32_t n
         int32_t n, pt;
         const bool ok = size_of(b, n, pt);
         const int32_t npad = ok ? (n + kSc2Tile - 1) / kSc2Tile * kSc2Tile : 0;
-        int64_t v[2] = {(int64_t)npad * npad, ok ? stage_items(kSc2, n, H, sp) * sc2_unit(npad) : 0}, excl[2], tot[2];
+        int64_t v[2] = {(int64_t)npad * npad, ok ? stage_items(kSc2, n, H, 0) * sc2_unit(npad) : 0}, excl[2], tot[2];
         block_scan_multi<2>(v, excl, tot, lds1);
         if (b < B) {
             PairDesc d = pair_desc_of(n, pt, excl[0] + acarry, pool);
@@ -168,6 +170,8 @@ __global__ void __launch_bounds__(1024) k_plan(const int32_t *offsets, int32_t n
             state[b] = st;
             atomicAdd(&kfirst[npad / kSc2Tile], 1);
             if (small) nl[b] = ok ? n : 0;
+            if (ok && sp_cus > 0)
+                for (int k = 0; k < kSpEdges; ++k) atomicAdd(&sp_tiles[k], (int)stage_items(kSp, n, H, 256 * (k + 1)));
         }
         acarry += tot[0];
         sc2_cost += tot[1];
@@ -229,8 +233,10 @@ __global__ void __launch_bounds__(1024) k_plan(const int32_t *offsets, int32_t n
     }
     __syncthreads();   // order[] is read by other threads below
     // pass 3, slot order: stage prefixes; SC2 range boundaries at x / 8 of the cost
+    const int32_t sp = sp_cus > 0 ? sparse_tile(sp_tiles, sp_cus) : 0;   // from the pairs there are, not the bound on them
     if (tid == 0) {
         plan->B = B;
+        plan->sp_tile = sp;
         plan->sc2_split[0] = 0;
         for (int x = 1; x < 8; ++x)
             if (sc2_cost * x / 8 == 0) plan->sc2_split[x] = 0;
@@ -935,8 +941,8 @@ __global__ void __launch_bounds__(256, kSc2PerCu) k_sc2(Work w)
     int32_t *hist = reinterpret_cast<int32_t *>(smem), *tmax = hist + kHistWords - 2;   // zero outside the epilogue
     uint16_t *T = reinterpret_cast<uint16_t *>(smem + (MODE == kSc2Features ? 0 : kHistBytes));
     int start, end;
-    const int nx = (gridDim.x - (blockIdx.x & 7) + 7) >> 3, m = w.sp_tile / kOut;
-    if (w.sp_list) {   // the tiles that the bit-count kernel left, dealt to the XCDs
+    const int nx = (gridDim.x - (blockIdx.x & 7) + 7) >> 3, sp = w.sp_list ? sc2_sparse_edge(w) : 0, m = sp / kOut;
+    if (sp) {   // the tiles that the bit-count kernel left, dealt to the XCDs
         start = 0;
         end = (w.sp_list[0] - (int)(blockIdx.x & 7) + 7) / 8 * m * m;
     } else {
@@ -950,10 +956,10 @@ __global__ void __launch_bounds__(256, kSc2PerCu) k_sc2(Work w)
     int par = 0;
     for (int it = start + (blockIdx.x >> 3); it < end; it += nx) {
         int local, b, bi, bj;
-        if (w.sp_list) {
+        if (sp) {
             const int q = it % (m * m);
             b = stage_pair(w, kSp, w.sp_list[2 + it / (m * m) * 8 + (blockIdx.x & 7)], local);
-            tri_decode(local, (pair_desc(w, b).n + w.sp_tile - 1) / w.sp_tile, bi, bj);
+            tri_decode(local, (pair_desc(w, b).n + sp - 1) / sp, bi, bj);
             bi = __builtin_amdgcn_readfirstlane(m * bi + q / m);
             bj = __builtin_amdgcn_readfirstlane(m * bj + q % m);
         } else {
@@ -1006,6 +1012,7 @@ constexpr int kSpSegAt = kSpLowAt + kSpCopies * kSpPitch * 4;    // maxima by 64
 constexpr int kSpZero = kSpSegAt / 4 + kSpMax / 64 * kSpMax;     // words cleared before the weights are collected
 constexpr int kSpLds = kSpRing + 8 * kSpWaves + 16;
 static_assert(kSpCap * 16 <= kSpRing && 4 * kSpZero <= kSpRing && kSpZero % 4 == 0, "LDS layout of the bit-count kernel");
+static_assert(kSpMax == 256 * kSpEdges, "tile edges of the bit-count kernel");
 
 // Wait until at most n vector-memory operations of this wave are outstanding (n is rounded down).
 __device__ __forceinline__ void wait_vm(int n)
@@ -1018,7 +1025,9 @@ __device__ __forceinline__ void wait_vm(int n)
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-template <int MODE>
+// BATCH: the tile edge is the plan's; a single pair's is a kernel argument (read from memory, N = 20000 took 611 us a
+// call, 604 so).
+template <int MODE, bool BATCH>
 __global__ void __launch_bounds__(kSpThreads) k_sc2_sparse(Work w)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -1030,8 +1039,9 @@ __global__ void __launch_bounds__(kSpThreads) k_sc2_sparse(Work w)
     int32_t *scan = reinterpret_cast<int32_t *>(smem + kSpRing);
     uint32_t *list = reinterpret_cast<uint32_t *>(smem);
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int S = w.sp_tile, total = stage_total(w, kSp);
+    const int total = stage_total(w, kSp);
     for (int item = blockIdx.x, next; item < total; item = next) {
+        const int S = BATCH ? __builtin_amdgcn_readfirstlane(w.plan->sp_tile) : w.sp_tile;
         int local;
         const int b = __builtin_amdgcn_readfirstlane(stage_pair(w, kSp, item, local));
         const PairDesc d = pair_desc(w, b);
@@ -1097,7 +1107,7 @@ __global__ void __launch_bounds__(kSpThreads) k_sc2_sparse(Work w)
         // (counted against the whole square, the half tiles on the diagonal and the narrow last ones of pairs too dense
         // for this kernel came here, up to two passes of 20 CUs alone: 1738 us a call at N = 20000, 5.3 %; 1389 now)
         const int entries = min(S, n - i0) * min(S, n - j0) / (diag ? 2 : 1);   // the last tiles are narrower
-        const bool take = (int64_t)edges << 16 <= (int64_t)w.sp_cap * entries;
+        const bool take = edges <= ((entries + 255) >> 8) * w.sp_cap >> 8;   // sp_cap of every 65536
         if (!take) {   // the same for the whole workgroup: the dense kernel's
             if (tid == 0) w.sp_list[2 + atomicAdd(&w.sp_list[0], 1)] = item;
             __syncthreads();
@@ -1297,11 +1307,11 @@ __global__ void __launch_bounds__(kSpThreads) k_sc2_sparse(Work w)
 
 }  // namespace
 
-hipError_t launch_plan(const Work &w, const int32_t *offsets, int32_t n_single, int32_t B, int32_t max_n,
+hipError_t launch_plan(const Work &w, const int32_t *offsets, int32_t n_single, int32_t B, int32_t max_n, int num_cus,
                        PairDesc *pairs, PairState *state, Plan *plan, int32_t *pre, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_plan, dim3(1), dim3(1024), 0, s, offsets, n_single, B, max_n, w.pool, w.H, w.sp_tile, pairs,
-                       state, plan, pre, w.pre_stride);
+    hipLaunchKernelGGL(k_plan, dim3(1), dim3(1024), 0, s, offsets, n_single, B, max_n, w.pool, w.H,
+                       w.sp_list ? num_cus : 0, pairs, state, plan, pre, w.pre_stride);
     return hipGetLastError();
 }
 
@@ -1339,31 +1349,14 @@ constexpr int sc2_lds(int mode)
 }
 }  // namespace
 
-// Tile edge of the bit-count kernel for B pairs of up to n matches: larger tiles read each row's bits fewer
-// times, smaller ones spread a short list over the CUs (one workgroup each). The cost of a round of tiles is
-// its edges, plus what a tile costs besides (as much as 2^17 entries).
-int sparse_tile(int64_t B, int32_t n, int num_cus)
-{
-    int best = kSpMax;
-    int64_t cost = INT64_MAX;
-    for (int S = kSpMax; S >= 256; S -= 256) {
-        const int64_t nb = (n + S - 1) / S, rounds = (B * nb * (nb + 1) / 2 + num_cus - 1) / num_cus;
-        const int64_t c = rounds * ((int64_t)S * S + (1 << 17));
-        if (c < cost) {
-            cost = c;
-            best = S;
-        }
-    }
-    return best;
-}
-
 // Tiles of the bit-count kernel, before launch_sc2 takes those it left. tiles: of its list, at most.
 hipError_t launch_sc2_sparse(const Work &w, int64_t tiles, int num_cus, hipStream_t s)
 {
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(tiles, num_cus));
-    if (!w.learned) hipLaunchKernelGGL(k_sc2_sparse<kSc2Plain>, dim3(grid), dim3(kSpThreads), kSpLds, s, w);
-    else if (!w.feat_all) hipLaunchKernelGGL(k_sc2_sparse<kSc2Learned>, dim3(grid), dim3(kSpThreads), kSpLds, s, w);
-    else hipLaunchKernelGGL(k_sc2_sparse<kSc2Features>, dim3(grid), dim3(kSpThreads), kSpLds, s, w);
+    const auto kernel = w.feat_all && w.learned ? k_sc2_sparse<kSc2Features, true>   // (features come in batches)
+                        : w.learned ? w.n1 ? k_sc2_sparse<kSc2Learned, false> : k_sc2_sparse<kSc2Learned, true>
+                        : w.n1 ? k_sc2_sparse<kSc2Plain, false> : k_sc2_sparse<kSc2Plain, true>;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kSpThreads), kSpLds, s, w);
     return hipGetLastError();
 }
 
@@ -1382,13 +1375,15 @@ hipError_t launch_sc2(const Work &w, int64_t items, int num_cus, hipStream_t s)
 
 hipError_t setup_graph_kernels()
 {
-    const void *fns[4] = {reinterpret_cast<const void *>(k_sc2_sparse<kSc2Plain>),
-                          reinterpret_cast<const void *>(k_sc2_sparse<kSc2Learned>),
-                          reinterpret_cast<const void *>(k_sc2_sparse<kSc2Features>),
-                          reinterpret_cast<const void *>(k_sc2<kSc2Learned>)};
-    const int lds[4] = {kSpLds, kSpLds, kSpLds, sc2_lds(kSc2Learned)};
+    const void *fns[] = {reinterpret_cast<const void *>(k_sc2_sparse<kSc2Plain, false>),
+                         reinterpret_cast<const void *>(k_sc2_sparse<kSc2Plain, true>),
+                         reinterpret_cast<const void *>(k_sc2_sparse<kSc2Learned, false>),
+                         reinterpret_cast<const void *>(k_sc2_sparse<kSc2Learned, true>),
+                         reinterpret_cast<const void *>(k_sc2_sparse<kSc2Features, true>),
+                         reinterpret_cast<const void *>(k_sc2<kSc2Learned>)};
+    const int lds[] = {kSpLds, kSpLds, kSpLds, kSpLds, kSpLds, sc2_lds(kSc2Learned)};
     hipError_t e = hipSuccess;
-    for (int k = 0; k < 4 && e == hipSuccess; ++k)
+    for (int k = 0; k < 6 && e == hipSuccess; ++k)
         e = hipFuncSetAttribute(fns[k], hipFuncAttributeMaxDynamicSharedMemorySize, lds[k]);
     return e;
 }

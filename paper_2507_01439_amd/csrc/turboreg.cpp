@@ -239,7 +239,7 @@ Work make_work(tr_handle *h, const float *src, const float *dst, const tr_params
     w.H = p.k1 * p.k2;
     w.graph = p.graph;
     w.sc2_super = 5;
-    w.sp_tile = 256;
+    w.sp_tile = 0;
     w.sp_list = nullptr;
     w.tau = p.tau;
     w.theta = p.inlier_thresh;
@@ -313,8 +313,13 @@ tr_status enqueue(tr_handle *h, const Work &w_in, const int32_t *offsets, int32_
     if (!ev_mask) ev_mask = &ev_mask_unused;
     Work w = w_in;
     w.sc2_super = cfg.sc2_super;
-    const bool sparse = cfg.sc2_sparse_cap > 0;   // (a tile that the bit-count kernel does not take costs it a count)
-    w.sp_tile = sparse ? sparse_tile(B, max_n, h->num_cus) : 256;
+    bool sparse = cfg.sc2_sparse_cap > 0;   // (a tile that the bit-count kernel does not take costs it a count)
+    if (sparse && w.n1) {   // the tile edge of a single pair; a batch has its plan's, from the pairs' own sizes
+        int32_t tiles[kSpEdges];
+        for (int k = 0; k < kSpEdges; ++k) tiles[k] = (int32_t)stage_items(kSp, w.n1, 0, 256 * (k + 1));
+        w.sp_tile = sparse_tile(tiles, h->num_cus);
+        sparse = w.sp_tile > 0;
+    }
     if (sparse) {
         w.sp_list = h->sp_list;
         w.sp_cap = cfg.sc2_sparse_cap;
@@ -340,7 +345,7 @@ tr_status enqueue(tr_handle *h, const Work &w_in, const int32_t *offsets, int32_
         w.prof_acc = h->prof_acc;
     }
     if (!w.n1) mark(TR_STAGE_PLAN);
-    if (!w.n1) chk(launch_plan(w, offsets, n_single, B, max_n, h->pairs, h->state, h->plan, h->pre, s));
+    if (!w.n1) chk(launch_plan(w, offsets, n_single, B, max_n, h->num_cus, h->pairs, h->state, h->plan, h->pre, s));
     mark(TR_STAGE_COMPAT);
     const int64_t tiles = B * stage_items(kCompat, max_n, 0, 256);
     w.compat_rows = compat_rows(tiles, h->num_cus);
@@ -353,7 +358,7 @@ tr_status enqueue(tr_handle *h, const Work &w_in, const int32_t *offsets, int32_
         // the kernel splits its items into 8 ranges, one per XCD (workgroup g runs on XCD g mod 8), of
         // equal counts for one pair and of equal modelled cost for a batch
         const int64_t items = (int64_t)B * nbs * (nbs + 1) / 2;
-        if (sparse) chk(launch_sc2_sparse(w, B * stage_items(kSp, max_n, 0, w.sp_tile), h->num_cus, s));
+        if (sparse) chk(launch_sc2_sparse(w, B * stage_items(kSp, max_n, 0, w.n1 ? w.sp_tile : 256), h->num_cus, s));
         chk(launch_sc2(w, items, h->num_cus, s));
     }
     if (features_only) return e == hipSuccess ? TR_OK : TR_ERR_HIP;
