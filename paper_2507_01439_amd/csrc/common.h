@@ -58,6 +58,7 @@ struct Plan {
     int32_t B;
     int32_t total[kNumPrefix];
     int32_t sp_tile;        // tile edge of the SC2 bit-count kernel, 0: every tile takes the product
+    int32_t compat_rows;    // rows of a compatibility tile per work item: 8, 16, 32 or 128
     int32_t sc2_split[9];   // SC2 items [sc2_split[x], sc2_split[x+1]) go to XCD x: equal modelled cost
 };
 
@@ -89,7 +90,7 @@ struct Work {
     int32_t hist_stride;      // max_n rounded up to 8 (16-byte aligned copies)
     uint16_t *segmax;         // per pair npad x npad / 64 from g_off / 64: the maximum of G over the pairs i < j of row
                               // i in each 64-column segment (order: part_at; written by the SC2 kernels)
-    int32_t compat_rows;      // rows of a compatibility tile per work item: 8, 16, 32, 64 or 128
+    int32_t compat_rows;      // the same for a single-pair call (compat_item_rows)
     uint32_t *cnt_part;       // per compatibility work item: edges (15 bits), boundary pairs << 15, non-finite
                               // input << 30
     int32_t *rowcnt;          // max_batch x max_n: pairs of weight alpha per row (ordered path)
@@ -256,6 +257,17 @@ __host__ __device__ inline int64_t stage_items(int stage, int32_t n, int32_t H, 
     }
 }
 
+// Rows per work item (one wave) of the compatibility kernel, for a list of `tiles` tiles: long items
+// amortise the item's loads and transposes, short ones spread a short list over the CUs.
+// Measured at 8 / 16 / 32 / 64 / 128 rows (us): N = 300 6.1 / 6.8 / 9.4, N = 1000 6.0 / 7.3 / 9.8,
+// N = 2749 (253 tiles) 9.1 / 9.0 / 10.8, N = 5000 (820) 20.5 / 18.3 / 17.2 / 19.7 / 29.7, N = 20000 (12403)
+// 199 / 143 / 116 / 112 / 107, 256 pairs 1580 / 1091 / 856 / 800 / 750. (With 64 x 64 tiles per workgroup, two
+// square roots a pair and packing through LDS: 6.1, 6.8, 10.6, 22.6, 229 and 2060.)
+__host__ __device__ inline int32_t compat_rows(int64_t tiles, int32_t num_cus)
+{
+    return tiles <= num_cus ? 8 : tiles <= 2 * num_cus ? 16 : tiles <= 16 * num_cus ? 32 : 128;
+}
+
 // Tile edge of the SC2 bit-count kernel, by the number of tiles of each edge 256, 512, 768 and 1024 over all pairs:
 // larger tiles read each row's bits fewer times, smaller ones spread a short list over the CUs (one workgroup each).
 // The cost of a round of tiles is its edges, plus what a tile costs besides (as much as 2^17 entries). 0: no tiles, a
@@ -291,6 +303,11 @@ __device__ __forceinline__ int stage_total(const Work &w, int stage)
 __device__ __forceinline__ int sc2_sparse_edge(const Work &w)
 {
     return w.n1 ? w.sp_tile : w.plan->sp_tile;
+}
+
+__device__ __forceinline__ int compat_item_rows(const Work &w)
+{
+    return w.n1 ? w.compat_rows : w.plan->compat_rows;
 }
 
 // The pair in slot k of the cost order (kernels with one workgroup, or a fixed number, per
@@ -397,7 +414,6 @@ __device__ inline void bitonic_sort_lds(uint64_t *keys, int P)
 hipError_t launch_plan(const Work &w, const int32_t *offsets, int32_t n_single, int32_t B,
                        int32_t max_n, int num_cus, PairDesc *pairs, PairState *state, Plan *plan, int32_t *pre,
                        hipStream_t s);
-int compat_rows(int64_t tiles, int num_cus);
 hipError_t launch_compat(const Work &w, int64_t tiles, int cap, hipStream_t s);
 hipError_t launch_compat_features(const Work &w, int64_t items, int cap, hipStream_t s);
 hipError_t launch_sc2_sparse(const Work &w, int64_t tiles, int num_cus, hipStream_t s);

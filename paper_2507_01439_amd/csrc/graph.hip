@@ -117,9 +117,10 @@ __device__ __forceinline__ int snake_slot(int p, int B)
 // order of the pairs (from 16 pairs on: by decreasing npad, pairs of one size in index order,
 // dealt to the XCDs; else index order);
 // the work-item counts of every stage and their prefix sums over that order; the XCD ranges of
-// the SC2 list, equal in modelled cost; with sp_cus > 0 (bit counts on so many CUs) their tile edge.
+// the SC2 list, equal in modelled cost; the launch shapes that follow the pairs' own sizes
+// (the sizes a batch is declared for may be far above them).
 __global__ void __launch_bounds__(1024) k_plan(const int32_t *offsets, int32_t n_single, int32_t B,
-                                               int32_t max_n, int32_t pool, int32_t H, int32_t sp_cus,
+                                               int32_t max_n, int32_t pool, int32_t H, int32_t num_cus, bool sparse,
                                                PairDesc *pairs, PairState *state, Plan *plan,
                                                int32_t *pre, int32_t pre_stride)
 {
@@ -170,7 +171,7 @@ __global__ void __launch_bounds__(1024) k_plan(const int32_t *offsets, int32_t n
             state[b] = st;
             atomicAdd(&kfirst[npad / kSc2Tile], 1);
             if (small) nl[b] = ok ? n : 0;
-            if (ok && sp_cus > 0)
+            if (ok && sparse)
                 for (int k = 0; k < kSpEdges; ++k) atomicAdd(&sp_tiles[k], (int)stage_items(kSp, n, H, 256 * (k + 1)));
         }
         acarry += tot[0];
@@ -233,7 +234,7 @@ __global__ void __launch_bounds__(1024) k_plan(const int32_t *offsets, int32_t n
     }
     __syncthreads();   // order[] is read by other threads below
     // pass 3, slot order: stage prefixes; SC2 range boundaries at x / 8 of the cost
-    const int32_t sp = sp_cus > 0 ? sparse_tile(sp_tiles, sp_cus) : 0;   // from the pairs there are, not the bound on them
+    const int32_t sp = sparse ? sparse_tile(sp_tiles, num_cus) : 0;
     if (tid == 0) {
         plan->B = B;
         plan->sp_tile = sp;
@@ -274,6 +275,7 @@ __global__ void __launch_bounds__(1024) k_plan(const int32_t *offsets, int32_t n
             plan->total[s] = (int32_t)carry[s];
         }
         plan->sc2_split[8] = (int32_t)carry[kSc2];
+        plan->compat_rows = compat_rows(carry[kCompat], num_cus);
     }
 }
 
@@ -361,7 +363,7 @@ __global__ void __launch_bounds__(256) k_compat(Work w)
     if (w.sp_list && blockIdx.x == 0 && threadIdx.x < 2) w.sp_list[threadIdx.x] = 0;   // counted up by k_sc2_sparse
     const bool cached = slot_cache_fill(w, kCompat, slots);
     __syncthreads();
-    const int ROWS = w.compat_rows, R = min(ROWS, 32), per = kCompatTile / ROWS, total = stage_total(w, kCompat) * per;
+    const int ROWS = __builtin_amdgcn_readfirstlane(compat_item_rows(w)), R = min(ROWS, 32), per = kCompatTile / ROWS, total = stage_total(w, kCompat) * per;
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const float tau = w.tau, t2 = 2.0f * tau * tau, t4 = (tau * tau) * (tau * tau);
     const bool odd_tau = !(tau >= 1e-9f && tau <= 1e8f);
@@ -1311,19 +1313,8 @@ hipError_t launch_plan(const Work &w, const int32_t *offsets, int32_t n_single, 
                        PairDesc *pairs, PairState *state, Plan *plan, int32_t *pre, hipStream_t s)
 {
     hipLaunchKernelGGL(k_plan, dim3(1), dim3(1024), 0, s, offsets, n_single, B, max_n, w.pool, w.H,
-                       w.sp_list ? num_cus : 0, pairs, state, plan, pre, w.pre_stride);
+                       num_cus, w.sp_list != nullptr, pairs, state, plan, pre, w.pre_stride);
     return hipGetLastError();
-}
-
-// Rows per work item (one wave) of the compatibility kernel, for a list of `tiles` tiles: long items
-// amortise the item's loads and transposes, short ones spread a short list over the CUs.
-// Measured at 8 / 16 / 32 / 64 / 128 rows (us): N = 300 6.1 / 6.8 / 9.4, N = 1000 6.0 / 7.3 / 9.8,
-// N = 2749 (253 tiles) 9.1 / 9.0 / 10.8, N = 5000 (820) 20.5 / 18.3 / 17.2 / 19.7 / 29.7, N = 20000 (12403)
-// 199 / 143 / 116 / 112 / 107, 256 pairs 1580 / 1091 / 856 / 800 / 750. (With 64 x 64 tiles per workgroup, two
-// square roots a pair and packing through LDS: 6.1, 6.8, 10.6, 22.6, 229 and 2060.)
-int compat_rows(int64_t tiles, int num_cus)
-{
-    return tiles <= num_cus ? 8 : tiles <= 2 * num_cus ? 16 : tiles <= 16 * num_cus ? 32 : 128;
 }
 
 // tiles: 128 x 128 tiles of the list; cap: workgroups to launch at most.

@@ -225,7 +225,7 @@ struct Tally {
 
     __device__ __forceinline__ Tally(const Work &w, int b)
     {
-        const int per = kCompatTile / w.compat_rows;   // work items per list tile
+        const int per = kCompatTile / compat_item_rows(w);   // work items per list tile
         t0 = per * stage_first(w, kCompat, b);
         t1 = t0 + per * stage_count(w, kCompat, b);
         load(w, t0 + (int)threadIdx.x);

@@ -45,7 +45,10 @@ def run(pairs, declared, cap, learned):
 
 @pytest.mark.parametrize("learned", [False, True])
 @pytest.mark.parametrize("ns,declared", [([1000] * 5, 9000), ([300, 257, 3, 700], 8192), ([130] * 300, 2000),
-                                         ([2300, 800, 64] * 8, 10000), ([8300] + [600] * 7, 12000)])
+                                         ([2300, 800, 64] * 8, 10000), ([8300] + [600] * 7, 12000),
+                                         # compatibility lists of 80, 360, 810 and 5400 tiles: 8, 16, 32, 128 rows
+                                         ([300] * 8, 8192), ([1000] * 10, 5000), ([500] * 81, 3000),
+                                         ([1000] * 150, 2000)])
 def test_results_do_not_depend_on_the_declared_size(ns, declared, learned):
     base = synth.CONFIGS["outdoor_n20000"]
     pairs = [synth.make_pair(base.replace(n=n, inlier_ratio=0.1), 300 + k % 5) for k, n in enumerate(ns)]
