@@ -1109,7 +1109,7 @@ __global__ void __launch_bounds__(kSpThreads) k_sc2_sparse(Work w)
         // (counted against the whole square, the half tiles on the diagonal and the narrow last ones of pairs too dense
         // for this kernel came here, up to two passes of 20 CUs alone: 1738 us a call at N = 20000, 5.3 %; 1389 now)
         const int entries = min(S, n - i0) * min(S, n - j0) / (diag ? 2 : 1);   // the last tiles are narrower
-        const bool take = edges <= ((entries + 255) >> 8) * w.sp_cap >> 8;   // sp_cap of every 65536
+        const bool take = edges <= (entries + 255) / 256 * w.sp_cap / 256;   // sp_cap of every 65536
         if (!take) {   // the same for the whole workgroup: the dense kernel's
             if (tid == 0) w.sp_list[2 + atomicAdd(&w.sp_list[0], 1)] = item;
             __syncthreads();
