@@ -13,7 +13,6 @@ constexpr int kCompatTile = 128;  // tile edge of the compatibility list
 constexpr int kCompatMinRows = 8; // fewest rows of a tile one work item takes (Work::compat_rows)
 constexpr int kRowsPerItem = 4;   // rows per work item of the pivot scans (one per wave)
 constexpr int kPrepRows = 256;    // rows per work item of the prep / feature kernels
-constexpr int kRankSortMax = 4096; // candidate lists up to this size are ordered by a rank sort
 constexpr int kScoreHyp = 64;     // hypotheses per scoring work item (four per thread)
 constexpr int kScorePts = 256;    // points per scoring work item (staged in LDS)
 // Counters that many workgroups update with device-scope atomics are spread out: same-address
@@ -115,7 +114,7 @@ struct Work {
     float *gscore;            // max_batch x h_cap error-based scores (metric != 0)
     int32_t metric;           // hypothesis ranking: 0 inlier number, 1 MAE form, 2 MSE form
     int32_t h_cap;
-    int32_t *rowstat;         // max_batch x max_n x 20 feature accumulators (learned mode): degree, two unused, 16 bins
+    int32_t *rowstat;         // max_batch x max_n x 20 feature accumulators (learned mode): degree, two unused, 16 bins, one unused
     // row sums and maxima of the SC2 matrix in parts that the SC2 kernels store (learned mode), with segmax: row i's
     // sum over the pairs i < j of each 64-column segment (as segmax), and per 128-row block and column the sum and
     // maximum over the pairs i < j of the block (npad x npad / 128 from g_off / 128)
@@ -139,8 +138,6 @@ struct Work {
 // Sums of the hypothesis kernel's phases over profiled calls (prof_acc slots).
 enum { kProfSearch = 0, kProfFit, kProfScore, kProfRecords, kProfSelect, kProfItems, kProfPairs, kProfSlots };
 
-
-// Largest b in [0, B) with pre[b] <= item (pre is non-decreasing, pre[0] = 0).
 // Length of a difference vector in float32: first square rounded, the other
 // two fused, then the correctly rounded square root (the order is part of the
 // bit-exact contract of C).
@@ -184,6 +181,7 @@ __device__ __forceinline__ int count_smaller(const uint64_t *keys, int q0, int q
     return rk;
 }
 
+// Largest b in [0, B) with pre[b] <= item (pre is non-decreasing, pre[0] = 0).
 __device__ __forceinline__ int find_pair(const int32_t *pre, int B, int item)
 {
     int lo = 0, hi = B - 1;
@@ -375,39 +373,6 @@ __device__ __forceinline__ int stage_count(const Work &w, int stage, int b)
 __device__ __forceinline__ PairDesc pair_desc(const Work &w, int b)
 {
     return w.n1 ? pair_desc_of(w.n1, 0, 0, w.pool) : w.pairs[b];
-}
-
-// Ascending bitonic sort of P keys in LDS by one workgroup (P a power of two,
-// P >= 64). Stages with stride >= 64 exchange through LDS; the stages with
-// stride < 64 of each merge run on 64-key blocks held one key per lane and
-// exchanged with wave shuffles, so a merge costs one barrier per LDS stage
-// plus one.
-__device__ inline void bitonic_sort_lds(uint64_t *keys, int P)
-{
-    const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, wv = tid >> 6, nw = nthr >> 6;
-    for (int size = 2; size <= P; size <<= 1) {
-        for (int stride = size >> 1; stride >= 64; stride >>= 1) {
-            for (int t = tid; t < P / 2; t += nthr) {
-                const int lo = 2 * t - (t & (stride - 1)), hi = lo + stride;
-                const bool up = (lo & size) == 0;
-                const uint64_t a = keys[lo], c = keys[hi];
-                if ((a > c) == up) { keys[lo] = c; keys[hi] = a; }
-            }
-            __syncthreads();
-        }
-        for (int blk = wv; blk < P / 64; blk += nw) {
-            const int p = blk * 64 + lane;
-            const bool up = (p & size) == 0;
-            uint64_t key = keys[p];
-            for (int stride = (size >> 1) < 32 ? (size >> 1) : 32; stride >= 1; stride >>= 1) {
-                const uint64_t other = __shfl_xor(key, stride, 64);
-                const bool keep_min = ((lane & stride) == 0) == up;
-                key = keep_min ? (key < other ? key : other) : (key > other ? key : other);
-            }
-            keys[p] = key;
-        }
-        __syncthreads();
-    }
 }
 
 // ---- launchers (one per kernel family); each returns the launch's hipError_t ----

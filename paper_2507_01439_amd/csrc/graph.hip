@@ -519,7 +519,7 @@ __global__ void __launch_bounds__(256) k_compat(Work w)
 // 2^-19 (|x| + |y|) + 2e-6 + 2^-17 q of the nearest bin edge (tau is edge 4; |y| <= |x| + 4 tau there) is
 // evaluated again with the correctly rounded ones, so every bin and bit is the exact one. One workgroup per
 // 64 rows (a quarter of a list item of kPrepRows rows), the 64-column blocks dealt to its waves; the sums
-// are written whole, the SC2 sums cleared for the next kernel.
+// are written whole.
 constexpr int kFeatWaves = 8;
 __global__ void __launch_bounds__(64 * kFeatWaves) k_compat_features(Work w)
 {
@@ -612,7 +612,7 @@ __global__ void __launch_bounds__(64 * kFeatWaves) k_compat_features(Work w)
         const float self = (x.x - x.x) + (x.y - x.y) + (x.z - x.z) + (y.x - y.x) + (y.y - y.y) + (y.z - y.z);   // 0 or NaN
         if (wv == 0) atomicAdd(&hist[self >= q ? 15 : 0][lane], -1);
         __syncthreads();
-        // slots: 0 degree, 1 and 2 the SC2 sum and maximum (added by the next kernel), 3 .. 18 the histogram
+        // slots: 0 degree, 3 .. 18 the histogram, the others padding (the SC2 sum and maximum come as parts)
         int32_t *rs = w.rowstat + ((int64_t)b * w.max_n + i0) * 20;
         for (int k = tid; k < 64 * 20 && i0 + k / 20 < n; k += 64 * kFeatWaves) {
             const int r = k / 20, f = k % 20;

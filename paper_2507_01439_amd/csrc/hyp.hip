@@ -823,7 +823,7 @@ __global__ void __launch_bounds__(64 * NW, 2) k_hyp(Work w, int B, int ppw)
 // order as in k_hyp, so a pose scores the same bits here as there.
 // Bound by the latency of the matches' loads and by the exact root and quotient of the scores: the next group's
 // loads are in flight meanwhile, and a wave without an inlier skips them. 2000 poses on 5000 matches with scores
-// 24.8 -> 16.9 us, 2500 on 20000 114 -> 62, counts only 52.8 -> 30.5 (from eight poses a workgroup and neither).
+// 23.5 -> 15.4 us a call, 2500 on 20000 112 -> 60, counts only 51.8 -> 28.9 (from eight poses a workgroup and neither).
 template <int U, bool SCORE>
 __global__ void __launch_bounds__(256) k_score_poses(const float *src, const float *dst, int n, const float *poses,
                                                      int P, float theta, int metric, int32_t *in_out,

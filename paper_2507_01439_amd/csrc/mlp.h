@@ -33,8 +33,8 @@ hipError_t mlp_grads(MlpState *s, const uint16_t *feat, const uint8_t *labels, i
 hipError_t mlp_train_step(MlpState *s, const uint16_t *feat, const uint8_t *labels, int64_t m, float lr,
                           float *loss, hipStream_t st);
 
-// Features of every pair from the accumulators filled by the compatibility and
-// SC2 kernels; written to w.feat, or packed by match index into `packed`.
+// Features of every pair from the accumulators of the compatibility kernel and the
+// parts of the SC2 kernels; written to w.feat, or packed by match index into `packed`.
 hipError_t launch_features(const Work &w, uint16_t *packed, int grid, hipStream_t st);
 // Learned scores of every match, then the per-pair pivot reorder.
 hipError_t launch_learned_order(const Work &w, const MlpState &mlp, int B, int grid, hipStream_t st);

@@ -86,8 +86,8 @@ __device__ __forceinline__ void sc2_row_parts(const Work &w, const PairDesc &d, 
     }
 }
 
-// 19 values per match from the integer accumulators (degree, SC2 row sum and
-// max, 16-bin delta histogram): ratios formed in float64, rounded to float32,
+// 19 values per match from the integer accumulators (degree, 16-bin delta histogram)
+// and the SC2 kernels' parts (row sum and maximum): ratios formed in float64, rounded to float32,
 // then to bfloat16.
 __global__ void __launch_bounds__(256) k_features(Work w, uint16_t *packed)
 {
@@ -112,11 +112,6 @@ __global__ void __launch_bounds__(256) k_features(Work w, uint16_t *packed)
 }
 
 // ---------------------------------------------------------------- inference + reorder
-
-__device__ __forceinline__ float lane_f(float v, int k)
-{
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k));
-}
 
 // Sum over the 64 lanes (DPP), valid in every lane.
 __device__ __forceinline__ int wave_total(int v)
@@ -576,8 +571,8 @@ constexpr size_t kTrainLds = kStepLds > kSumLds ? kStepLds : kSumLds;
 // contraction on the matrix cores (v_mfma_f32_32x32x16_bf16, float32 sums). The weights, features and
 // activations are bfloat16, so the forward products are exact; the deltas stay float32: each is split
 // into three bfloat16 terms whose sum is the delta itself, and their three products run on the same
-// instruction. Against float64 the gradients' error is a third of the float32 multiply-adds' (1e-7 to 3e-7
-// relative over m = 2125 .. 200000, 4e-7 to 5e-7 before).
+// instruction. Against float64 (samples whose activations round alike on both sides) the gradients are off by 5e-8
+// to 8e-8 relative at m = 1000 .. 200000, the float32 multiply-adds' by 8e-8 to 3.5e-7.
 //
 // Accumulators hold one unit per lane and 16 of the samples, (lane: unit l31 of a 32-block; entry r:
 // sample 8 (r / 4) + 4 lh + r % 4). With deltas and activations in that layout the weight gradients

@@ -29,24 +29,6 @@
 namespace tr {
 namespace {
 
-__device__ __forceinline__ int wave_sum(int v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-__device__ __forceinline__ int wave_excl_scan(int v, int lane)
-{
-    int x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(x, o, 64);
-        if (lane >= o) x += y;
-    }
-    return x - v;
-}
-
 // Inclusive prefix sum over the 64 lanes: shifts by 1, 2, 4, 8 inside each
 // 16-lane row, then the last lane of row 0 is added to row 1 and of row 2 to
 // row 3, then lane 31 to rows 2 and 3 (DPP row_shr / row_bcast, no LDS).
@@ -89,18 +71,6 @@ __device__ T block_exclusive_scan(T v, T *lds, T &total)
 __device__ __forceinline__ uint64_t pivot_key(uint32_t w, uint32_t i, uint32_t j)
 {
     return ((uint64_t)(0xFFFFu - w) << 40) | ((uint64_t)i << 20) | (uint64_t)j;
-}
-
-// Eight consecutive weights G[i][8c .. 8c+7] (rows are 256-byte aligned).
-__device__ __forceinline__ void load8(const uint16_t *row, int c, int (&v)[8])
-{
-    const uint4 q = *reinterpret_cast<const uint4 *>(row + 8 * c);
-    const uint32_t u[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        v[2 * k] = (int)(u[k] & 0xFFFFu);
-        v[2 * k + 1] = (int)(u[k] >> 16);
-    }
 }
 
 constexpr int kMaxFirst = 2048;
@@ -312,8 +282,8 @@ constexpr int kCollectCap = 1024;   // keys a workgroup stages in LDS before its
 // FUSED (a single pair of few matches): every workgroup finds the threshold itself, from the same histograms, in
 // place of a kernel before this one; the first stores it, the last sums the pair's counts. No more workgroups than
 // CUs, as each reads all copies of the histogram. Both kernels / this one alone (us, without the gap between them):
-// N = 300 11.3 / 7.4, N = 1000 11.3 / 7.6, N = 2749 12.1 / 8.1, N = 5000 13.9 / 8.5; a call of 6500 matches
-// 125.4 / 122.3, of 8000 170.9 / 170.9 (both before the largest weight bounded the bins read).
+// N = 300 11.3 / 7.4, N = 1000 11.3 / 7.6, N = 2749 12.1 / 8.1, N = 5000 13.9 / 8.5; whole calls of 5000 matches
+// 87.9 / 84.1, of 8000 169.2 / 164.7, of 10000 264.4 / 262.8, of 13000 468.6 / 472.1.
 template <bool FUSED>
 __global__ void __launch_bounds__(256) k_rowscan(Work w)
 {
@@ -324,7 +294,7 @@ __global__ void __launch_bounds__(256) k_rowscan(Work w)
     __shared__ uint16_t list[4][64 * 16];
     __shared__ SlotCache slots;
     // batches of up to kInfoMax pairs: each slot's threshold, path and sizes in LDS as well, so an
-    // item (four rows) starts with no device-memory round trip but its rows' maxima
+    // item starts with no device-memory round trip but its segments' maxima
     constexpr int kInfoMax = 256;
     struct SlotInfo {
         int32_t alpha, fast, kpiv, n, npad, pad;
