@@ -128,7 +128,8 @@ tr_status tr_register_noalloc(const float *src, const float *dst, int32_t n, con
 /* Register B pairs of uneven size in one pass. Pair b owns matches
  * [offsets[b], offsets[b+1]) of src/dst; offsets_dev is B+1 int32 in device
  * memory, non-decreasing, every N_b <= max_n (host-side bound, <= the handle's).
- * A pair with N_b < 3 or N_b > max_n gets status TR_ERR_INVALID_ARG. out_dev is
+ * A pair with N_b < 3 or N_b > max_n gets status TR_ERR_INVALID_ARG (its mask
+ * entries are 0, or for N_b > max_n left as they are). out_dev is
  * B results; masks_dev (nullable) is offsets[B] uint8. On a stream other than the
  * legacy default one, the launch sequence is captured once into a hipGraph per
  * (pointers, stream, B, max_n, params) and replayed; a handle keeps the 8 most recently

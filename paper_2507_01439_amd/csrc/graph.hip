@@ -122,7 +122,7 @@ __device__ __forceinline__ int snake_slot(int p, int B)
 __global__ void __launch_bounds__(1024) k_plan(const int32_t *offsets, int32_t n_single, int32_t B,
                                                int32_t max_n, int32_t pool, int32_t H, int32_t num_cus, bool sparse,
                                                PairDesc *pairs, PairState *state, Plan *plan,
-                                               int32_t *pre, int32_t pre_stride)
+                                               int32_t *pre, int32_t pre_stride, uint8_t *masks)
 {
     constexpr int NV = kNumPrefix + 1;   // the work-list stages, then the SC2 cost
     __shared__ int64_t lds[17][NV];
@@ -168,6 +168,8 @@ __global__ void __launch_bounds__(1024) k_plan(const int32_t *offsets, int32_t n
             pairs[b] = d;
             PairState st = {};
             st.status = ok ? TR_OK : TR_ERR_INVALID_ARG;
+            if (masks && n < 3)   // no other kernel writes the mask of such a pair
+                for (int k = 0; k < n; ++k) masks[pt + k] = 0;
             state[b] = st;
             atomicAdd(&kfirst[npad / kSc2Tile], 1);
             if (small) nl[b] = ok ? n : 0;
@@ -1313,7 +1315,7 @@ hipError_t launch_plan(const Work &w, const int32_t *offsets, int32_t n_single, 
                        PairDesc *pairs, PairState *state, Plan *plan, int32_t *pre, hipStream_t s)
 {
     hipLaunchKernelGGL(k_plan, dim3(1), dim3(1024), 0, s, offsets, n_single, B, max_n, w.pool, w.H,
-                       num_cus, w.sp_list != nullptr, pairs, state, plan, pre, w.pre_stride);
+                       num_cus, w.sp_list != nullptr, pairs, state, plan, pre, w.pre_stride, w.masks);
     return hipGetLastError();
 }
 
