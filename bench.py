@@ -17,6 +17,7 @@ workloads) the CPU oracle timed on a bounded sample.
 import argparse
 import hashlib
 import json
+import math
 import os
 import platform
 import sys
@@ -30,6 +31,7 @@ PEAK_FP4_TFLOPS = 10100.0   # MI355X dense FP4 MFMA, TFLOP/s (the SC2 product ru
 PEAK_VALU_TOPS = 256 * 64 * 2.4e9 / 1e12   # unpacked float32 vector issue, lane slots / s
 COMPAT_SLOTS_PER_PAIR = 18.0   # minimum vector issue slots of one compatibility evaluation
 PEAK_HBM_GBS = 8000.0       # MI355X HBM3E, GB/s
+PEAK_LDS_TBS = 256 * 128 * 2.4e9 / 1e12   # 128 bytes per clock and CU
 WEIGHTS = os.path.join(ROOT, "paper_2507_01439_amd", "weights", "scorer_indoor.bin")
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA, TFLOP/s (the scorer's training products run on bf16 operands)
 # Scorer training, per sample (19 -> 64 -> 64 -> 1): multiply-adds of the forward pass (5376), of
@@ -322,6 +324,13 @@ def main():
             "traffic": load_counters(f"k_sc2_{args.workload}_traffic.txt")[0],
             "mfma_busy_fraction": load_counters(f"k_sc2_{args.workload}_traffic.txt")[1],
             "avg_launch_us": sc2_ms * 1000.0, "algorithmic_ops_per_launch": sc2_ops}
+    edges = [r.n_edges for r in res[:B]]   # of the first group, as ns_all
+    if tuning.sc2_sparse_cap > 0 and sum(edges) * 2.0 * 65536 <= tuning.sc2_sparse_cap * sum(float(n) * n for n in ns_all):
+        # tiles of few edges count bits: per edge and 128 columns 16 bytes of row j, and of row i once for four edges
+        lds = float(sum(e * math.ceil(n / 128) * 20 for e, n in zip(edges, ns_all)))
+        roof = {"kernel": "k_sc2_sparse (common neighbours per edge, bit rows in LDS)", "bound": "lds",
+                "achieved": lds / (sc2_ms * 1e-3) / 1e12, "peak": PEAK_LDS_TBS, "unit": "TB/s", "traffic": None,
+                "avg_launch_us": sc2_ms * 1000.0, "algorithmic_bytes_per_launch": lds}
     roof["frac"] = roof["achieved"] / roof["peak"]
     # k_compat is bound by vector ALU issue: per pair evaluation six coordinate differences, two
     # squared norms (multiply + two fused multiply-adds each), their sum and difference, two fused
