@@ -255,6 +255,19 @@ __host__ __device__ inline int64_t stage_items(int stage, int32_t n, int32_t H, 
     }
 }
 
+// Pivots per work item of the hypothesis kernel: ppw, less while an item would still make more than one pass of eight
+// poses over the matches and the smaller items all run at once on the `slots` workgroups that the CUs hold (one of eight
+// waves each; two of four for the error rankings). One item more per CU costs a whole second round: whole calls (us) with
+// items in one round / halved again, past it: K1 = 1000, K2 = 8 on N = 300 53.0 / 62.8, on 2749 77.6 / 87.7, on 6000
+// 123.4 / 135.6, 100 pairs of 100 matches, K1 = 32 86.5 / 93.7. Items left larger than that / halved: N = 2749,
+// K1 = 250, K2 = 8 (63 items of 4 pivots, 250 of one) 53 / 32 us of the kernel; MAE ranking, K1 = 550 on N = 2749 (138
+// items of 4, 275 of two) 103.1 / 86.7.
+__host__ __device__ inline int32_t hyp_item_pivots(int32_t B, int32_t k1, int32_t k2, int32_t ppw, int32_t slots)
+{
+    while (ppw > 1 && ppw * k2 > 8 && (int64_t)B * ((k1 + ppw / 2 - 1) / (ppw / 2)) <= slots) ppw /= 2;
+    return ppw;
+}
+
 // Rows per work item (one wave) of the compatibility kernel, for a list of `tiles` tiles: long items
 // amortise the item's loads and transposes, short ones spread a short list over the CUs.
 // Measured at 8 / 16 / 32 / 64 / 128 rows (us): N = 300 6.1 / 6.8 / 9.4, N = 1000 6.0 / 7.3 / 9.8,

@@ -955,13 +955,12 @@ hipError_t setup_hyp_kernels()
     return hipSuccess;
 }
 
-// ppw: pivots per work item, a multiple of 4 up to 16 (the LDS pose slots), less where that leaves CUs idle
-// and an item would still make more than one pass of eight poses over the matches (N = 2749, K1 = 250, K2 = 8:
-// 63 items of 4 pivots 53 us, 250 of one 32); grid: workgroups to launch (capped at the number of items).
+// ppw: pivots per work item, a multiple of 4 up to 16 (the LDS pose slots), at most (hyp_item_pivots); grid:
+// workgroups to launch (capped at the number of items).
 hipError_t launch_hyp(const Work &w, int B, int ppw, int grid, int num_cus, hipStream_t s)
 {
     if (ppw < 4 || ppw > 16 || ppw % 4) return hipErrorInvalidValue;
-    while (ppw > 1 && ppw * w.k2 > 8 && B * ((w.k1 + ppw - 1) / ppw) < num_cus) ppw /= 2;
+    ppw = hyp_item_pivots(B, w.k1, w.k2, ppw, w.metric ? 2 * num_cus : num_cus);
     const int total = B * ((w.k1 + ppw - 1) / ppw);
     grid = max(1, min(total, grid));
     const bool small = w.k2 <= 2;
